@@ -172,6 +172,12 @@ int64_t ktruss(pgabb_graph *g, int32_t k, uint8_t *keep, bool on_device, int32_t
 // bytes; 0: in device memory, or streamed under the cap of the count that
 // moved them to the host.
 uint64_t four_cliques(pgabb_graph *g, uint64_t device_cap_bytes);
+// The 4-cliques whose lowest vertex has at most kQuadRowCap out-edges, from
+// the oriented CSR (clique_rows.hip): counts of every (i, j, k, l) of the
+// graph's stripes, read with quad_rows_count.  Returns the device time in ms.
+constexpr int kQuadRowCap = 1024;
+double quad_rows(pgabb_graph *g, std::vector<uint64_t> &per_list);
+uint64_t quad_rows_count(const std::vector<uint64_t> &per_list, const std::array<int32_t, 4> &q);
 // Moves the device block arena to the pinned host store (once per partition).
 void move_blocks_to_host(pgabb_graph *g);
 // Connected components by Shiloach-Vishkin over the device blocks:

@@ -23,6 +23,11 @@
 // A_il[a] above it, and an entry of A_kl[c] (stripe l, shifted too) can only
 // match a key of A_il[a].  Items whose staged rows hold more than kStageCap
 // entries go to a kernel with one thread per (item, b) and plain merges.
+//
+// In device memory, the vertices with at most kQuadRowCap out-edges are
+// counted from the CSR instead (quad_rows, clique_rows.hip), and the kernels
+// here take the others; a streamed count takes all of them here, from the
+// blocks in its cache.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,7 +47,7 @@ namespace pgabb {
 namespace {
 
 constexpr int kQB = 256;
-constexpr int kStageCap = 1024;  // entries a wave stages (both rows)
+constexpr int kStageCap = kQuadRowCap;  // entries a wave stages (both rows)
 constexpr int kTableLg = 11;     // hash slots of a wave: at most 2^11
 constexpr int kCliqueWaves = 4;
 constexpr int kQuadUnroll = 2;   // walk chunks in flight
@@ -75,8 +80,16 @@ struct QuadDesc {
     int32_t slot;    // counter of the 4-list
     int32_t same;    // k == l: A_il is A_ik and A_jl is A_jk
     int32_t lshift;  // k < l: width of stripe k, added to stripe l's ids in the table; else 0
-    int32_t pad;
+    int32_t base_i;  // rank of stripe i's local row 0
 };
+
+// Whether row a of the edge block's stripe is left to quad_rows (row_off
+// given: only rows of more than kQuadRowCap entries are counted here).
+__device__ __forceinline__ bool quad_left_out(const int64_t *row_off, const QuadDesc &Q, int32_t a) {
+    if (!row_off) return false;
+    const gptr<int64_t> ro = as_global(row_off) + Q.base_i;
+    return ro[a + 1] - ro[a] <= kQuadRowCap;
+}
 
 // Whether a wave stages row a of A_ik (dk entries) and of A_il (dl).
 __device__ __forceinline__ bool quad_staged(int32_t dk, int32_t dl, int32_t same) {
@@ -131,7 +144,8 @@ __global__ __launch_bounds__(kCliqueWaves *kWave) void k_quad_items(const QuadDe
                                                                      int32_t nq,
                                                                      unsigned long long *__restrict__ next,
                                                                      int64_t grab,
-                                                                     unsigned long long *__restrict__ counts) {
+                                                                     unsigned long long *__restrict__ counts,
+                                                                     const int64_t *__restrict__ row_off) {
     __shared__ int32_t s_table[kCliqueWaves][1 << kTableLg];
     __shared__ int32_t s_own[kCliqueWaves][kQuadUnroll * kWave];
     __shared__ int32_t s_gather[kCliqueWaves][2][kWave];  // walked lists: start, length
@@ -177,7 +191,7 @@ __global__ __launch_bounds__(kCliqueWaves *kWave) void k_quad_items(const QuadDe
             const gptr<int32_t> it = as_global(Q.ij.items) + kItemWords * r;
             const int32_t a = it[0];
             const int32_t eb = it[1] + part * kQuadSpan, ee = min(eb + kQuadSpan, it[2]);
-            if (eb >= ee) continue;
+            if (eb >= ee || quad_left_out(row_off, Q, a)) continue;
             const gptr<int32_t> ikr = as_global(Q.ik.rptr), ilr = as_global(Q.il.rptr);
             const int32_t k0 = ikr[a], dk = ikr[a + 1] - k0;
             const int32_t l0 = ilr[a], dl = ilr[a + 1] - l0;
@@ -346,7 +360,8 @@ __device__ __forceinline__ unsigned long long three_way(gptr<int32_t> x, int32_t
 // Items whose staged rows exceed the LDS region: one thread per (item, b).
 __global__ __launch_bounds__(kQB) void k_quad_long(const QuadDesc *__restrict__ quads,
                                                     const int64_t *__restrict__ item_pre, int32_t nq,
-                                                    unsigned long long *__restrict__ counts) {
+                                                    unsigned long long *__restrict__ counts,
+                                                    const int64_t *__restrict__ row_off) {
     const gptr<int64_t> ip = as_global(item_pre);
     const int64_t nitems = ip[nq];
     for (int64_t g = blockIdx.x * int64_t(kQB) + threadIdx.x; g < nitems * kQuadSpan;
@@ -359,7 +374,7 @@ __global__ __launch_bounds__(kQB) void k_quad_long(const QuadDesc *__restrict__ 
         const int32_t part = static_cast<int32_t>((q - ip[t]) - r * kQuadParts);
         const gptr<int32_t> it = as_global(Q.ij.items) + kItemWords * r;
         const int32_t a = it[0], e = it[1] + part * kQuadSpan + rb;
-        if (e >= it[2] || rb + part * kQuadSpan >= kSplitV) continue;
+        if (e >= it[2] || rb + part * kQuadSpan >= kSplitV || quad_left_out(row_off, Q, a)) continue;
         const gptr<int32_t> ikr = as_global(Q.ik.rptr), ilr = as_global(Q.il.rptr);
         const int32_t k0 = ikr[a], dk = ikr[a + 1] - k0;
         const int32_t l0 = ilr[a], dl = ilr[a + 1] - l0;
@@ -426,10 +441,10 @@ BlockRef quad_ref(const BlockInfo &bi, const int32_t *base) {
 
 // Counts the 4-lists lists[first, last) (their blocks at the given device
 // bases), adding to dcnt[slot]; dcnt[NQ .. NQ + kQuadQueues) are the work
-// counters.
+// counters.  over_cap: only rows of more than kQuadRowCap entries.
 void quad_launch(pgabb_graph *g, const std::vector<std::array<int32_t, 4>> &lists, int32_t first, int32_t last,
-                 const std::vector<const int32_t *> &base, unsigned long long *dcnt, int32_t NQ, double &kernel_ms,
-                 int64_t &launches) {
+                 const std::vector<const int32_t *> &base, unsigned long long *dcnt, int32_t NQ, bool over_cap,
+                 double &kernel_ms, int64_t &launches) {
     hipStream_t s = g->stream;
     const int32_t p = g->p;
     const int32_t W = last - first;
@@ -451,7 +466,7 @@ void quad_launch(pgabb_graph *g, const std::vector<std::array<int32_t, 4>> &list
         d.slot = first + q;
         d.same = L[2] == L[3];
         d.lshift = d.same ? 0 : g->cuts[L[2] + 1] - g->cuts[L[2]];
-        d.pad = 0;
+        d.base_i = g->base[L[0]];
         hpre[q + 1] = hpre[q] + static_cast<int64_t>(kQuadParts) * g->blocks[b6[0]].nitems;
     }
     const int64_t nitems = hpre[W];
@@ -464,21 +479,25 @@ void quad_launch(pgabb_graph *g, const std::vector<std::array<int32_t, 4>> &list
     // some row too long to stage (with p > 1, two rows of a 4-list may
     // share the table)
     const bool long_rows = (p == 1 ? max_row : 2 * max_row) > kStageCap;
+    // in one block, a row over kQuadRowCap (= kStageCap) entries is never staged
+    const bool staged_rows = !(over_cap && p == 1);
+    const int64_t *row_off = over_cap ? g->row_off.get() : nullptr;
     StreamTimer tm;
     tm.start(s);
     const unsigned grid =
         static_cast<unsigned>(std::min<int64_t>(256 * 4, (nitems + kCliqueWaves - 1) / kCliqueWaves));
     int64_t grab = kQuadGrabMin;
     while (grab < kQuadGrabMax && nitems / (grab * 2) >= kQuadGrabsPerWave * grid * kCliqueWaves) grab *= 2;
-    k_quad_items<<<grid, kCliqueWaves * kWave, 0, s>>>(dq.get(), dpre.get(), W, dcnt + NQ, grab, dcnt);
+    if (staged_rows)
+        k_quad_items<<<grid, kCliqueWaves * kWave, 0, s>>>(dq.get(), dpre.get(), W, dcnt + NQ, grab, dcnt, row_off);
     if (long_rows)
         k_quad_long<<<std::min<unsigned>(grid_for(nitems * kQuadSpan, kQB), 256u * 16u), kQB, 0, s>>>(
-            dq.get(), dpre.get(), W, dcnt);
+            dq.get(), dpre.get(), W, dcnt, row_off);
     PGABB_HIP(hipGetLastError());
     tm.stop(s);
     PGABB_HIP(hipStreamSynchronize(s));  // the descriptors and the blocks may go once this returns
     kernel_ms += tm.ms();
-    launches += long_rows ? 2 : 1;
+    launches += (staged_rows ? 1 : 0) + (long_rows ? 1 : 0);
 }
 
 }  // namespace
@@ -527,10 +546,15 @@ uint64_t four_cliques(pgabb_graph *g, uint64_t device_cap_bytes) {
         double kernel_ms = 0;
         int64_t launches = 0;
         const bool streamed = device_cap_bytes > 0 || g->blocks_on_host;
+        std::vector<uint64_t> per_list;  // in core: the rows quad_rows counts
         if (!streamed) {
-            std::vector<const int32_t *> base(nblk);
-            for (int32_t b = 0; b < nblk; ++b) base[b] = g->arena.get() + g->blocks[b].walk_lo(kOrientRow);
-            quad_launch(g, g->quads, 0, NQ, base, dcnt.get(), NQ, kernel_ms, launches);
+            kernel_ms += quad_rows(g, per_list);
+            ++launches;
+            if (g->max_out > kQuadRowCap) {
+                std::vector<const int32_t *> base(nblk);
+                for (int32_t b = 0; b < nblk; ++b) base[b] = g->arena.get() + g->blocks[b].walk_lo(kOrientRow);
+                quad_launch(g, g->quads, 0, NQ, base, dcnt.get(), NQ, true, kernel_ms, launches);
+            }
         } else {
             // ---- streamed: the blocks move from the host store through a
             // cache of at most `cap` bytes.  Consecutive 4-lists form a
@@ -635,7 +659,7 @@ uint64_t four_cliques(pgabb_graph *g, uint64_t device_cap_bytes) {
                     lru.clear();
                     rp = RangePool(cap);
                 }
-                quad_launch(g, g->quads, q, e, base, dcnt.get(), NQ, kernel_ms, launches);
+                quad_launch(g, g->quads, q, e, base, dcnt.get(), NQ, false, kernel_ms, launches);
                 q = e;
                 ++win;
             }
@@ -644,7 +668,9 @@ uint64_t four_cliques(pgabb_graph *g, uint64_t device_cap_bytes) {
         PGABB_HIP(hipMemcpyAsync(h.get(), dcnt.get(), h.bytes(), hipMemcpyDeviceToHost, s));
         PGABB_HIP(hipStreamSynchronize(s));
         g->quad_counts.assign(h.get(), h.get() + NQ);
-        for (int32_t x = 0; x < NQ; ++x) result += h[x];
+        if (!per_list.empty())
+            for (int32_t x = 0; x < NQ; ++x) g->quad_counts[x] += quad_rows_count(per_list, g->quads[x]);
+        for (int32_t x = 0; x < NQ; ++x) result += g->quad_counts[x];
         g->t_kernel_ms = kernel_ms;
         g->kernel_launches = launches;
     }
