@@ -118,7 +118,8 @@ typedef struct pgabb_tc_options {
                                   streaming) */
     int32_t unroll;            /* 64-element chunks of walked lists per load
                                   batch (the next batch loads while one is
-                                  probed): 1, 2, 4 or 8 (0 = 2) */
+                                  probed): 1, 2, 4 or 8 (0 = 4; 1 and 2 run
+                                  as 4, the entries of one load per lane) */
     int32_t host_threads;      /* PGABB_OPT_HYBRID only: host threads that
                                   count the light tasks (0 = one per core,
                                   at most 64) */

@@ -257,13 +257,11 @@ struct BatchArgs {
 
 template <int MODE, int LDS_WORDS, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void k_tc_batch(BatchArgs a) {
-    __shared__ int32_t lds_all[WAVES][LDS_WORDS];
-    __shared__ int32_t own_all[WAVES][2 * kWave];  // the walk's list positions (two chunks in flight)
+    __shared__ int32_t lds_all[WAVES][LDS_WORDS + kWave];  // staged list, then the walk's list positions
     const int lane = lane_id();
     int32_t *lds = lds_all[threadIdx.x >> 6];
-    int32_t *own = own_all[threadIdx.x >> 6];
+    int32_t *own = lds + LDS_WORDS;
     own[lane] = 0;
-    own[kWave + lane] = 0;
     wave_lds_sync();
     if (MODE == kModeBitmap) {
         for (int q = lane; q < LDS_WORDS; q += kWave) lds[q] = 0;
@@ -313,7 +311,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_batch(BatchArgs a) {
                 cnt = 0;
                 gcur = gid;
             }
-            cnt += tiny_items<2>(mg, h_sb, h_se, h_sb, h_se, a.col, a.col, a.rptr, a.col, own, lane);
+            cnt += tiny_items<1>(mg, h_sb, h_se, h_sb, h_se, a.col, a.col, a.rptr, a.col, own, lane);
         }
         while (rest) {
             const int l = __builtin_ctzll(rest);
@@ -327,7 +325,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_batch(BatchArgs a) {
             }
             const int32_t sb = __builtin_amdgcn_readlane(h_sb, l), se = __builtin_amdgcn_readlane(h_se, l);
             cnt += tc_item_core<MODE, LDS_WORDS>(a.col, sb, se, a.rptr, a.col, a.col, sb, se,
-                                                 __builtin_amdgcn_readlane(h_nv, l), lds, own,
+                                                 __builtin_amdgcn_readlane(h_nv, l), lds,
                                                  __builtin_amdgcn_readlane(h_vb, l));
         }
         const unsigned long long s = wave_sum(static_cast<unsigned long long>(cnt));
@@ -596,7 +594,7 @@ void batch_build(pgabb_batch *b, const int32_t *n, const int64_t *eoff, const in
             k_orient_b<<<cap_grid(mu), B, 0, s>>>(k0, mu, nb, b->dvbase.get(), rank.get(), k1);
             PGABB_HIP(hipGetLastError());
             if (radix_sort_u64_bits(k1, k0, nullptr, nullptr, mu, 0, kbits, s)) std::swap(k0, k1);
-            b->col.reset(mu, s);
+            b->col.reset(mu + kSeg, s);  // walked in segments, which may reach past the last list
             k_union_csr_b<<<cap_grid(mu), B, 0, s>>>(k1, mu, nb, b->dvbase.get(),
                                                      reinterpret_cast<int32_t *>(outdeg.get()), b->col.get());
             PGABB_HIP(hipGetLastError());

@@ -105,31 +105,26 @@ int choose_lds_words(int32_t mode, int32_t max_stage_len, int32_t max_width_k) {
 
 namespace {
 
-// A launch of a split pair: the default shape (four waves, two chunks per
-// batch), items filtered by staged list length.
+// A launch of a split pair: the default shape (four waves, one segment per
+// lane and batch), items filtered by staged list length.
 void launch_filtered(const CountArgs &a, int mode, int lds_words, hipStream_t s, int grid_override) {
     if (mode == kModeBitmap) {
-        if (lds_words <= 1280) launch_one<kModeBitmap, 1280, 4, 2, true>(a, s, grid_override);
-        else if (lds_words <= 2304) launch_one<kModeBitmap, 2304, 4, 2, true>(a, s, grid_override);
-        else launch_one<kModeBitmap, 4352, 4, 2, true>(a, s, grid_override);
+        if (lds_words <= 1280) launch_one<kModeBitmap, 1280, 4, 1, true>(a, s, grid_override);
+        else if (lds_words <= 2304) launch_one<kModeBitmap, 2304, 4, 1, true>(a, s, grid_override);
+        else launch_one<kModeBitmap, 4352, 4, 1, true>(a, s, grid_override);
     } else {
-        if (lds_words <= 1280) launch_one<kModeHash, 1280, 4, 2, true>(a, s, grid_override);
-        else if (lds_words <= 2304) launch_one<kModeHash, 2304, 4, 2, true>(a, s, grid_override);
-        else launch_one<kModeHash, 4352, 4, 2, true>(a, s, grid_override);
+        if (lds_words <= 1280) launch_one<kModeHash, 1280, 4, 1, true>(a, s, grid_override);
+        else if (lds_words <= 2304) launch_one<kModeHash, 2304, 4, 1, true>(a, s, grid_override);
+        else launch_one<kModeHash, 4352, 4, 1, true>(a, s, grid_override);
     }
 }
 
 void launch_one(const CountArgs &a, int mode, int lds_words, int waves, hipStream_t s, int grid_override,
                 int unroll) {
-    // default 2: with the next batch loading while one is probed, two chunks
-    // per batch keep four loads in flight per wave within 64 VGPRs (eight
-    // waves per SIMD)
-    switch (unroll) {
-        case 1: launch_mode<1>(a, mode, lds_words, waves, s, grid_override); break;
-        case 4: launch_mode<4>(a, mode, lds_words, waves, s, grid_override); break;
-        case 8: launch_mode<8>(a, mode, lds_words, waves, s, grid_override); break;
-        default: launch_mode<2>(a, mode, lds_words, waves, s, grid_override); break;
-    }
+    // default: one 4-entry segment per lane and batch (the next batch loads
+    // while one is probed); the option counts 64-entry chunks
+    if (unroll == 8) launch_mode<2>(a, mode, lds_words, waves, s, grid_override);
+    else launch_mode<1>(a, mode, lds_words, waves, s, grid_override);
 }
 
 
@@ -608,8 +603,8 @@ void count_graphs(pgabb_graph *const *gs, int64_t G, const pgabb_tc_options &opt
                     const MergedTasks mt = merge_tasks(gs, kv.second, orient);
                     MergedLaunch ml(mt, opt, orient, s);
                     const int gr = ml.default_grab_();
-                    ml.run(4, gr, 2);  // warm
-                    const double ms = std::min(ml.run(4, gr, 2), ml.run(4, gr, 2));
+                    ml.run(4, gr, 0);  // warm
+                    const double ms = std::min(ml.run(4, gr, 0), ml.run(4, gr, 0));
                     if (ms < best) {
                         best = ms;
                         bp = kGridP[c];
@@ -663,7 +658,7 @@ void count_graphs(pgabb_graph *const *gs, int64_t G, const pgabb_tc_options &opt
             double best = 1e30;
             for (int w : {2, 4, 8})
                 for (int gr : {std::max(1, g0 / 2), g0, std::min(64, 2 * g0)})
-                    for (int un : {2, 4}) {
+                    for (int un : {4, 8}) {
                         ml.run(w, gr, un);  // warm
                         const double ms = std::min(ml.run(w, gr, un), ml.run(w, gr, un));
                         if (ms < best) {

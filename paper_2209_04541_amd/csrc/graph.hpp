@@ -33,6 +33,8 @@ namespace pgabb {
 // the partition fills the chunk and are not kept.
 constexpr int32_t kSplitV = 32;
 constexpr int32_t kItemWords = 3;
+// Entries of a walked list that one lane loads at a time (see tc_device.hpp).
+constexpr int kSeg = 4;
 
 // Which list of a block-list edge (u, v) is staged in LDS: the row u of A_ik
 // (the edge block is walked by rows) or the row v of A_jk (walked by

@@ -107,6 +107,47 @@ __device__ __forceinline__ int32_t quad_of(gptr<int64_t> pre, int32_t nq, int64_
     return lo;
 }
 
+// Loads elements base + q * 64 + lane (q < UNROLL) of the flattened walk over
+// the lists of one group of up to 64 ids (lane l: list wk_col[pb .. pb +
+// len), at position pre of the walk); past the group's end a lane gets -1.
+// The lane whose list holds an element is found without a search: every
+// list that starts inside the batch writes its lane + 1 at its first
+// position in `own` (64 * UNROLL words of the wave's LDS, zero between
+// calls, and left zero), and a running maximum over the lanes fills the
+// positions in between; `carry` (lane + 1 of the list holding the element
+// before the batch) starts at 0 for a new group.  Walked lists are short
+// next to a batch on skewed graphs (a batch often crosses several), where
+// advancing one list per step cost more.  Every call issues exactly UNROLL
+// loads (past the end, of element 0 of wk_col, which exists whenever a walk
+// does), so the compiler can wait for one batch while the next is in
+// flight.
+template <int UNROLL>
+__device__ __forceinline__ void quad_walk_load(int32_t (&w)[UNROLL], int32_t base, int32_t total, int32_t pre,
+                                          int32_t len, int32_t pb, uint32_t &carry, int32_t *__restrict__ own,
+                                          gptr<int32_t> wk_col, int lane) {
+    const int32_t p = pre - base;
+    if (len > 0 && p >= 0 && p < UNROLL * kWave) own[p] = lane + 1;
+    wave_lds_sync();
+    uint32_t o[UNROLL];
+#pragma unroll
+    for (int q = 0; q < UNROLL; ++q) {
+        o[q] = static_cast<uint32_t>(own[q * kWave + lane]);
+        own[q * kWave + lane] = 0;
+    }
+    wave_lds_sync();
+    const int32_t rel = pb - pre;  // element e of the walk is wk_col[rel + e] for the lane's list
+#pragma unroll
+    for (int q = 0; q < UNROLL; ++q) {
+        const uint32_t sl = max(wave_max_scan_dpp(o[q]), carry);
+        carry = __builtin_amdgcn_readlane(sl, kWave - 1);
+        const int32_t e = base + q * kWave + lane;
+        const bool inb = e < total;
+        const int32_t off = __shfl(rel, static_cast<int>(sl) - 1);
+        const int32_t x = wk_col[inb ? off + e : 0];
+        w[q] = inb ? x : -1;
+    }
+}
+
 // Marks the entries of the sorted list x[0, n) found in the table, each
 // looked up as its id plus `add` (ids above top cannot be there), sets the
 // marked slots' bits in `bits`, and returns how many it marked (the same on
@@ -252,11 +293,11 @@ __global__ __launch_bounds__(kCliqueWaves *kWave) void k_quad_items(const QuadDe
                     if (total == 0) return;
                     uint32_t carry = 0;
                     int32_t w[kQuadUnroll];
-                    walk_load<kQuadUnroll>(w, 0, total, pre, len, pb, carry, own, klc, lane);
+                    quad_walk_load<kQuadUnroll>(w, 0, total, pre, len, pb, carry, own, klc, lane);
                     for (int32_t base = 0; base < total; base += kQuadUnroll * kWave) {
                         int32_t wn[kQuadUnroll];
-                        walk_load<kQuadUnroll>(wn, base + kQuadUnroll * kWave, total, pre, len, pb, carry, own, klc,
-                                               lane);
+                        quad_walk_load<kQuadUnroll>(wn, base + kQuadUnroll * kWave, total, pre, len, pb, carry, own, klc,
+                                                    lane);
 #pragma unroll
                         for (int u = 0; u < kQuadUnroll; ++u) {
                             bool go = w[u] >= 0 && w[u] <= topl;

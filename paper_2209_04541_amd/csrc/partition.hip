@@ -694,7 +694,8 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
             }
         }
         const int32_t nblk = static_cast<int32_t>(g->blocks.size());
-        g->arena.reset(static_cast<size_t>(g->arena_words), s);
+        // (walked lists are read in segments, which may reach past the last list)
+        g->arena.reset(static_cast<size_t>(g->arena_words) + kSeg, s);
         // the transposes' dense column offsets, needed only while the chunks
         // are filled
         std::vector<int64_t> coff(static_cast<size_t>(nblk) + 1, 0);

@@ -184,7 +184,8 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
     for (auto &x : cs) PGABB_HIP(hipStreamCreateWithFlags(&x, hipStreamNonBlocking));
 
     // device pool and per-run arrays
-    DArray<uint8_t> pool(static_cast<size_t>(cap), s);
+    // (walked lists are read in segments, which may reach past the last list)
+    DArray<uint8_t> pool(static_cast<size_t>(cap) + kSeg * sizeof(int32_t), s);
     DArray<TaskDesc> ddesc(static_cast<size_t>(T), s);
     DArray<int64_t> dpre(static_cast<size_t>(2 * T + 1), s);
     // counts, then kQueues work counters per window (at most T windows)

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kSupB) void k_sup_widen(const int32_t *__restrict__
 // in-edge lists of the group (lane l: positions pb .. pb + len of the column
 // array, at position pre of the walk), with their column positions and the
 // lane whose list holds each; past total a lane gets value -1.  Lists are
-// found as in walk_load: list starts scattered into `own`, then a running
+// found as in walk_load (tc_device.hpp): list starts scattered into `own`, then a running
 // maximum over the lanes.
 template <int U>
 __device__ __forceinline__ void sup_walk_load(int32_t (&w)[U], uint32_t (&ev)[U], int32_t (&sl)[U], int32_t base,

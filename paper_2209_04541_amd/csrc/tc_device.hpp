@@ -70,26 +70,48 @@ struct Staging {
     int32_t *table = nullptr;   // hash table, after the filter
 };
 
-// Loads elements base + q * 64 + lane (q < UNROLL) of the flattened walk over
-// the lists of one group of up to 64 ids (lane l: list wk_col[pb .. pb +
-// len), at position pre of the walk); past the group's end a lane gets -1.
-// The lane whose list holds an element is found without a search: every
-// list that starts inside the batch writes its lane + 1 at its first
-// position in `own` (64 * UNROLL words of the wave's LDS, zero between
-// calls, and left zero), and a running maximum over the lanes fills the
-// positions in between; `carry` (lane + 1 of the list holding the element
-// before the batch) starts at 0 for a new group.  Walked lists are short
-// next to a batch on skewed graphs (a batch often crosses several), where
-// advancing one list per step cost more.  Every call issues exactly UNROLL
-// loads (past the end, of element 0 of wk_col, which exists whenever a walk
-// does), so the compiler can wait for one batch while the next is in
-// flight.
+// Walked lists are read in segments of kSeg consecutive entries, one per lane
+// and load: finding the list that holds an entry takes about 25 instructions
+// per lane, which a segment shares among its entries, and the load is one 16
+// byte access.  The last segment of a list may be partial; its load then
+// reads past the list (at most kSeg - 1 words), so the arrays that lists lie
+// in are allocated kSeg words longer.  Kernel ms, one entry per lane against
+// segments (with the cut to `after` below): R-MAT scale 20 in 8 x 8 blocks
+// 2.35 -> 1.75, in one block 4.48 -> 3.01, in 32 x 32 4.18 -> 2.79; scale 22
+// in 8 x 8 13.8 -> 9.76; 777 small graphs 1.35 -> 0.94.  At 8 x 8 the vector
+// units are then busy 56 % of the time and 10.7 GB cross from the fabric to
+// the L2s (6 TB/s): the lists' lines bound it as much as the instructions.
+typedef int32_t seg_t __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ int32_t segs_of(int32_t len) { return (len + kSeg - 1) / kSeg; }
+
+// One load batch: UNROLL segments per lane, n[q] valid entries in each (none
+// when n[q] <= 0).
 template <int UNROLL>
-__device__ __forceinline__ void walk_load(int32_t (&w)[UNROLL], int32_t base, int32_t total, int32_t pre,
-                                          int32_t len, int32_t pb, uint32_t &carry, int32_t *__restrict__ own,
-                                          gptr<int32_t> wk_col, int lane) {
+struct SegBatch {
+    seg_t v[UNROLL];
+    int32_t n[UNROLL];
+};
+
+// Loads segments base + q * 64 + lane (q < UNROLL) of the flattened walk over
+// the lists of one group of up to 64 lanes (lane l: wk_col[pb .. end), nseg
+// segments from position pre of the walk), and for each the lane whose list
+// holds it (src).  That lane is found without a search: every list that
+// starts inside the batch writes its lane + 1 at its first position in `own`
+// (64 * UNROLL words of the wave's LDS, zero between calls, and left zero),
+// and a running maximum over the lanes fills the positions in between;
+// `carry` (lane + 1 of the list holding the segment before the batch) starts
+// at 0 for a new group.  Every call issues exactly UNROLL loads (past the
+// end, of the first words of wk_col, which exist whenever a walk does), so
+// the compiler can wait for one batch while the next is in flight; the
+// entries past a list's end are masked when they are probed, not here, for
+// the same reason.
+template <int UNROLL>
+__device__ __forceinline__ void walk_load(SegBatch<UNROLL> &B, int (&src)[UNROLL], int32_t base, int32_t total,
+                                          int32_t pre, int32_t nseg, int32_t pb, int32_t end, uint32_t &carry,
+                                          int32_t *__restrict__ own, gptr<int32_t> wk_col, int lane) {
     const int32_t p = pre - base;
-    if (len > 0 && p >= 0 && p < UNROLL * kWave) own[p] = lane + 1;
+    if (nseg > 0 && p >= 0 && p < UNROLL * kWave) own[p] = lane + 1;
     wave_lds_sync();
     uint32_t o[UNROLL];
 #pragma unroll
@@ -98,16 +120,18 @@ __device__ __forceinline__ void walk_load(int32_t (&w)[UNROLL], int32_t base, in
         own[q * kWave + lane] = 0;
     }
     wave_lds_sync();
-    const int32_t rel = pb - pre;  // element e of the walk is wk_col[rel + e] for the lane's list
+    const int32_t rel = pb - kSeg * pre;  // segment s of the walk starts at wk_col[rel + kSeg s] for the lane's list
 #pragma unroll
     for (int q = 0; q < UNROLL; ++q) {
         const uint32_t sl = max(wave_max_scan_dpp(o[q]), carry);
         carry = __builtin_amdgcn_readlane(sl, kWave - 1);
-        const int32_t e = base + q * kWave + lane;
-        const bool inb = e < total;
-        const int32_t off = __shfl(rel, static_cast<int>(sl) - 1);
-        const int32_t x = wk_col[inb ? off + e : 0];
-        w[q] = inb ? x : -1;
+        const int32_t s = base + q * kWave + lane;
+        src[q] = static_cast<int>(sl) - 1;
+        const int32_t at = __shfl(rel, src[q]) + kSeg * s;
+        const int32_t left = __shfl(end, src[q]) - at;
+        const bool inb = s < total;
+        B.n[q] = inb ? left : 0;
+        B.v[q] = *reinterpret_cast<const __attribute__((address_space(1))) seg_t *>(wk_col + (inb ? at : 0));
     }
 }
 
@@ -165,41 +189,29 @@ __device__ __forceinline__ uint32_t tiny_items(uint64_t m, int32_t b, int32_t e,
             pb = wk_rptr[id];
             len = wk_rptr[id + 1] - pb;
         }
-        // the elements of these lists, flattened over the lanes
-        const int32_t incl = wave_inclusive_scan(len);
-        const int32_t pre = incl - len;
+        // the segments of these lists, flattened over the lanes
+        const int32_t nseg = segs_of(len);
+        const int32_t incl = wave_inclusive_scan(nseg);
+        const int32_t pre = incl - nseg;
         const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
-        const int32_t rel = pb - pre;  // element x of the run is wk_col[rel + x] for the lane's list
         uint32_t carry = 0;
         for (int32_t base = 0; base < total; base += UNROLL * kWave) {
-            const int32_t p2 = pre - base;
-            if (len > 0 && p2 >= 0 && p2 < UNROLL * kWave) own[p2] = lane + 1;
-            wave_lds_sync();
-            uint32_t o2[UNROLL];
+            SegBatch<UNROLL> B;
+            int src[UNROLL];
+            walk_load<UNROLL>(B, src, base, total, pre, nseg, pb, pb + len, carry, own, wk_col, lane);
 #pragma unroll
             for (int q = 0; q < UNROLL; ++q) {
-                o2[q] = static_cast<uint32_t>(own[q * kWave + lane]);
-                own[q * kWave + lane] = 0;
-            }
-            wave_lds_sync();
-            int32_t y[UNROLL], sl[UNROLL];
+                int32_t sv[kTinyCap];
 #pragma unroll
-            for (int q = 0; q < UNROLL; ++q) {
-                const uint32_t sl1 = max(wave_max_scan_dpp(o2[q]), carry);
-                carry = __builtin_amdgcn_readlane(sl1, kWave - 1);
-                sl[q] = static_cast<int>(sl1) - 1;
-                const int32_t x = base + q * kWave + lane;
-                const bool inb = x < total;
-                const int32_t off = __shfl(rel, sl[q]);
-                const int32_t v = wk_col[inb ? off + x : 0];
-                y[q] = inb ? v : -1;
-            }
+                for (int x = 0; x < kTinyCap; ++x) sv[x] = __shfl(ls[x], src[q]);
 #pragma unroll
-            for (int q = 0; q < UNROLL; ++q) {
-                uint32_t hit = 0;
+                for (int r = 0; r < kSeg; ++r) {
+                    if (__ballot(r < B.n[q]) == 0) break;  // lists of a few entries
+                    bool hit = false;
 #pragma unroll
-                for (int t = 0; t < kTinyCap; ++t) hit |= y[q] == __shfl(ls[t], sl[q]) ? 1u : 0u;
-                cnt += hit;
+                    for (int x = 0; x < kTinyCap; ++x) hit |= B.v[q][r] == sv[x];
+                    cnt += (hit && r < B.n[q]) ? 1u : 0u;
+                }
             }
         }
     }
@@ -212,44 +224,58 @@ __device__ __forceinline__ uint32_t tiny_items(uint64_t m, int32_t b, int32_t e,
 constexpr int kPackS = 64;
 constexpr int kPackLists = 8;
 
-// Hash slot of value w of the pack's item il (the item enters the key, so
-// equal values of different items fall apart).
-__device__ __forceinline__ uint32_t pack_slot(int32_t w, int il, int shift, uint32_t mask) {
-    return hash_slot(w + il * 0x3C6EF35, shift, mask);
+// Staged entries that a pack may hold in a region of LDS_WORDS words (table
+// load <= 1/2).
+template <int LDS_WORDS>
+constexpr int kPackEntries = HashLds<LDS_WORDS>::kTableCap / 2;
+
+// Items of one pack over a stripe of `width` columns: the item's number and
+// the entry share a 32-bit key.
+__device__ __forceinline__ int pack_items(int32_t width) {
+    return width < (1 << 26) ? kWave : 1 << (__clz(width) > 0 ? __clz(width) : 0);
 }
 
 // Counts the items of the lanes in `m` (one task; lane l: ids[b .. e) are
 // its walked lists' ids, st_col[sb .. se) its staged list) in one walk: the
 // items' staged lists go into one open-addressing table in the wave's LDS
-// region, each entry with its item's lane as a tag (the table in the hash
-// table words, the tags as bytes in the filter words; at most kPackSlots
-// slots, load <= 1/2, so the items' staged entries must sum to at most half
-// of that); the walked lists are then flattened as in tiny_items and each
-// element probes the table with its list's item.  The region is left zero
-// (what bitmap kernels expect; hash staging clears what it uses).
-template <int UNROLL, int LDS_WORDS>
+// region behind a bit filter, as in tc_item_core, each entry keyed with its
+// item's number (lane - first lane of m, below pack_items(width_k)); the
+// walked lists are then flattened as in tiny_items and each entry probes with
+// its list's item.  A key is never 0, the empty slot.  The used part of the
+// region is zeroed: before the pack when hash staging left it (MODE hash),
+// after it where bitmap staging expects zeros.
+template <int MODE, int UNROLL, int LDS_WORDS>
 __device__ __forceinline__ uint32_t packed_items(uint64_t m, int32_t b, int32_t e, int32_t sb, int32_t se,
                                                  const int32_t *st_col_, const int32_t *ids_,
-                                                 const int32_t *wk_rptr_, const int32_t *wk_col_,
+                                                 const int32_t *wk_rptr_, const int32_t *wk_col_, int32_t width_k,
                                                  int32_t *__restrict__ lds, int32_t *own, int lane) {
     constexpr int FC = HashLds<LDS_WORDS>::kFilterCap;
-    constexpr int kPackSlots = HashLds<LDS_WORDS>::kTableCap < 4 * FC ? HashLds<LDS_WORDS>::kTableCap : 4 * FC;
-    int32_t *table = lds + FC;
-    uint8_t *tag = reinterpret_cast<uint8_t *>(lds);
+    uint32_t *table = reinterpret_cast<uint32_t *>(lds) + FC;
+    uint32_t *filter = reinterpret_cast<uint32_t *>(lds);
     const gptr<int32_t> st_col = as_global(st_col_), ids = as_global(ids_);
     const gptr<int32_t> wk_rptr = as_global(wk_rptr_), wk_col = as_global(wk_col_);
     const bool in = (m >> lane) & 1ull;
-    // ---- stage every item's list, tagged with the item's lane
+    const int first = __builtin_ctzll(m);
+    const int kshift = width_k < (1 << 26) ? 26 : 32 - __clz(width_k);
+    // ---- stage every item's list
     const int32_t ns = in ? se - sb : 0;
     const int32_t incls = wave_inclusive_scan(ns);
     const int32_t pres = incls - ns;
     const int32_t nsum = __builtin_amdgcn_readlane(incls, kWave - 1);
     int lg = 6;
-    while ((1 << lg) < 2 * nsum && (1 << lg) < kPackSlots) ++lg;
-    const uint32_t tmask = (1u << lg) - 1u;
-    const int shift = 24 - lg;
-    for (int q = lane; q < (1 << lg); q += kWave) table[q] = -1;
-    wave_lds_sync();
+    while ((1 << lg) < 2 * nsum) ++lg;  // at most kTableCap (nsum <= kPackEntries)
+    int flg = 8;
+    while ((1 << flg) < 16 * nsum && (1 << flg) < 32 * FC) ++flg;
+    while ((1 << flg) > 32 * FC) --flg;
+    const uint32_t tmask = (1u << lg) - 1u, fmask = (1u << flg) - 1u;
+    const int shift = 24 - lg, fshift = 24 - flg;
+    auto clear = [&]() {
+        wave_lds_sync();
+        for (int q = lane; q < (1 << lg); q += kWave) table[q] = 0u;
+        for (int q = lane; q < (1 << flg) / 32; q += kWave) filter[q] = 0u;
+        wave_lds_sync();
+    };
+    if (MODE != kModeBitmap) clear();
     const int32_t sbase = sb - pres;  // staged entry k of the item is st_col[sbase + k]
     uint32_t carry0 = 0;
     for (int32_t k0 = 0; k0 < nsum; k0 += kWave) {
@@ -266,9 +292,13 @@ __device__ __forceinline__ uint32_t packed_items(uint64_t m, int32_t b, int32_t 
         const int32_t base_k = __shfl(sbase, il);
         if (k < nsum) {
             const int32_t v = st_col[base_k + k];
-            uint32_t h = pack_slot(v, il, shift, tmask);
-            while (atomicCAS(&table[h], -1, v) != -1) h = (h + 1) & tmask;
-            tag[h] = static_cast<uint8_t>(il);
+            const uint32_t item = static_cast<uint32_t>(il - first);
+            const uint32_t key = ((item << kshift) | static_cast<uint32_t>(v)) + 1u;
+            const int32_t hv = v + static_cast<int32_t>(item) * 0x3C6EF35;  // the item enters the hash
+            const uint32_t f = filter_slot(hv, fshift, fmask);
+            atomicOr(&filter[f >> 5], 1u << (f & 31));
+            uint32_t h = hash_slot(hv, shift, tmask);
+            while (atomicCAS(&table[h], 0u, key) != 0u) h = (h + 1) & tmask;
         }
     }
     wave_lds_sync();
@@ -298,120 +328,141 @@ __device__ __forceinline__ uint32_t packed_items(uint64_t m, int32_t b, int32_t 
             pb = wk_rptr[id];
             len = wk_rptr[id + 1] - pb;
         }
-        const int32_t incl = wave_inclusive_scan(len);
-        const int32_t pre = incl - len;
+        const int32_t nseg = segs_of(len);
+        const int32_t incl = wave_inclusive_scan(nseg);
+        const int32_t pre = incl - nseg;
         const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
-        const int32_t rel = pb - pre;
         uint32_t carry = 0;
         for (int32_t base = 0; base < total; base += UNROLL * kWave) {
-            const int32_t p2 = pre - base;
-            if (len > 0 && p2 >= 0 && p2 < UNROLL * kWave) own[p2] = lane + 1;
-            wave_lds_sync();
-            uint32_t o2[UNROLL];
+            SegBatch<UNROLL> B;
+            int src[UNROLL];
+            walk_load<UNROLL>(B, src, base, total, pre, nseg, pb, pb + len, carry, own, wk_col, lane);
 #pragma unroll
             for (int q = 0; q < UNROLL; ++q) {
-                o2[q] = static_cast<uint32_t>(own[q * kWave + lane]);
-                own[q * kWave + lane] = 0;
-            }
-            wave_lds_sync();
-            int32_t y[UNROLL], yi[UNROLL];
+                const uint32_t item = static_cast<uint32_t>(__shfl(il, src[q]) - first);  // the segment's item
+                const int32_t mix = static_cast<int32_t>(item) * 0x3C6EF35;
+                bool maybe[kSeg];
 #pragma unroll
-            for (int q = 0; q < UNROLL; ++q) {
-                const uint32_t sl1 = max(wave_max_scan_dpp(o2[q]), carry);
-                carry = __builtin_amdgcn_readlane(sl1, kWave - 1);
-                const int sl = static_cast<int>(sl1) - 1;
-                const int32_t x = base + q * kWave + lane;
-                const bool inb = x < total;
-                const int32_t off = __shfl(rel, sl);
-                yi[q] = __shfl(il, sl);  // the element's item
-                const int32_t v = wk_col[inb ? off + x : 0];
-                y[q] = inb ? v : -1;
-            }
-#pragma unroll
-            for (int q = 0; q < UNROLL; ++q) {
-                bool go = y[q] >= 0;
-                uint32_t h = pack_slot(y[q], yi[q], shift, tmask);
-                uint32_t hit = 0;
-                while (__ballot(go) != 0) {
-                    const int32_t sv = table[h];
-                    const bool same = go && sv == y[q] && tag[h] == static_cast<uint8_t>(yi[q]);
-                    hit |= same ? 1u : 0u;
-                    go = go && sv != -1 && !same;
-                    h = (h + 1) & tmask;
+                for (int r = 0; r < kSeg; ++r) {
+                    const uint32_t f = filter_slot(B.v[q][r] + mix, fshift, fmask);
+                    maybe[r] = r < B.n[q] && ((filter[f >> 5] >> (f & 31)) & 1u) != 0u;
                 }
-                cnt += hit;
+#pragma unroll
+                for (int r = 0; r < kSeg; ++r) {
+                    bool go = maybe[r];
+                    const uint32_t key = ((item << kshift) | static_cast<uint32_t>(B.v[q][r])) + 1u;
+                    uint32_t h = hash_slot(B.v[q][r] + mix, shift, tmask);
+                    while (__ballot(go) != 0) {
+                        const uint32_t sv = table[h];
+                        cnt += (go && sv == key) ? 1u : 0u;
+                        go = go && sv != 0u && sv != key;
+                        h = (h + 1) & tmask;
+                    }
+                }
             }
         }
     }
-    // ---- leave the region zero
-    wave_lds_sync();
-    for (int q = lane; q < (1 << lg); q += kWave) table[q] = 0;
-    for (int q = lane; q < ((1 << lg) + 3) / 4; q += kWave) lds[q] = 0;
-    wave_lds_sync();
+    if (MODE == kModeBitmap) clear();
     return cnt;
 }
 
-// Adds to cnt the hits of the UNROLL elements in w (-1 = none) against S.
-// Hash probes are predicated: a wave-uniform loop runs while any lane is
-// still searching, with no per-lane branches.
+// Adds to cnt the hits of the entries of batch B against S.  Hash probes are
+// predicated: a wave-uniform loop runs while any lane is still searching,
+// with no per-lane branches.  `own` (see walk_load) holds zeros here: a
+// bitmap probe of an entry past its list's end reads own[0] instead, which
+// saves masking its result.
 template <int PM, int UNROLL>
-__device__ __forceinline__ void probe_batch(const int32_t (&w)[UNROLL], uint32_t &cnt,
+__device__ __forceinline__ void probe_batch(const SegBatch<UNROLL> &B, uint32_t &cnt,
                                             const int32_t *__restrict__ lds, const Staging &sg,
-                                            gptr<int32_t> st_col, int32_t sb, int32_t se,
-                                            int32_t wbase) {
+                                            gptr<int32_t> st_col, int32_t sb, int32_t se, int32_t wbase,
+                                            int32_t own_bit) {
 #pragma unroll
     for (int q = 0; q < UNROLL; ++q) {
-        const int32_t wq = w[q];
-        if (PM == kModeHash) {
-            const uint32_t f = filter_slot(wq, sg.fshift, sg.fmask);  // in range for any wq
-            const uint32_t bit = (static_cast<uint32_t>(lds[f >> 5]) >> (f & 31)) & 1u;
-            bool go = (wq >= 0) & (bit != 0u);
-            uint32_t h = hash_slot(wq, sg.shift, sg.tmask);
-            uint32_t hit = 0;
-            while (__ballot(go) != 0) {
-                const int32_t sv = sg.table[h];
-                hit |= (go && sv == wq) ? 1u : 0u;
-                go = go && sv >= 0 && sv != wq;
-                h = (h + 1) & sg.tmask;
+        if (PM == kModeBitmap) {
+#pragma unroll
+            for (int r = 0; r < kSeg; ++r) {
+                const int32_t wl = r < B.n[q] ? B.v[q][r] - wbase : own_bit;
+                cnt += (static_cast<uint32_t>(lds[wl >> 5]) >> (wl & 31)) & 1u;
             }
-            cnt += hit;
-        } else if (PM == kModeBitmap) {
-            const bool ok = wq >= 0;
-            const int32_t wl = ok ? wq - wbase : 0;
-            const uint32_t bit = (static_cast<uint32_t>(lds[wl >> 5]) >> (wl & 31)) & 1u;
-            cnt += ok ? bit : 0u;
+        } else if (PM == kModeHash) {
+            int32_t w[kSeg];
+            uint32_t bit[kSeg];
+#pragma unroll
+            for (int r = 0; r < kSeg; ++r) {
+                w[r] = r < B.n[q] ? B.v[q][r] : -1;
+                const uint32_t f = filter_slot(w[r], sg.fshift, sg.fmask);  // in range for any w
+                bit[r] = (static_cast<uint32_t>(lds[f >> 5]) >> (f & 31)) & 1u;
+            }
+#pragma unroll
+            for (int r = 0; r < kSeg; ++r) {
+                bool go = (w[r] >= 0) & (bit[r] != 0u);
+                uint32_t h = hash_slot(w[r], sg.shift, sg.tmask);
+                uint32_t hit = 0;
+                while (__ballot(go) != 0) {
+                    const int32_t sv = sg.table[h];
+                    hit |= (go && sv == w[r]) ? 1u : 0u;
+                    go = go && sv >= 0 && sv != w[r];
+                    h = (h + 1) & sg.tmask;
+                }
+                cnt += hit;
+            }
         } else {
-            if (wq >= 0) cnt += sorted_contains(st_col, sb, se, wq);
+#pragma unroll
+            for (int r = 0; r < kSeg; ++r)
+                if (r < B.n[q]) cnt += sorted_contains(st_col, sb, se, B.v[q][r]);
         }
     }
 }
 
+// A group's lists are cut to their entries above `after` when they have at
+// least this many segments each on average: half of the walk goes, for a
+// search of about ten dependent loads per group.  (R-MAT scale 20, kernel ms
+// at 3 / 6 / 12 segments: 8 x 8 blocks 1.79 / 1.78 / 1.77, one block 3.68 /
+// 3.75 / 3.83.)
+constexpr int32_t kAfterSegs = 6;
+
 // The walk of one item once the staging kind PM is known: groups of up to 64
-// walked lists; for the first group the first chunk batch is loaded before S
-// is staged, and every later batch loads while the previous one is probed.
+// walked lists; for the first group the first batch is loaded before S is
+// staged, and every later batch loads while the previous one is probed.
 // S is staged when the first non-empty group comes (`staged` tells the
 // caller whether it was), so an item whose lists are all empty stages
-// nothing.
+// nothing.  after >= 0: no entry up to `after` is in S (see tc_item_core).
 template <int PM, int UNROLL>
 __device__ __forceinline__ uint32_t walk_item(Staging stg, gptr<int32_t> st_col, int32_t sb,
                                               int32_t se, gptr<int32_t> wk_rptr,
                                               gptr<int32_t> wk_col, gptr<int32_t> ids, int32_t ib,
                                               int32_t ie, int32_t g0, int32_t gn, int32_t id,
                                               int32_t *__restrict__ lds, int32_t wbase, int lane,
-                                              bool &staged, int32_t *__restrict__ own) {
+                                              bool &staged, int32_t *__restrict__ own, int32_t own_bit,
+                                              int32_t after) {
     uint32_t cnt = 0;
     for (;;) {  // groups of up to 64 walked lists
-        int32_t pb = 0, len = 0;
+        int32_t pb = 0, end = 0;
         if (lane < gn) {
             pb = wk_rptr[id];
-            len = wk_rptr[id + 1] - pb;
+            end = wk_rptr[id + 1];
         }
-        const int32_t incl = wave_inclusive_scan(len);
-        const int32_t pre = incl - len;
-        const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        int32_t nseg = segs_of(end - pb);
+        int32_t incl = wave_inclusive_scan(nseg);
+        int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        if (after >= 0 && total >= kAfterSegs * gn) {
+            int32_t hi = end;
+            while (__ballot(pb < hi) != 0) {  // pb: first entry above after
+                const int32_t mid = (pb + hi) >> 1;
+                if (pb < hi) {
+                    if (wk_col[mid] <= after) pb = mid + 1;
+                    else hi = mid;
+                }
+            }
+            nseg = segs_of(end - pb);
+            incl = wave_inclusive_scan(nseg);
+            total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        }
+        const int32_t pre = incl - nseg;
         uint32_t carry = 0;
-        int32_t w[UNROLL];
-        walk_load<UNROLL>(w, 0, total, pre, len, pb, carry, own, wk_col, lane);
+        SegBatch<UNROLL> B;
+        int src[UNROLL];
+        walk_load<UNROLL>(B, src, 0, total, pre, nseg, pb, end, carry, own, wk_col, lane);
 
         if (!staged && total > 0) {
             staged = true;
@@ -436,13 +487,14 @@ __device__ __forceinline__ uint32_t walk_item(Staging stg, gptr<int32_t> st_col,
             }
         }
 
-        for (int32_t base = 0; base < total; base += UNROLL * kWave) {
-            int32_t wn[UNROLL];
-            walk_load<UNROLL>(wn, base + UNROLL * kWave, total, pre, len, pb, carry, own, wk_col, lane);
-            probe_batch<PM, UNROLL>(w, cnt, lds, stg, st_col, sb, se, wbase);
-#pragma unroll
-            for (int q = 0; q < UNROLL; ++q) w[q] = wn[q];
+        // the last batch is probed after the loop, with no further one loading
+        for (int32_t base = UNROLL * kWave; base < total; base += UNROLL * kWave) {
+            SegBatch<UNROLL> Bn;
+            walk_load<UNROLL>(Bn, src, base, total, pre, nseg, pb, end, carry, own, wk_col, lane);
+            probe_batch<PM, UNROLL>(B, cnt, lds, stg, st_col, sb, se, wbase, own_bit);
+            B = Bn;
         }
+        if (total > 0) probe_batch<PM, UNROLL>(B, cnt, lds, stg, st_col, sb, se, wbase, own_bit);
 
         g0 += kWave;
         if (g0 >= ie) break;
@@ -458,10 +510,11 @@ __device__ __forceinline__ uint32_t walk_item(Staging stg, gptr<int32_t> st_col,
 // sum_x |S & L_x| (the sum over lanes is the item's count).  With the edge
 // block walked by rows this is S = A_ik[u], L_v = A_jk[v] for v in A_ij[u];
 // walked by columns, S = A_jk[v], L_u = A_ik[u] for u with (u, v) in A_ij.
-// `lds` holds LDS_WORDS int32 words private to the wave and `own` 64 *
+// `lds` holds LDS_WORDS int32 words private to the wave, followed by 64 *
 // UNROLL more, zero on entry and left zero (the walk's list positions).
-// Column ids of both lists lie in [wbase, wbase + width_k).  Every lane of
-// the wave must call this with the same arguments.
+// Column ids of both lists lie in [wbase, wbase + width_k).  after >= 0: every
+// entry of S exceeds `after`, so the lists' entries up to it may be skipped.
+// Every lane of the wave must call this with the same arguments.
 //
 // Hash staging: S goes into an open-addressing table (load <= 2/3) and into
 // a bit filter with about eight bits per entry; a probe reads the filter
@@ -476,14 +529,16 @@ __device__ __forceinline__ uint32_t walk_item(Staging stg, gptr<int32_t> st_col,
 // ids of the walked lists with the bounds of S, the first chunks of the walk
 // before S is staged, and every later chunk before the previous one is
 // probed.
-template <int MODE, int LDS_WORDS, int UNROLL = 2>
+template <int MODE, int LDS_WORDS, int UNROLL = 1>
 __device__ __forceinline__ uint32_t tc_item_core(const int32_t *__restrict__ st_col_, int32_t sb, int32_t se,
                                                  const int32_t *__restrict__ wk_rptr_,
                                                  const int32_t *__restrict__ wk_col_,
                                                  const int32_t *__restrict__ ids_, int32_t ib, int32_t ie,
-                                                 int32_t width_k, int32_t *__restrict__ lds,
-                                                 int32_t *__restrict__ own, int32_t wbase = 0) {
+                                                 int32_t width_k, int32_t *__restrict__ lds, int32_t wbase = 0,
+                                                 int32_t after = -1) {
     const int lane = lane_id();
+    int32_t *own = lds + LDS_WORDS;
+    constexpr int32_t own_bit = 32 * LDS_WORDS;
     if (ib >= ie) return 0u;
     const gptr<int32_t> st_col = as_global(st_col_);
     const gptr<int32_t> wk_rptr = as_global(wk_rptr_), wk_col = as_global(wk_col_);
@@ -525,13 +580,13 @@ __device__ __forceinline__ uint32_t tc_item_core(const int32_t *__restrict__ st_
     bool staged = false;
     if (mode == kModeHash)
         cnt = walk_item<kModeHash, UNROLL>(stg, st_col, sb, se, wk_rptr, wk_col, ids, ib, ie, ib, gn, id,
-                                           lds, wbase, lane, staged, own);
+                                           lds, wbase, lane, staged, own, own_bit, after);
     else if (mode == kModeBitmap)
         cnt = walk_item<kModeBitmap, UNROLL>(stg, st_col, sb, se, wk_rptr, wk_col, ids, ib, ie, ib, gn, id,
-                                             lds, wbase, lane, staged, own);
+                                             lds, wbase, lane, staged, own, own_bit, after);
     else
         cnt = walk_item<kModeSearch, UNROLL>(stg, st_col, sb, se, wk_rptr, wk_col, ids, ib, ie, ib, gn, id,
-                                             lds, wbase, lane, staged, own);
+                                             lds, wbase, lane, staged, own, own_bit, after);
 
     // ---- leave the LDS clean for the next row of this wave
     if (!staged) return cnt;
@@ -551,21 +606,6 @@ __device__ __forceinline__ uint32_t tc_item_core(const int32_t *__restrict__ st_
         }
     }
     return cnt;
-}
-
-// The same with the staged list given by its row: S = st_col[st_rptr[srow]
-// .. st_rptr[srow + 1]).
-template <int MODE, int LDS_WORDS, int UNROLL = 2>
-__device__ __forceinline__ uint32_t tc_item(const int32_t *__restrict__ st_rptr,
-                                            const int32_t *__restrict__ st_col, int32_t srow,
-                                            const int32_t *__restrict__ wk_rptr,
-                                            const int32_t *__restrict__ wk_col,
-                                            const int32_t *__restrict__ ids, int32_t ib, int32_t ie,
-                                            int32_t width_k, int32_t *__restrict__ lds,
-                                            int32_t *__restrict__ own, int32_t wbase = 0) {
-    const gptr<int32_t> rp = as_global(st_rptr);
-    return tc_item_core<MODE, LDS_WORDS, UNROLL>(st_col, rp[srow], rp[srow + 1], wk_rptr, wk_col, ids, ib, ie,
-                                                 width_k, lds, own, wbase);
 }
 
 }  // namespace pgabb

@@ -21,14 +21,18 @@ namespace pgabb {
 //
 // With FILTER, only the items whose staged list length lies in
 // (a.stage_lo, a.stage_hi] are counted (a launch split by list length).
+// Seven waves per SIMD, the most that regions of 1280 words (and 64 of list
+// positions) leave room for in LDS; left alone the compiler takes 75
+// registers, six waves (R-MAT scale 20 in 32 x 32 blocks 3.23 against 2.96
+// ms, a random geometric graph of 400,001 vertices 622 against 607 us).
 template <int MODE, int LDS_WORDS, int WAVES, int UNROLL, int ORIENT, bool FILTER = false>
-__global__ __launch_bounds__(WAVES * 64) void k_tc_tasks(CountArgs a) {
-    __shared__ int32_t lds_all[WAVES][LDS_WORDS];
-    __shared__ int32_t own_all[WAVES][UNROLL * kWave];  // the walk's list positions
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(LDS_WORDS <= 1280 ? 7 : 4)))
+void k_tc_tasks(CountArgs a) {
+    __shared__ int32_t lds_all[WAVES][LDS_WORDS + UNROLL * kWave];  // staged list, then the walk's list positions
     const int w = threadIdx.x >> 6;
     const int lane = lane_id();
     int32_t *lds = lds_all[w];
-    int32_t *own = own_all[w];
+    int32_t *own = lds + LDS_WORDS;
 #pragma unroll
     for (int q = 0; q < UNROLL; ++q) own[q * kWave + lane] = 0;
     wave_lds_sync();
@@ -112,16 +116,14 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_tasks(CountArgs a) {
             }
             // items with small staged lists and few walked lists: packed into
             // one LDS table, task by task, while their staged entries fit
-            constexpr int kPackSlots = HashLds<LDS_WORDS>::kTableCap < 4 * HashLds<LDS_WORDS>::kFilterCap
-                                           ? HashLds<LDS_WORDS>::kTableCap
-                                           : 4 * HashLds<LDS_WORDS>::kFilterCap;
             uint64_t small = todo & __ballot(se - sb <= kPackS && e - b <= kPackLists);
             todo &= ~small;
             while (small) {
                 const int32_t t = __builtin_amdgcn_readlane(tl, __builtin_ctzll(small));
                 const uint64_t mt = small & __ballot(tl == t);
                 const int32_t ns = ((mt >> lane) & 1ull) ? se - sb : 0;
-                const uint64_t mp = mt & __ballot(wave_inclusive_scan(ns) <= kPackSlots / 2);
+                const uint64_t mp = mt & __ballot(wave_inclusive_scan(ns) <= kPackEntries<LDS_WORDS> &&
+                                                  lane - __builtin_ctzll(mt) < pack_items(tasks[t].width_k));
                 small &= ~mp;
                 if (t != cur) {
                     flush();
@@ -129,11 +131,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_tasks(CountArgs a) {
                 }
                 const auto &T = tasks[t];
                 if (ORIENT == kOrientRow)
-                    cnt += packed_items<UNROLL, LDS_WORDS>(mp, b, e, sb, se, T.ik.col, T.ij.col, T.jk.rptr, T.jk.col,
-                                                           lds, own, lane);
+                    cnt += packed_items<MODE, UNROLL, LDS_WORDS>(mp, b, e, sb, se, T.ik.col, T.ij.col, T.jk.rptr,
+                                                                 T.jk.col, T.width_k, lds, own, lane);
                 else
-                    cnt += packed_items<UNROLL, LDS_WORDS>(mp, b, e, sb, se, T.jk.col, T.ij.crow, T.ik.rptr,
-                                                           T.ik.col, lds, own, lane);
+                    cnt += packed_items<MODE, UNROLL, LDS_WORDS>(mp, b, e, sb, se, T.jk.col, T.ij.crow, T.ik.rptr,
+                                                                 T.ik.col, T.width_k, lds, own, lane);
             }
             while (todo) {
                 const int l = __builtin_ctzll(todo);
@@ -148,12 +150,17 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_tasks(CountArgs a) {
                 const int32_t sbl = __builtin_amdgcn_readlane(sb, l);
                 const int32_t sel = __builtin_amdgcn_readlane(se, l);
                 const auto &T = tasks[t];
+                // j = k: the walked lists are rows u of A_ij itself, and A_jj[v]
+                // holds entries above v only.  (A row walk's lists A_jk[v] hold
+                // none up to v in the first place.)
+                const int32_t after = ORIENT == kOrientCol && T.ij.col == T.ik.col
+                                          ? __builtin_amdgcn_readlane(x, l) : -1;
                 if (ORIENT == kOrientRow)
                     cnt += tc_item_core<MODE, LDS_WORDS, UNROLL>(T.ik.col, sbl, sel, T.jk.rptr, T.jk.col, T.ij.col,
-                                                                 bl, el, T.width_k, lds, own);
+                                                                 bl, el, T.width_k, lds);
                 else
                     cnt += tc_item_core<MODE, LDS_WORDS, UNROLL>(T.jk.col, sbl, sel, T.ik.rptr, T.ik.col, T.ij.crow,
-                                                                 bl, el, T.width_k, lds, own);
+                                                                 bl, el, T.width_k, lds, 0, after);
             }
             flush();
         }
