@@ -3,25 +3,34 @@
 // one block suffice).  Two of the paper's examples run here on the blocks
 // the triangle count uses:
 //
-//   * connected components by Shiloach-Vishkin (Section 3.4): even
-//     iterations hook -- for every edge whose endpoints point to different
-//     roots, the larger root is hooked under the smaller -- and odd
-//     iterations link every vertex to its tree's root by pointer jumping;
-//     the iterations stop after a hooking pass that hooked nothing;
+//   * connected components by Shiloach-Vishkin (Section 3.4): hooking
+//     iterations put the trees of an edge's ends under one root, linking
+//     iterations point every vertex at its tree's root by pointer jumping.
+//     The smaller root goes under the larger: ranks ascend with the degree,
+//     so trees gather at the hubs.  The first hooking pass puts every vertex
+//     under its highest neighbour (the last entry of its row), the second
+//     takes each row's last entry but one, which leaves few trees, and the
+//     third visits every edge.  A hook that another edge got ahead of is
+//     tried again with the roots found then, so the third pass leaves no
+//     edge between two trees and no pass is needed to see that (R-MAT scale
+//     20 over 8 x 8 blocks: 3.6 -> 0.66 ms a call; five passes over the
+//     blocks' items with a host round trip each took 2.8 ms of kernels, these
+//     0.35 ms, most of it the gathers of the third pass);
 //   * PageRank (Section 5.2, an SpMV-like iteration with damping d,
 //     tolerance and iteration limit), pulled through the blocks with atomic
-//     additions, as the paper does on its two-dimensional layout.
+//     additions, as the paper does on its two-dimensional layout.  On R-MAT
+//     scale 20 over 8 x 8 blocks an iteration's pull takes 225 us (271 with
+//     one entry per lane), for 31 M gathers of shares and one addition per
+//     item in device memory; four iterations are queued per host round trip
+//     (eight of them 3.07 -> 2.55 ms a call).
 //
-// Work items are the blocks' own (x, b, e) records: a run of at most
-// kSplitV entries of one row (or, through the stored transpose, of one
-// column).  All items of all blocks form one list per launch, one item per
-// lane; a lane finds its block by a binary search of the item prefix.  For
-// the hooking pass the list is ordered by the stripe an item gathers from
-// (the column stripe of a row item) and cut into eight contiguous ranges,
-// one work queue each; workgroup b starts on queue
-// b % 8, its XCD under round-robin dispatch, so each XCD's gathers fall
-// mostly in one or two stripes' slice of the vertex arrays, which its L2
-// holds (the two-dimensional layout's locality, per XCD).
+// PageRank's work items are the blocks' own (x, b, e) records: a run of at
+// most kSplitV entries of one row or, through the stored transpose, of one
+// column.  All items of all blocks form one list per launch; a wave takes 64
+// of them, a lane finding its item's block by a binary search of the item
+// prefix, and reads their entries in segments of kSeg, one per lane and load
+// (walk_items; see tc_device.hpp).  The components' passes read the rows of
+// the oriented graph.
 // Vertices are ranks (the ids of the oriented graph); results come back by
 // input id through the graph's rank array.
 #include <hip/hip_runtime.h>
@@ -34,6 +43,7 @@
 
 #include "common.hpp"
 #include "graph.hpp"
+#include "tc_device.hpp"
 #include "wave.hpp"
 
 namespace pgabb {
@@ -44,28 +54,9 @@ constexpr int kBB = 256;
 constexpr int kBspQueues = 8;
 constexpr int kBspStride = 32;  // queue counters 256 bytes apart
 constexpr int kBspQueueWords = kBspQueues * kBspStride;
-
-// Walks the work queues (queue q covers the q-th eighth of the item list): fn(item) for every item this wave takes, one item
-// per lane.  Every lane of the wave must call it.
-template <class F>
-__device__ __forceinline__ void for_items_by_queue(int64_t total, unsigned long long *__restrict__ next, F fn) {
-    const int lane = lane_id();
-    const int64_t per = (total + kBspQueues - 1) / kBspQueues;
-    const int home = static_cast<int>(blockIdx.x % kBspQueues);
-    for (int qi = 0; qi < kBspQueues; ++qi) {
-        const int q = (home + qi) % kBspQueues;
-        const int64_t q0 = q * per, q1 = min(q0 + per, total);
-        for (;;) {
-            unsigned long long g = 0;
-            if (lane == 0) g = atomicAdd(&next[q * kBspStride], static_cast<unsigned long long>(kWave));
-            g = shfl_t(g, 0);
-            const int64_t i0 = q0 + static_cast<int64_t>(g);
-            if (i0 >= q1) break;
-            const int64_t item = i0 + lane;
-            if (item < q1) fn(item);
-        }
-    }
-}
+// Rows a wave hooks at a time (R-MAT scale 20, all kernels of a call: 8 / 16
+// / 32 / 64 rows 506 / 387 / 346 / 372 us).
+constexpr int kHookRows = 32;
 
 // One run of items: the row items of a block (entries in `idx` = col, item
 // ids in stripe i, entries in stripe j) or its column items (idx = crow,
@@ -101,47 +92,164 @@ __device__ __forceinline__ int32_t find_seg(const int64_t *__restrict__ pre, int
     return lo;
 }
 
-__global__ __launch_bounds__(kBB) void k_sv_init(int32_t *__restrict__ C, int32_t n) {
-    for (int64_t r = blockIdx.x * int64_t(kBB) + threadIdx.x; r < n; r += int64_t(gridDim.x) * kBB)
-        C[r] = static_cast<int32_t>(r);
+// Reads the entries of one list per lane -- len of them at src_ptr, vertices
+// by + entry -- as one flattened run of segments: own[] is 64 words of the
+// wave's LDS, zero on entry and left zero.  Calls seg(n, src, y) for every
+// segment on the lane that holds it: n entries (some lanes may hold none) of
+// the list of lane src, the vertices y[0 .. n).  The segment of a list's last
+// entries reads up to kSeg - 1 words past them: the arrays that lists lie in
+// are allocated kSeg words longer.
+template <class SegFn>
+__device__ __forceinline__ void walk_lists(const int32_t *src_ptr, int32_t len, int32_t by, int32_t *own, int lane,
+                                           SegFn seg) {
+    const int32_t ns = (len + kSeg - 1) / kSeg;
+    const int32_t incl = wave_inclusive_scan(ns);
+    const int32_t pre_l = incl - ns;
+    const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    // segment t of the run starts at rel + kSeg t words of its item's lane
+    const uint64_t rel = reinterpret_cast<uint64_t>(src_ptr) -
+                         static_cast<uint64_t>(pre_l) * (kSeg * sizeof(int32_t));
+    const int32_t rel_lo = static_cast<int32_t>(static_cast<uint32_t>(rel));
+    const int32_t rel_hi = static_cast<int32_t>(static_cast<uint32_t>(rel >> 32));
+    const int32_t last = len + kSeg * pre_l;  // entries of the item before position kSeg t: kSeg t - kSeg pre_l
+    uint32_t carry = 0;
+    for (int32_t base = 0; base < total; base += kWave) {
+        const int32_t p = pre_l - base;
+        if (ns > 0 && p >= 0 && p < kWave) own[p] = lane + 1;
+        wave_lds_sync();
+        const uint32_t o = static_cast<uint32_t>(own[lane]);
+        own[lane] = 0;
+        wave_lds_sync();
+        const uint32_t sl1 = max(wave_max_scan_dpp(o), carry);
+        carry = __builtin_amdgcn_readlane(sl1, kWave - 1);
+        const int sl = static_cast<int>(sl1) - 1;
+        const int32_t t = base + lane;
+        const uint64_t r = (static_cast<uint64_t>(static_cast<uint32_t>(__shfl(rel_hi, sl))) << 32) |
+                           static_cast<uint32_t>(__shfl(rel_lo, sl));
+        const int32_t left = __shfl(last, sl) - kSeg * t;  // (every lane shuffles)
+        const int32_t n = t < total ? min(left, kSeg) : 0;
+        const int32_t yb = __shfl(by, sl);
+        int32_t y[kSeg] = {0, 0, 0, 0};
+        if (n > 0) {
+            const seg_t v = *reinterpret_cast<const __attribute__((address_space(1))) seg_t *>(
+                as_global(reinterpret_cast<const int32_t *>(r)) + static_cast<int64_t>(kSeg) * t);
+#pragma unroll
+            for (int k = 0; k < kSeg; ++k) y[k] = yb + v[k];
+        }
+        seg(n, sl, y);
+    }
 }
 
-// Hooking: for every edge (u, v) with C(u) != C(v), the larger of the two
-// (a root after the previous linking pass) is hooked under the smaller if it
-// still is a root.  Parents only ever decrease (C(x) <= x), so the pointers
-// form a forest whatever order the hooks land in.  *hooks becomes nonzero
-// when a hook was made (a wave adds its hooks only while it reads zero
-// there, so the word takes few atomics).
-__global__ __launch_bounds__(kBB) void k_sv_hook(const BspSeg *__restrict__ segs, const int64_t *__restrict__ pre,
-                                                 int32_t nseg, int32_t *__restrict__ C,
-                                                 unsigned long long *__restrict__ hooks,
-                                                 unsigned long long *__restrict__ next) {
-    const int64_t total = pre[nseg];
-    uint32_t h = 0;
-    for_items_by_queue(total, next, [&](int64_t q) {
+// walk_lists over the items [q0, q1), at most 64, after item(x) on every lane
+// (x: its item's vertex, or -1).
+template <class Item, class SegFn>
+__device__ __forceinline__ void walk_items(const BspSeg *__restrict__ segs, const int64_t *__restrict__ pre,
+                                           int32_t nseg, int64_t q0, int64_t q1, int32_t *own, int lane, Item item,
+                                           SegFn seg) {
+    const int64_t q = q0 + lane;
+    int32_t x = -1, len = 0, by = 0;
+    const int32_t *src_ptr = nullptr;
+    if (q < q1) {
         const int32_t s = find_seg(pre, nseg, q);
         const BspSeg sg = segs[s];
-        const int32_t *it = sg.items + kItemWords * (q - pre[s]);
-        const int32_t u = sg.base_x + it[0];
+        const gptr<int32_t> it = as_global(sg.items) + kItemWords * (q - pre[s]);
+        x = sg.base_x + it[0];
         const int32_t b = it[1], e = it[2];
-        for (int32_t t = b; t < e; ++t) {
-            const int32_t v = sg.base_y + sg.idx[t];
-            const int32_t cu = __atomic_load_n(&C[u], __ATOMIC_RELAXED);
-            const int32_t cv = __atomic_load_n(&C[v], __ATOMIC_RELAXED);
-            if (cu == cv) continue;
-            const int32_t r1 = max(cu, cv), r2 = min(cu, cv);
-            if (__atomic_load_n(&C[r1], __ATOMIC_RELAXED) == r1) {
-                atomicMin(&C[r1], r2);
-                ++h;
-            }
+        len = e - b;
+        src_ptr = sg.idx + b;
+        by = sg.base_y;
+    }
+    item(x);
+    walk_lists(src_ptr, len, by, own, lane, seg);
+}
+
+// The first hooking pass: every vertex under its highest neighbour, the last
+// entry of its row (itself without one).
+__global__ __launch_bounds__(kBB) void k_sv_first(const int64_t *__restrict__ row_off, const int32_t *__restrict__ col,
+                                                  int32_t n, int32_t *__restrict__ C) {
+    for (int64_t r = blockIdx.x * int64_t(kBB) + threadIdx.x; r < n; r += int64_t(gridDim.x) * kBB) {
+        const int64_t e0 = row_off[r], e1 = row_off[r + 1];
+        C[r] = e1 > e0 ? col[e1 - 1] : static_cast<int32_t>(r);
+    }
+}
+
+// Puts the trees of cu and cv (ancestors of an edge's ends) under one root:
+// the smaller of two different ancestors is hooked under the larger if it is
+// a root; if another hook got there first, both ancestors are read again.
+// Parents only ever increase, so the pointers form a forest whatever order
+// the hooks land in, and every retry starts from higher ancestors.
+__device__ __forceinline__ void sv_hook(int32_t *__restrict__ C, int32_t cu, int32_t cv) {
+    while (cu != cv) {
+        const int32_t r1 = min(cu, cv), r2 = max(cu, cv);
+        const int32_t up = __atomic_load_n(&C[r1], __ATOMIC_RELAXED);
+        if (up == r2) return;
+        if (up == r1) {
+            const int32_t was = atomicCAS(&C[r1], r1, r2);
+            if (was == r1 || was == r2) return;
         }
-    });
-    const unsigned long long sum = wave_sum(static_cast<unsigned long long>(h));
-    if (lane_id() == 0 && sum && __atomic_load_n(hooks, __ATOMIC_RELAXED) == 0) atomicAdd(hooks, sum);
+        cu = __atomic_load_n(&C[__atomic_load_n(&C[r1], __ATOMIC_RELAXED)], __ATOMIC_RELAXED);
+        cv = __atomic_load_n(&C[r2], __ATOMIC_RELAXED);
+    }
+}
+
+// The second hooking pass: every row's last entry but one.
+__global__ __launch_bounds__(kBB) void k_sv_second(const int64_t *__restrict__ row_off,
+                                                   const int32_t *__restrict__ col, int32_t n,
+                                                   int32_t *__restrict__ C) {
+    for (int64_t r = blockIdx.x * int64_t(kBB) + threadIdx.x; r < n; r += int64_t(gridDim.x) * kBB) {
+        const int64_t e0 = row_off[r], e1 = row_off[r + 1];
+        if (e1 - e0 >= 2)
+            sv_hook(C, __atomic_load_n(&C[r], __ATOMIC_RELAXED), __atomic_load_n(&C[col[e1 - 2]], __ATOMIC_RELAXED));
+    }
+}
+
+// Hooking over every edge: a wave takes kHookRows consecutive rows of the
+// oriented graph, highest ranks (the longest rows) first, from eight work
+// counters.
+// Rows, not the blocks' items: at 8 x 8 blocks an item holds about four
+// entries, and finding 64 items' blocks and records cost more than their
+// entries (R-MAT scale 20: 330 us a pass over the items).
+__global__ __launch_bounds__(kBB) void k_sv_hook_edges(const int64_t *__restrict__ row_off,
+                                                       const int32_t *__restrict__ col, int32_t n,
+                                                       int32_t *__restrict__ C,
+                                                       unsigned long long *__restrict__ next) {
+    __shared__ int32_t s_own[kBB];
+    const int lane = lane_id();
+    int32_t *own = s_own + (threadIdx.x - lane);
+    own[lane] = 0;
+    wave_lds_sync();
+    const gptr<int64_t> ro = as_global(row_off);
+    const int64_t groups = (static_cast<int64_t>(n) + kHookRows - 1) / kHookRows;
+    const int home = static_cast<int>(blockIdx.x % kBspQueues);
+    for (int qi = 0; qi < kBspQueues; ++qi) {
+        const int q = (home + qi) % kBspQueues;
+        for (;;) {
+            unsigned long long c = 0;
+            if (lane == 0) c = atomicAdd(&next[q * kBspStride], 1ull);
+            c = shfl_t(c, 0);
+            const int64_t g = static_cast<int64_t>(c) * kBspQueues + q;
+            if (g >= groups) break;
+            const int64_t x = lane < kHookRows ? n - 1 - g * kHookRows - lane : -1;
+            const int64_t e0 = x >= 0 ? ro[x] : 0, e1 = x >= 0 ? ro[x + 1] : 0;
+            const int32_t cu = x >= 0 ? __atomic_load_n(&C[x], __ATOMIC_RELAXED) : 0;
+            walk_lists(col + e0, static_cast<int32_t>(e1 - e0), 0, own, lane,
+                       [&](int32_t m, int src, const int32_t (&y)[kSeg]) {
+                           const int32_t c0 = __shfl(cu, src);
+                           int32_t cv[kSeg];
+#pragma unroll
+                           for (int k = 0; k < kSeg; ++k)
+                               cv[k] = k < m ? __atomic_load_n(&C[y[k]], __ATOMIC_RELAXED) : c0;
+#pragma unroll
+                           for (int k = 0; k < kSeg; ++k) sv_hook(C, c0, cv[k]);
+                       });
+        }
+    }
 }
 
 // Linking: every vertex points to the root of its tree (pointer jumping to
-// the end; no hook runs meanwhile, so the roots stay fixed).
+// the end; no hook runs meanwhile, so the roots stay fixed).  The ancestors
+// reached on the way are stored, which shortens the chains that pass through
+// x.
 __global__ __launch_bounds__(kBB) void k_sv_link(int32_t *__restrict__ C, int32_t n) {
     for (int64_t x = blockIdx.x * int64_t(kBB) + threadIdx.x; x < n; x += int64_t(gridDim.x) * kBB) {
         int32_t y = __atomic_load_n(&C[x], __ATOMIC_RELAXED);
@@ -149,8 +257,8 @@ __global__ __launch_bounds__(kBB) void k_sv_link(int32_t *__restrict__ C, int32_
             const int32_t z = __atomic_load_n(&C[y], __ATOMIC_RELAXED);
             if (z == y) break;
             y = z;
+            __atomic_store_n(&C[x], y, __ATOMIC_RELAXED);
         }
-        __atomic_store_n(&C[x], y, __ATOMIC_RELAXED);
     }
 }
 
@@ -167,15 +275,13 @@ __global__ __launch_bounds__(kBB) void k_sv_minid(const int32_t *__restrict__ C,
         const int64_t v = base + lane;
         const bool ok = v < n;
         const int32_t root = ok ? C[rank[v]] : -1;
-        // one large component holds most vertices: the lanes whose root is
-        // the first lane's send one minimum, the others one atomic each
+        // one large component holds most vertices: of the lanes whose root is
+        // the first lane's, the first holds the smallest id and alone sends
+        // it (most ids are above a minimum already there, which one load
+        // shows)
         const int32_t r0 = __builtin_amdgcn_readfirstlane(root);
-        const bool same = ok && root == r0;
-        int32_t mv = same ? static_cast<int32_t>(v) : INT32_MAX;
-#pragma unroll
-        for (int m = 1; m < kWave; m <<= 1) mv = min(mv, __shfl_xor(mv, m));
-        if (lane == 0 && r0 >= 0 && mv != INT32_MAX) atomicMin(&minid[r0], mv);
-        if (ok && !same) atomicMin(&minid[root], static_cast<int32_t>(v));
+        if (ok && (lane == 0 || root != r0) && v < __atomic_load_n(&minid[root], __ATOMIC_RELAXED))
+            atomicMin(&minid[root], static_cast<int32_t>(v));
         c += ok && C[v] == v ? 1u : 0u;
     }
     const unsigned long long sum = block_sum(static_cast<unsigned long long>(c));
@@ -203,33 +309,24 @@ __global__ __launch_bounds__(kBB) void k_sv_label(const int32_t *__restrict__ C,
         label[v] = minid[C[rank[v]]];
 }
 
-// PageRank, one iteration in three launches: each vertex's share
-// contrib(x) = r(x) / deg(x) (zero for isolated vertices), the pull of the
-// shares over every block's rows and columns into acc, and the update
-// r'(x) = (1 - d) / n + d * acc(x) with the sum of |r' - r|.
-__global__ __launch_bounds__(kBB) void k_pr_prep(const double *__restrict__ r, const int32_t *__restrict__ outdeg,
-                                                 const int32_t *__restrict__ indeg, int32_t n,
-                                                 double *__restrict__ contrib, double *__restrict__ acc) {
-    for (int64_t x = blockIdx.x * int64_t(kBB) + threadIdx.x; x < n; x += int64_t(gridDim.x) * kBB) {
-        const int32_t d = outdeg[x] + indeg[x];
-        contrib[x] = d ? r[x] / static_cast<double>(d) : 0.0;
-        acc[x] = 0.0;
-    }
-}
-
+// PageRank, one iteration in two launches: the pull of the shares
+// contrib(x) = r(x) / deg(x) (zero for isolated vertices) over every block's
+// rows and columns into acc, and the update r'(x) = (1 - d) / n + d * acc(x)
+// with the sum of |r' - r|, the next shares and the clearing of acc.  `prev`
+// is the change of the iteration before: below tol, the iterations have
+// stopped and the launch does nothing (iterations are queued several at a
+// time).
+//
 // (PageRank walks the items in block order, grid-stride: dealt to per-XCD
 // queues by gather stripe, as the hooking pass is, an iteration on R-MAT
 // scale 20 took 0.81 ms against 0.72 ms.)
-// The pull: each wave takes 64 consecutive items (one per lane: its target
-// x and entry range) and reads their entries as one flattened run over the
-// lanes -- consecutive items of a block have consecutive entry ranges, so
-// the index loads are contiguous -- finding each element's item by
-// scattering the items' first positions into LDS and a running maximum
-// over the lanes; each element adds its source's share to its item's sum in
-// LDS, and every item adds its sum to acc[x] once.
+// The pull: each lane adds up its segment's shares and adds them to its
+// item's sum in LDS, and every item adds its sum to acc[x] once.
 __global__ __launch_bounds__(kBB) void k_pr_pull(const BspSeg *__restrict__ segs, const int64_t *__restrict__ pre,
                                                  int32_t nseg, const double *__restrict__ contrib_,
-                                                 double *__restrict__ acc) {
+                                                 double *__restrict__ acc, const double *__restrict__ prev,
+                                                 double tol) {
+    if (prev && *prev < tol) return;
     __shared__ double s_sum[kBB];
     __shared__ int32_t s_own[kBB];
     const int lane = lane_id();
@@ -241,61 +338,39 @@ __global__ __launch_bounds__(kBB) void k_pr_pull(const BspSeg *__restrict__ segs
     const int64_t total = pre[nseg];
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kBB;
     for (int64_t q0 = blockIdx.x * int64_t(kBB) + (threadIdx.x - lane); q0 < total; q0 += stride) {
-        const int64_t q = q0 + lane;
-        int32_t x = 0, len = 0, by = 0;
-        const int32_t *src = nullptr;  // the item's entries: src[0 .. len)
-        if (q < total) {
-            const int32_t s = find_seg(pre, nseg, q);
-            const BspSeg sg = segs[s];
-            const gptr<int32_t> it = as_global(sg.items) + kItemWords * (q - pre[s]);
-            x = sg.base_x + it[0];
-            const int32_t b = it[1], e = it[2];
-            len = e - b;
-            src = sg.idx + b;
-            by = sg.base_y;
-        }
-        sum[lane] = 0.0;
-        const int32_t incl = wave_inclusive_scan(len);
-        const int32_t pre_l = incl - len;
-        const int32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
-        // element el of the run is src[el - pre_l] of its item's lane
-        const uint64_t rel = reinterpret_cast<uint64_t>(src) - static_cast<uint64_t>(pre_l) * sizeof(int32_t);
-        const uint32_t rel_lo = static_cast<uint32_t>(rel), rel_hi = static_cast<uint32_t>(rel >> 32);
+        int32_t x = -1;
+        walk_items(
+            segs, pre, nseg, q0, min(q0 + kWave, total), own, lane,
+            [&](int32_t v) {
+                x = v;
+                sum[lane] = 0.0;
+            },
+            [&](int32_t n, int src, const int32_t (&y)[kSeg]) {
+                double c[kSeg];
+#pragma unroll
+                for (int k = 0; k < kSeg; ++k) c[k] = k < n ? contrib[y[k]] : 0.0;
+                if (n > 0) unsafeAtomicAdd(&sum[src], (c[0] + c[1]) + (c[2] + c[3]));
+            });
         wave_lds_sync();
-        uint32_t carry = 0;
-        for (int32_t base = 0; base < tot; base += kWave) {
-            const int32_t p = pre_l - base;
-            if (len > 0 && p >= 0 && p < kWave) own[p] = lane + 1;
-            wave_lds_sync();
-            const uint32_t o = static_cast<uint32_t>(own[lane]);
-            own[lane] = 0;
-            wave_lds_sync();
-            const uint32_t sl1 = max(wave_max_scan_dpp(o), carry);
-            carry = __builtin_amdgcn_readlane(sl1, kWave - 1);
-            const int sl = static_cast<int>(sl1) - 1;
-            const uint64_t r = (static_cast<uint64_t>(static_cast<uint32_t>(__shfl(static_cast<int>(rel_hi), sl)))
-                                << 32) |
-                               static_cast<uint32_t>(__shfl(static_cast<int>(rel_lo), sl));
-            const int32_t yb = __shfl(by, sl);
-            const int32_t el = base + lane;
-            if (el < tot) {
-                const gptr<int32_t> ptr = as_global(reinterpret_cast<const int32_t *>(r));
-                unsafeAtomicAdd(&sum[sl], contrib[yb + ptr[el]]);
-            }
-        }
-        wave_lds_sync();
-        if (len > 0) unsafeAtomicAdd(&acc[x], sum[lane]);
+        if (x >= 0) unsafeAtomicAdd(&acc[x], sum[lane]);
         wave_lds_sync();  // before the next items reset the sums
     }
 }
 
-__global__ __launch_bounds__(kBB) void k_pr_update(double *__restrict__ r, const double *__restrict__ acc, int32_t n,
-                                                   double teleport, double d, double *__restrict__ err) {
+__global__ __launch_bounds__(kBB) void k_pr_update(double *__restrict__ r, double *__restrict__ acc,
+                                                   const int32_t *__restrict__ outdeg,
+                                                   const int32_t *__restrict__ indeg, int32_t n, double teleport,
+                                                   double d, double *__restrict__ contrib, double *__restrict__ err,
+                                                   const double *__restrict__ prev, double tol) {
+    if (prev && *prev < tol) return;
     double e = 0.0;
     for (int64_t x = blockIdx.x * int64_t(kBB) + threadIdx.x; x < n; x += int64_t(gridDim.x) * kBB) {
         const double nx = teleport + d * acc[x];
         e += fabs(nx - r[x]);
         r[x] = nx;
+        const int32_t deg = outdeg[x] + indeg[x];
+        contrib[x] = deg ? nx / static_cast<double>(deg) : 0.0;
+        acc[x] = 0.0;
     }
 #pragma unroll
     for (int m = 1; m < kWave; m <<= 1) e += __shfl_xor(e, m);
@@ -311,8 +386,16 @@ __global__ __launch_bounds__(kBB) void k_pr_update(double *__restrict__ r, const
     }
 }
 
-__global__ __launch_bounds__(kBB) void k_pr_init(double *__restrict__ r, int32_t n, double v) {
-    for (int64_t x = blockIdx.x * int64_t(kBB) + threadIdx.x; x < n; x += int64_t(gridDim.x) * kBB) r[x] = v;
+__global__ __launch_bounds__(kBB) void k_pr_init(double *__restrict__ r, double *__restrict__ acc,
+                                                 const int32_t *__restrict__ outdeg,
+                                                 const int32_t *__restrict__ indeg, int32_t n, double v,
+                                                 double *__restrict__ contrib) {
+    for (int64_t x = blockIdx.x * int64_t(kBB) + threadIdx.x; x < n; x += int64_t(gridDim.x) * kBB) {
+        r[x] = v;
+        const int32_t deg = outdeg[x] + indeg[x];
+        contrib[x] = deg ? v / static_cast<double>(deg) : 0.0;
+        acc[x] = 0.0;
+    }
 }
 
 __global__ __launch_bounds__(kBB) void k_pr_by_id(const double *__restrict__ r, const int32_t *__restrict__ rank,
@@ -321,6 +404,10 @@ __global__ __launch_bounds__(kBB) void k_pr_by_id(const double *__restrict__ r, 
         out[v] = r[rank[v]];
 }
 
+// Iterations of PageRank queued between two reads of their changes (a round
+// trip costs about five launches).
+constexpr int kPrRound = 4;
+
 // Grid of a grid-stride launch over `work` elements: enough workgroups to
 // fill every CU a few times over, no more than the work needs.
 unsigned bsp_grid(int64_t work) {
@@ -328,8 +415,8 @@ unsigned bsp_grid(int64_t work) {
     return std::min(need, 256u * 16u);
 }
 
-// The item segments of the graph's blocks (rows only, or rows and columns),
-// staged on the device.
+// The item segments of the graph's blocks (rows and columns), staged on the
+// device.
 struct Segs {
     DArray<BspSeg> segs;
     DArray<int64_t> pre;
@@ -337,32 +424,21 @@ struct Segs {
     int64_t total = 0;
 };
 
-void make_segs(pgabb_graph *g, bool columns_too, bool by_gather_stripe, Segs &out) {
+void make_segs(pgabb_graph *g, Segs &out) {
     hipStream_t s = g->stream;
     const int32_t *arena = g->arena.get();
-    // (gather stripe, segment, items), ordered by the gather stripe
-    struct Entry {
-        int32_t stripe;
-        BspSeg seg;
-        int64_t items;
-    };
-    std::vector<Entry> ev;
-    for (const BlockInfo &bi : g->blocks) {
-        if (bi.nnz == 0) continue;
-        if (bi.nitems > 0)
-            ev.push_back({bi.j, BspSeg{arena + bi.off_items(), arena + bi.off_col(), g->base[bi.i], g->base[bi.j]},
-                          bi.nitems});
-        if (columns_too && bi.ncitems > 0)
-            ev.push_back({bi.i, BspSeg{arena + bi.off_citems(), arena + bi.off_crow(), g->base[bi.j], g->base[bi.i]},
-                          bi.ncitems});
-    }
-    if (by_gather_stripe)
-        std::stable_sort(ev.begin(), ev.end(), [](const Entry &a, const Entry &b) { return a.stripe < b.stripe; });
     std::vector<BspSeg> sv;
     std::vector<int64_t> pv(1, 0);
-    for (const Entry &e : ev) {
-        sv.push_back(e.seg);
-        pv.push_back(pv.back() + e.items);
+    for (const BlockInfo &bi : g->blocks) {
+        if (bi.nnz == 0) continue;
+        if (bi.nitems > 0) {
+            sv.push_back({arena + bi.off_items(), arena + bi.off_col(), g->base[bi.i], g->base[bi.j]});
+            pv.push_back(pv.back() + bi.nitems);
+        }
+        if (bi.ncitems > 0) {
+            sv.push_back({arena + bi.off_citems(), arena + bi.off_crow(), g->base[bi.j], g->base[bi.i]});
+            pv.push_back(pv.back() + bi.ncitems);
+        }
     }
     out.n = static_cast<int32_t>(sv.size());
     out.total = pv.back();
@@ -397,35 +473,24 @@ int64_t components(pgabb_graph *g, int32_t *label, bool on_device, int32_t *iter
     double kernel_ms = 0;
     if (n > 0) {
         require_blocks(g);
-        Segs sg;
-        make_segs(g, false, true, sg);
         DArray<int32_t> C(static_cast<size_t>(n), s);
-        DArray<unsigned long long> ctr(2 + kBspQueueWords, s);  // hooks, roots, work queues
-        Staged<unsigned long long> hctr(2, s);
+        DArray<unsigned long long> ctr(1 + kBspQueueWords, s);  // roots, work queues
+        Staged<unsigned long long> hctr(1, s);
         StreamTimer tm;
         tm.start(s);
-        k_sv_init<<<bsp_grid(n), kBB, 0, s>>>(C.get(), n);
-        PGABB_HIP(hipGetLastError());
-        tm.stop(s);
-        kernel_ms += tm.ms();
-        for (;;) {
-            // one hooking and one linking iteration; stop after a hooking
-            // pass that hooked nothing
-            tm.start(s);
-            zero_words(ctr.get(), 1, s);
-            zero_words(ctr.get() + 2, kBspQueueWords, s);
-            if (sg.total > 0)
-                k_sv_hook<<<bsp_grid(sg.total), kBB, 0, s>>>(sg.segs.get(), sg.pre.get(), sg.n, C.get(), ctr.get(),
-                                                             ctr.get() + 2);
+        zero_words(ctr.get(), 1 + kBspQueueWords, s);
+        k_sv_first<<<bsp_grid(n), kBB, 0, s>>>(g->row_off.get(), g->col.get(), n, C.get());
+        k_sv_link<<<bsp_grid(n), kBB, 0, s>>>(C.get(), n);
+        iters = 2;
+        if (g->m > 0) {
+            k_sv_second<<<bsp_grid(n), kBB, 0, s>>>(g->row_off.get(), g->col.get(), n, C.get());
             k_sv_link<<<bsp_grid(n), kBB, 0, s>>>(C.get(), n);
-            PGABB_HIP(hipGetLastError());
-            tm.stop(s);
-            PGABB_HIP(hipMemcpyAsync(hctr.get(), ctr.get(), sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-            PGABB_HIP(hipStreamSynchronize(s));
-            kernel_ms += tm.ms();
-            iters += 2;
-            if (hctr[0] == 0) break;
+            k_sv_hook_edges<<<std::min(bsp_grid(n), 2048u), kBB, 0, s>>>(g->row_off.get(), g->col.get(), n, C.get(),
+                                                                        ctr.get() + 1);
+            k_sv_link<<<bsp_grid(n), kBB, 0, s>>>(C.get(), n);
+            iters = 6;
         }
+        PGABB_HIP(hipGetLastError());
         DArray<int32_t> minid(static_cast<size_t>(n), s);
         DArray<int32_t> own;
         int32_t *dst = label;
@@ -433,19 +498,17 @@ int64_t components(pgabb_graph *g, int32_t *label, bool on_device, int32_t *iter
             own.reset(static_cast<size_t>(n), s);
             dst = own.get();
         }
-        tm.start(s);
         k_fill_i32<<<bsp_grid(n), kBB, 0, s>>>(minid.get(), INT32_MAX, n);
-        zero_words(ctr.get() + 1, 1, s);
-        k_sv_minid<<<std::min(bsp_grid(n), 512u), kBB, 0, s>>>(C.get(), g->rank.get(), n, minid.get(), ctr.get() + 1);
+        k_sv_minid<<<std::min(bsp_grid(n), 512u), kBB, 0, s>>>(C.get(), g->rank.get(), n, minid.get(), ctr.get());
         k_sv_label<<<bsp_grid(n), kBB, 0, s>>>(C.get(), g->rank.get(), minid.get(), n, dst);
         PGABB_HIP(hipGetLastError());
         tm.stop(s);
-        PGABB_HIP(hipMemcpyAsync(hctr.get() + 1, ctr.get() + 1, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+        PGABB_HIP(hipMemcpyAsync(hctr.get(), ctr.get(), sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
         if (!on_device)
             PGABB_HIP(hipMemcpyAsync(label, dst, sizeof(int32_t) * static_cast<size_t>(n), hipMemcpyDeviceToHost, s));
         PGABB_HIP(hipStreamSynchronize(s));
         kernel_ms += tm.ms();
-        comps = static_cast<int64_t>(hctr[1]);
+        comps = static_cast<int64_t>(hctr[0]);
     }
     if (iterations) *iterations = iters;
     g->t_kernel_ms = kernel_ms;
@@ -464,33 +527,42 @@ int32_t pagerank(pgabb_graph *g, double damping, double tol, int32_t max_iter, d
     if (n > 0) {
         require_blocks(g);
         Segs sg;
-        make_segs(g, true, false, sg);
+        make_segs(g, sg);
         DArray<double> r(static_cast<size_t>(n), s), contrib(static_cast<size_t>(n), s), acc(static_cast<size_t>(n), s);
-        DArray<double> derr(1, s);
-        Staged<double> herr(1, s);
+        DArray<double> derr(kPrRound, s);
+        Staged<double> herr(kPrRound, s);
         const double teleport = (1.0 - damping) / n;
         StreamTimer tm;
         tm.start(s);
-        k_pr_init<<<bsp_grid(n), kBB, 0, s>>>(r.get(), n, 1.0 / n);
+        k_pr_init<<<bsp_grid(n), kBB, 0, s>>>(r.get(), acc.get(), g->outdeg.get(), g->indeg.get(), n, 1.0 / n,
+                                              contrib.get());
         PGABB_HIP(hipGetLastError());
         tm.stop(s);
         kernel_ms += tm.ms();
-        while (iters < max_iter) {
+        for (bool stop = max_iter <= 0; !stop;) {
+            const int round = std::min(kPrRound, max_iter - iters);
             tm.start(s);
-            k_pr_prep<<<bsp_grid(n), kBB, 0, s>>>(r.get(), g->outdeg.get(), g->indeg.get(), n, contrib.get(), acc.get());
-            if (sg.total > 0)
-                k_pr_pull<<<bsp_grid(sg.total), kBB, 0, s>>>(sg.segs.get(), sg.pre.get(), sg.n, contrib.get(), acc.get());
-            zero_words(reinterpret_cast<unsigned long long *>(derr.get()), 1, s);  // +0.0 is all zero bits
-            k_pr_update<<<std::min(bsp_grid(n), 512u), kBB, 0, s>>>(r.get(), acc.get(), n, teleport, damping,
-                                                                   derr.get());
+            zero_words(reinterpret_cast<unsigned long long *>(derr.get()), kPrRound, s);  // +0.0 is all zero bits
+            for (int q = 0; q < round; ++q) {
+                const double *prev = q ? derr.get() + q - 1 : nullptr;
+                if (sg.total > 0)
+                    k_pr_pull<<<bsp_grid(sg.total), kBB, 0, s>>>(sg.segs.get(), sg.pre.get(), sg.n, contrib.get(),
+                                                                 acc.get(), prev, tol);
+                k_pr_update<<<std::min(bsp_grid(n), 512u), kBB, 0, s>>>(r.get(), acc.get(), g->outdeg.get(),
+                                                                       g->indeg.get(), n, teleport, damping,
+                                                                       contrib.get(), derr.get() + q, prev, tol);
+            }
             PGABB_HIP(hipGetLastError());
             tm.stop(s);
-            PGABB_HIP(hipMemcpyAsync(herr.get(), derr.get(), sizeof(double), hipMemcpyDeviceToHost, s));
+            PGABB_HIP(hipMemcpyAsync(herr.get(), derr.get(), sizeof(double) * kPrRound, hipMemcpyDeviceToHost, s));
             PGABB_HIP(hipStreamSynchronize(s));
             kernel_ms += tm.ms();
-            ++iters;
-            err = herr[0];
-            if (err < tol) break;
+            for (int q = 0; q < round && !stop; ++q) {
+                ++iters;
+                err = herr[q];
+                stop = err < tol;
+            }
+            stop = stop || iters >= max_iter;
         }
         DArray<double> own;
         double *dst = ranks;

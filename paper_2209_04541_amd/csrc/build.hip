@@ -268,7 +268,8 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
             PGABB_HIP(hipGetLastError());
             if (radix_sort_u64_bits(k1, k0, nullptr, nullptr, mu, 0, kbits, s)) std::swap(k0, k1);
             // sorted oriented keys now in k1
-            g->col.reset(static_cast<size_t>(mu), s);
+            // (rows are read in segments, which may reach past the last one)
+            g->col.reset(static_cast<size_t>(mu) + kSeg, s);
             k_row_counts_and_cols<<<cap_grid(mu), B, 0, s>>>(k1, mu, nb, g->outdeg.get(), g->col.get());
             PGABB_HIP(hipGetLastError());
         }
