@@ -156,8 +156,10 @@ void ensure_partition(pgabb_graph *g, const pgabb_tc_options &opt);
 // Shard of each task when the tasks are split over nshards devices.
 std::vector<int32_t> task_shards(const pgabb_graph *g, int32_t nshards);
 // Triangles containing each oriented edge, into out[m'] (device or host
-// memory); returns the triangle count.
-uint64_t edge_support(pgabb_graph *g, uint32_t *out, bool out_on_device);
+// memory); returns the triangle count.  in_off, in_pos: receive the in-edges
+// (see in_edges), which it makes, where the caller goes on with them (m' > 0).
+uint64_t edge_support(pgabb_graph *g, uint32_t *out, bool out_on_device, DArray<int64_t> *in_off = nullptr,
+                      DArray<uint32_t> *in_pos = nullptr);
 // In-edges of every vertex of the oriented graph: in_off (n + 1 offsets from
 // the kept in-degrees) and in_pos (the CSR positions of the edges, grouped by
 // their higher end, each group ascending in the lower end).

@@ -7,22 +7,34 @@
 // (a, b), (a, c) and (b, c).
 //
 // The edge is reached from its higher end: one wave owns a vertex b at a
-// time, stages N+(b) in an LDS hash table (each key with its position in the
-// row, and one counter per position), and for every in-edge (a, b) walks the
-// part of N+(a) after b (only c > b can lie in N+(b)), flattened over the
-// lanes, 64 in-edges at a time, looking each walked entry up in the table.
-// This reads sum_a d+(a) (d+(a) - 1) / 2 entries, against sum over edges
-// (a, b) of d+(b) when every N+(b) is walked from the lower end (3.6 x more
-// on R-MAT scale 20).  A hit counts (b, c) in LDS (flushed once per unit),
-// (a, b) in a per-in-edge LDS counter (flushed once per unit) and
-// (a, c), the walked entry, with a device atomic.  Work units are runs of at
-// most 64 in-edges of one owner (one per lane), so an owner with many
-// in-edges spreads over many waves (each stages N+(b) and flushes its own
-// counters; 64 measured faster than 128 – 1024);
-// units are listed from the highest rank down (the hubs, whose in-edges are
-// many, start first), only for owners with both in-edges and a non-empty
-// row, and dealt round-robin to eight work counters.  Rows longer than the
-// LDS region are searched and counted in device memory.
+// time, stages N+(b) in LDS with one counter per entry, and for every in-edge
+// (a, b) walks the part of N+(a) after b (only c > b can lie in N+(b)) in
+// segments of kSeg entries, one per lane and load, flattened over the lanes
+// (tc_device.hpp), looking each walked entry up.  This reads sum_a d+(a)
+// (d+(a) - 1) / 2 entries, against sum over edges (a, b) of d+(b) when every
+// N+(b) is walked from the lower end (3.6 x more on R-MAT scale 20).  A hit
+// counts (b, c) in LDS (flushed once per unit), (a, b) in a per-in-edge LDS
+// counter (flushed once per unit) and (a, c), the walked entry, with a device
+// atomic.
+//
+// N+(b) is staged as a bitmap of the kSupHubs highest ranks ("hubs", which
+// hold most walked entries on skewed graphs) with the number of entries
+// before each word, so an entry is found, and its position known, with no
+// search; entries below the hubs go to a small hash table.  Held in one hash
+// table of all entries (load up to 2/3, probed until the last of 64 lanes is
+// done) a chunk of 64 walked entries cost 105 vector and 97 scalar
+// instructions and the pass was bound by them: R-MAT scale 20 7.15 ms with
+// the walked-edge atomics, 6.50 without.  Now 4.75 and 2.0 ms: bound by the
+// 424 M device atomics, which go past the L2s (one segment per lane in each
+// atomic instruction, touching four times the lines, took 9.8 ms).
+//
+// Work units are runs of at most 64 in-edges of one owner (one per lane), so
+// an owner with many in-edges spreads over many waves (each stages N+(b) and
+// flushes its own counters); units are listed from the highest rank down (the
+// hubs, whose in-edges are many, start first), only for owners with both
+// in-edges and a non-empty row, and dealt round-robin to eight work counters.
+// Rows that do not fit the LDS region are searched and counted in device
+// memory.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,40 +50,35 @@ namespace pgabb {
 namespace {
 
 constexpr int kSupWaves = 4;
-constexpr int kSupCap = 682;      // longest row staged in LDS (table load <= 2/3)
-constexpr int kSupTableLg = 10;   // at most 1024 hash slots
 constexpr int kSupB = 256;
-constexpr int kSupUnroll = 2;     // walk chunks in flight
+constexpr int kSupHubs = 8192;                // ranks of the bitmap: four words a lane
+constexpr int kSupWords = kSupHubs / 32;
+constexpr int kSupCap = 1024;                 // longest row staged in LDS
+constexpr int kSupLowCap = 341;               // entries below the hubs that are (table load <= 2/3)
+constexpr int kSupTableLg = 9;
 constexpr int kSupUnitEdges = kWave;  // in-edges per work unit (one per lane)
+// Units per grab (random geometric graph, 200,003 vertices: 549 us at 1, 399
+// at 2, 347 at 4, where a unit is a short chain of dependent loads).
+constexpr int kSupGrab = 4;
 constexpr int kSupQueues = 8;       // work counters, kSupQueueStride words apart
 constexpr int kSupQueueStride = 32;
 
 struct SupportLds {
-    int32_t key[1 << kSupTableLg];      // hash table of N+(b): entry, or -1
-    int16_t pos[1 << kSupTableLg];      // its position in the row
-    uint32_t cnt[kSupCap];              // triangles found so far on edge (b, row[x])
-    uint32_t hits[kWave];               // triangles found on each in-edge of the group
-    int32_t own[kSupUnroll * kWave];    // list positions of the flattened walk
+    uint32_t bits[kSupWords + 1];      // N+(b)'s hubs; a zero word after them
+    uint32_t own[kWave];               // list positions of the flattened walk
+    uint16_t before[kSupWords + 2];    // N+(b)'s hubs before each word
+    int32_t key[1 << kSupTableLg];     // hash table of the entries below the hubs: entry, or -1
+    uint16_t pos[1 << kSupTableLg];    // its position in the row
+    uint32_t cnt[kSupCap / 4];         // triangles found on edge (b, row[x]), a byte each: a unit's
+                                       // 64 in-edges find at most one each
+    uint32_t hits[kWave];              // triangles found on each in-edge of the unit
 };
 
-// Entries after every CSR position in its row (a thread per row): the
-// length of the walk an in-edge at that position starts.
+// Entries after every CSR position in its row: the length of the walk an
+// in-edge at that position starts.
 __global__ __launch_bounds__(kSupB) void k_sup_rest(const int64_t *__restrict__ row_off, int32_t n,
                                                      int32_t *__restrict__ rest) {
-    for (int64_t a = blockIdx.x * static_cast<int64_t>(kSupB) + threadIdx.x; a < n;
-         a += static_cast<int64_t>(gridDim.x) * kSupB) {
-        const int64_t end = row_off[a + 1];
-        for (int64_t e = row_off[a]; e < end; ++e) rest[e] = static_cast<int32_t>(end - e - 1);
-    }
-}
-
-// The walk length of every in-edge, in in-edge order.
-__global__ __launch_bounds__(kSupB) void k_sup_in_len(const uint32_t *__restrict__ in_pos,
-                                                       const int32_t *__restrict__ rest, int64_t m,
-                                                       int32_t *__restrict__ in_len) {
-    for (int64_t k = blockIdx.x * static_cast<int64_t>(kSupB) + threadIdx.x; k < m;
-         k += static_cast<int64_t>(gridDim.x) * kSupB)
-        in_len[k] = rest[in_pos[k]];
+    for_row_entries(row_off, n, [&](int32_t, int64_t e, int64_t e1) { rest[e] = static_cast<int32_t>(e1 - e - 1); });
 }
 
 // Work units of every owner, in processing order (rank n - 1 first): one per
@@ -115,64 +122,38 @@ __global__ __launch_bounds__(kSupB) void k_sup_widen(const int32_t *__restrict__
         out[v] = in[v];
 }
 
-// Loads elements base + q * 64 + lane (q < U) of the flattened walk over the
-// in-edge lists of the group (lane l: positions pb .. pb + len of the column
-// array, at position pre of the walk), with their column positions and the
-// lane whose list holds each; past total a lane gets value -1.  Lists are
-// found as in walk_load (tc_device.hpp): list starts scattered into `own`, then a running
-// maximum over the lanes.
-template <int U>
-__device__ __forceinline__ void sup_walk_load(int32_t (&w)[U], uint32_t (&ev)[U], int32_t (&sl)[U], int32_t base,
-                                              int32_t total, int32_t pre, int32_t len, uint32_t pb, uint32_t &carry,
-                                              int32_t *own, gptr<int32_t> cl, int lane) {
-    const int32_t p = pre - base;
-    if (len > 0 && p >= 0 && p < U * kWave) own[p] = lane + 1;
-    wave_lds_sync();
-    uint32_t o[U];
-#pragma unroll
-    for (int q = 0; q < U; ++q) {
-        o[q] = static_cast<uint32_t>(own[q * kWave + lane]);
-        own[q * kWave + lane] = 0;
-    }
-    wave_lds_sync();
-    const uint32_t rel = pb - static_cast<uint32_t>(pre);  // element e sits at position rel + e
-#pragma unroll
-    for (int q = 0; q < U; ++q) {
-        const uint32_t s = max(wave_max_scan_dpp(o[q]), carry);
-        carry = __builtin_amdgcn_readlane(s, kWave - 1);
-        const int32_t e = base + q * kWave + lane;
-        const bool inb = e < total;
-        sl[q] = static_cast<int32_t>(s) - 1;
-        ev[q] = __shfl(rel, sl[q]) + static_cast<uint32_t>(e);
-        const int32_t x = cl[inb ? ev[q] : 0u];
-        w[q] = inb ? x : -1;
-    }
-}
-
-__global__ __launch_bounds__(kSupWaves *kWave) void k_edge_support(const int64_t *__restrict__ row_off,
+// Six waves per SIMD, what the LDS leaves room for.
+__global__ __launch_bounds__(kSupWaves *kWave) __attribute__((amdgpu_waves_per_eu(6)))
+void k_edge_support(const int64_t *__restrict__ row_off,
                                                                     const int32_t *__restrict__ col,
                                                                     const int64_t *__restrict__ in_off,
                                                                     const uint32_t *__restrict__ in_pos,
-                                                                    const int32_t *__restrict__ in_len,
+                                                                    const int32_t *__restrict__ rest,
                                                                     const int2 *__restrict__ units,
                                                                     const int64_t *__restrict__ nunits_dev,
+                                                                    int32_t hub_lo,
                                                                     uint32_t *__restrict__ support,
                                                                     unsigned long long *__restrict__ next,
                                                                     unsigned long long *__restrict__ total) {
     __shared__ SupportLds s_lds[kSupWaves];
     SupportLds &L = s_lds[threadIdx.x / kWave];
     const int lane = lane_id();
-    gptr<int64_t> ro = as_global(row_off);
-    gptr<int32_t> cl = as_global(col);
-    gptr<int64_t> io = as_global(in_off);
-    gptr<uint32_t> ip = as_global(in_pos);
-    gptr<int32_t> il = as_global(in_len);
-#pragma unroll
-    for (int q = 0; q < kSupUnroll; ++q) L.own[q * kWave + lane] = 0;
+    const gptr<int64_t> ro = as_global(row_off);
+    const gptr<int32_t> cl = as_global(col);
+    const gptr<int64_t> io = as_global(in_off);
+    const gptr<uint32_t> ip = as_global(in_pos);
+    const gptr<int32_t> rs = as_global(rest);
+    L.own[lane] = 0;
+    if (lane == 0) L.bits[kSupWords] = 0u;
     wave_lds_sync();
     const gptr<int32_t> un = as_global(reinterpret_cast<const int32_t *>(units));  // (owner, first in-edge) pairs
     const int64_t nunits = *as_global(nunits_dev);
     unsigned long long found = 0;
+    // units per grab: kSupGrab share their headers' round trips; one where that
+    // would leave waves without units (R-MAT scale 12, 77 us: 96 at four)
+    const int64_t waves = static_cast<int64_t>(gridDim.x) * kSupWaves;
+    const int grab = static_cast<int>(max(min(nunits / (4 * waves), static_cast<int64_t>(kSupGrab)),
+                                          static_cast<int64_t>(1)));
     const int home = static_cast<int>(blockIdx.x % kSupQueues);
     for (int qi = 0; qi < kSupQueues; ++qi) {
       const int qq = (home + qi) % kSupQueues;
@@ -180,107 +161,230 @@ __global__ __launch_bounds__(kSupWaves *kWave) void k_edge_support(const int64_t
         unsigned long long c0 = 0;
         if (lane == 0) c0 = atomicAdd(&next[qq * kSupQueueStride], 1ull);
         c0 = shfl_t(c0, 0);
-        const int64_t u = static_cast<int64_t>(c0) * kSupQueues + qq;  // unit u sits on queue u mod 8
-        if (u >= nunits) break;
-        const int32_t b = un[2 * u];
-        const int64_t b0 = ro[b];
-        const int32_t d = static_cast<int32_t>(ro[b + 1] - b0);
-        const int64_t i0 = io[b] + un[2 * u + 1];
-        const int64_t nin = min(io[b + 1] - i0, static_cast<int64_t>(kSupUnitEdges));
-        const bool staged = d <= kSupCap;
-        // table of 2^lg >= 1.5 d slots (64 .. 2^kSupTableLg)
-        int lg = 6;
-        while ((1 << lg) * 2 < 3 * d && lg < kSupTableLg) ++lg;
+        const int64_t u0 = (static_cast<int64_t>(c0) * kSupQueues + qq) * grab;  // grab g sits on queue g mod 8
+        if (u0 >= nunits) break;
+        const int ng = static_cast<int>(min(nunits - u0, static_cast<int64_t>(grab)));
+        // the units' headers, one per lane; then per unit its in-edges, one per
+        // lane (position of (a, b) and its walk's length), and the first 64
+        // entries of N+(b): four round trips for the whole grab
+        int32_t hb = 0, hd = 0, hin = 0;
+        int64_t hb0 = 0, hi0 = 0;
+        if (lane < ng) {
+            hb = un[2 * (u0 + lane)];
+            const int32_t i = un[2 * (u0 + lane) + 1];
+            hb0 = ro[hb];
+            hd = static_cast<int32_t>(ro[hb + 1] - hb0);
+            hi0 = io[hb] + i;
+            hin = static_cast<int32_t>(min(io[hb + 1] - hi0, static_cast<int64_t>(kSupUnitEdges)));
+        }
+        uint32_t g_eab[kSupGrab];
+        int32_t g_len[kSupGrab], g_v0[kSupGrab];
+#pragma unroll
+        for (int j = 0; j < kSupGrab; ++j) {  // (hin, hd: 0 past the grab's end)
+            const int64_t i0 = shfl_t(hi0, j), b0 = shfl_t(hb0, j);  // (every lane shuffles)
+            g_eab[j] = lane < __builtin_amdgcn_readlane(hin, j) ? ip[i0 + lane] : 0u;
+            g_v0[j] = lane < __builtin_amdgcn_readlane(hd, j) ? cl[b0 + lane] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < kSupGrab; ++j)
+            g_len[j] = lane < __builtin_amdgcn_readlane(hin, j) ? rs[g_eab[j]] : 0;
+#pragma unroll 1
+        for (int j = 0; j < ng; ++j) {
+        const int32_t b = __builtin_amdgcn_readlane(hb, j);
+        const int32_t d = __builtin_amdgcn_readlane(hd, j);
+        const int32_t nin = __builtin_amdgcn_readlane(hin, j);
+        const int64_t b0 = shfl_t(hb0, j);
+        uint32_t eab = g_eab[0];
+        int32_t len = g_len[0], v0 = g_v0[0];
+#pragma unroll
+        for (int q = 1; q < kSupGrab; ++q)
+            if (j == q) {
+                eab = g_eab[q];
+                len = g_len[q];
+                v0 = g_v0[q];
+            }
+        // ---- stage N+(b): its entries below the hubs are its first `low`
+        int32_t low = __popcll(__ballot(lane < d && v0 < hub_lo));
+        for (int32_t x0 = kWave; x0 < d && low == x0; x0 += kWave) {
+            const int32_t x = x0 + lane;
+            low += __popcll(__ballot(x < d && cl[b0 + x] < hub_lo));
+        }
+        const bool staged = d <= kSupCap && low <= kSupLowCap;
+        const bool hubs = d > low;
+        int lg = 6;  // table of 2^lg >= 1.5 low slots
+        while ((1 << lg) * 2 < 3 * low && lg < kSupTableLg) ++lg;
         const uint32_t tmask = (1u << lg) - 1u;
         const int shift = 24 - lg;
         if (staged) {
-            for (int x = lane; x < (1 << lg); x += kWave) L.key[x] = -1;
+            if (hubs) {
+#pragma unroll
+                for (int q = 0; q < kSupWords / kWave; ++q) L.bits[q * kWave + lane] = 0u;
+            }
+            for (int x = lane; x < (d + 3) / 4; x += kWave) L.cnt[x] = 0u;
+            if (low > 0)
+                for (int x = lane; x < (1 << lg); x += kWave) L.key[x] = -1;
             wave_lds_sync();
             for (int x = lane; x < d; x += kWave) {
-                const int32_t v = cl[b0 + x];
-                L.cnt[x] = 0;
-                uint32_t h = hash_slot(v, shift, tmask);
-                while (atomicCAS(&L.key[h], -1, v) != -1) h = (h + 1) & tmask;
-                L.pos[h] = static_cast<int16_t>(x);
-            }
-            wave_lds_sync();
-        }
-        const int32_t hi_b = cl[b0 + d - 1];  // no c above N+(b)'s last entry can match
-        {  // the unit's in-edges, one per lane: position of (a, b) and its walk's length
-            const int64_t k = lane;
-            uint32_t eab = 0;
-            int32_t len = 0;
-            if (k < nin) {
-                eab = ip[i0 + k];
-                len = il[i0 + k];
-            }
-            const int32_t incl = wave_inclusive_scan(len);
-            const int32_t pre = incl - len;
-            const int32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
-            L.hits[lane] = 0;
-            wave_lds_sync();
-            // Hits on a lane's current walk gather in a register and go to
-            // the walk's LDS counter when the lane moves to another walk.
-            int32_t acc_lo = 0;
-            uint32_t acc = 0;
-            uint32_t carry = 0;
-            int32_t w[kSupUnroll], sl[kSupUnroll];
-            uint32_t ev[kSupUnroll];
-            if (tot > 0) sup_walk_load<kSupUnroll>(w, ev, sl, 0, tot, pre, len, eab + 1u, carry, L.own, cl, lane);
-            for (int32_t f = 0; f < tot; f += kSupUnroll * kWave) {
-                int32_t wn[kSupUnroll], sn[kSupUnroll];
-                uint32_t en[kSupUnroll];
-                sup_walk_load<kSupUnroll>(wn, en, sn, f + kSupUnroll * kWave, tot, pre, len, eab + 1u, carry, L.own,
-                                          cl, lane);
-#pragma unroll
-                for (int u = 0; u < kSupUnroll; ++u) {
-                    const int32_t c = w[u];
-                    int32_t at = -1;  // position of c in N+(b)
-                    if (staged) {
-                        bool go = c >= 0 && c <= hi_b;
-                        uint32_t h = hash_slot(c, shift, tmask);
-                        while (__ballot(go) != 0) {
-                            const int32_t kv = L.key[h];
-                            if (go && kv == c) at = L.pos[h];
-                            go = go && kv != -1 && kv != c;
-                            h = (h + 1) & tmask;
-                        }
-                    } else if (c >= 0 && c <= hi_b) {
-                        int32_t lo = 0, hi = d;
-                        while (lo < hi) {
-                            const int32_t mid = (lo + hi) >> 1;
-                            if (cl[b0 + mid] < c) lo = mid + 1;
-                            else hi = mid;
-                        }
-                        if (lo < d && cl[b0 + lo] == c) at = lo;
-                    }
-                    if (at >= 0) {
-                        ++found;
-                        atomicAdd(&support[ev[u]], 1u);
-                        if (sl[u] != acc_lo) {
-                            if (acc) atomicAdd(&L.hits[acc_lo], acc);
-                            acc_lo = sl[u];
-                            acc = 0;
-                        }
-                        ++acc;
-                        if (staged) atomicAdd(&L.cnt[at], 1u);
-                        else atomicAdd(&support[b0 + at], 1u);
-                    }
-                    w[u] = wn[u];
-                    sl[u] = sn[u];
-                    ev[u] = en[u];
+                const int32_t v = x < kWave ? v0 : cl[b0 + x];
+                const int32_t h = v - hub_lo;
+                if (h >= 0) {
+                    atomicOr(&L.bits[h >> 5], 1u << (h & 31));
+                } else {
+                    uint32_t s = hash_slot(v, shift, tmask);
+                    while (atomicCAS(&L.key[s], -1, v) != -1) s = (s + 1) & tmask;
+                    L.pos[s] = static_cast<uint16_t>(x);
                 }
             }
-            if (acc) atomicAdd(&L.hits[acc_lo], acc);
             wave_lds_sync();
-            if (k < nin && L.hits[lane]) atomicAdd(&support[eab], L.hits[lane]);
-            wave_lds_sync();  // before the next unit resets the counters
+            if (hubs) {  // lane l takes words 4 l .. 4 l + 3
+                int32_t pc[4], sum = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    pc[q] = sum;
+                    sum += __popc(L.bits[4 * lane + q]);
+                }
+                const int32_t base = low + wave_inclusive_scan(sum) - sum;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) L.before[4 * lane + q] = static_cast<uint16_t>(base + pc[q]);
+            }
         }
-        if (staged) {
+        L.hits[lane] = 0;
+        wave_lds_sync();
+        // ---- the walk
+        const int32_t nseg = segs_of(len);
+        const int32_t incl = wave_inclusive_scan(nseg);
+        const int32_t pre = incl - nseg;
+        const int32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+        const uint32_t rel = eab + 1u - static_cast<uint32_t>(kSeg * pre);  // segment t starts at rel + kSeg t
+        const int32_t end = len + kSeg * pre;                              // entries left at segment t: end - kSeg t
+        uint32_t carry = 0;
+        seg_t v, vn;
+        int32_t n = 0, nn = 0, sl = 0, sn = 0;
+        uint32_t ev = 0, en = 0;
+        auto load = [&](int32_t base, seg_t &w, int32_t &cnt, int32_t &src, uint32_t &at) {
+            const int32_t p = pre - base;
+            if (nseg > 0 && p >= 0 && p < kWave) L.own[p] = static_cast<uint32_t>(lane + 1);
             wave_lds_sync();
-            for (int x = lane; x < d; x += kWave)
-                if (L.cnt[x]) atomicAdd(&support[b0 + x], L.cnt[x]);
-            wave_lds_sync();  // before the next unit is staged
+            const uint32_t o = L.own[lane];
+            L.own[lane] = 0;
+            wave_lds_sync();
+            const uint32_t s1 = max(wave_max_scan_dpp(o), carry);
+            carry = __builtin_amdgcn_readlane(s1, kWave - 1);
+            const int32_t t = base + lane;
+            src = static_cast<int32_t>(s1) - 1;
+            at = __shfl(rel, src) + static_cast<uint32_t>(kSeg * t);
+            const int32_t left = __shfl(end, src) - kSeg * t;
+            const bool inb = t < tot;
+            cnt = inb ? left : 0;
+            w = *reinterpret_cast<const __attribute__((address_space(1))) seg_t *>(cl + (inb ? at : 0u));
+        };
+        int32_t acc_lo = 0;  // hits on a lane's current list gather in a register
+        uint32_t acc = 0;
+        auto probe = [&](int32_t segs) {  // segments in the batch
+            uint32_t hits = 0;  // of the segment's entries, a bit each
+            if (staged) {
+                if (hubs) {
+                    int32_t h[kSeg];
+                    uint32_t word[kSeg];
+#pragma unroll
+                    for (int r = 0; r < kSeg; ++r) {
+                        h[r] = v[r] - hub_lo;
+                        word[r] = L.bits[r < n && h[r] >= 0 ? h[r] >> 5 : kSupWords];
+                    }
+#pragma unroll
+                    for (int r = 0; r < kSeg; ++r) {
+                        if (((word[r] >> (h[r] & 31)) & 1u) == 0u) continue;
+                        const uint32_t at = L.before[h[r] >> 5] + __popc(word[r] & ((1u << (h[r] & 31)) - 1u));
+                        atomicAdd(&L.cnt[at >> 2], 1u << (8 * (at & 3u)));
+                        hits |= 1u << r;
+                    }
+                }
+                if (low > 0) {
+                    // the segment's entries probe together: their reads overlap
+                    bool go[kSeg], any = false;
+                    uint32_t s[kSeg];
+#pragma unroll
+                    for (int r = 0; r < kSeg; ++r) {
+                        go[r] = r < n && v[r] < hub_lo;
+                        s[r] = hash_slot(v[r], shift, tmask);
+                        any |= go[r];
+                    }
+                    while (__ballot(any) != 0) {
+                        any = false;
+#pragma unroll
+                        for (int r = 0; r < kSeg; ++r) {
+                            const int32_t kv = L.key[s[r]];
+                            if (go[r] && kv == v[r]) {
+                                const uint32_t at = L.pos[s[r]];
+                                atomicAdd(&L.cnt[at >> 2], 1u << (8 * (at & 3u)));
+                                hits |= 1u << r;
+                            }
+                            go[r] = go[r] && kv != -1 && kv != v[r];
+                            s[r] = (s[r] + 1) & tmask;
+                            any |= go[r];
+                        }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < kSeg; ++r) {
+                    if (r >= n) continue;
+                    int32_t lo = 0, hi = d;
+                    while (lo < hi) {
+                        const int32_t mid = (lo + hi) >> 1;
+                        if (cl[b0 + mid] < v[r]) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    if (lo < d && cl[b0 + lo] == v[r]) {
+                        atomicAdd(&support[b0 + lo], 1u);
+                        hits |= 1u << r;
+                    }
+                }
+            }
+            // the walked edges: 16 segments at a time with one entry per lane, so
+            // that an atomic instruction touches consecutive words (one segment
+            // per lane would touch each line four times)
+            if (__ballot(hits != 0u) == 0) return;
+#pragma unroll
+            for (int k = 0; k < kSeg; ++k) {
+                if (k * (kWave / kSeg) >= segs) break;
+                const int from = k * (kWave / kSeg) + lane / kSeg;
+                const uint32_t hs = __shfl(hits, from);
+                const uint32_t at = __shfl(ev, from) + static_cast<uint32_t>(lane % kSeg);
+                if ((hs >> (lane % kSeg)) & 1u) atomicAdd(&support[at], 1u);
+            }
+            const uint32_t hit = __popc(hits);
+            if (hit) {
+                found += hit;
+                if (sl != acc_lo) {
+                    if (acc) atomicAdd(&L.hits[acc_lo], acc);
+                    acc_lo = sl;
+                    acc = 0;
+                }
+                acc += hit;
+            }
+        };
+        if (tot > 0) {
+            load(0, v, n, sl, ev);
+            for (int32_t f = kWave; f < tot; f += kWave) {  // the next batch loads while one is probed
+                load(f, vn, nn, sn, en);
+                probe(kWave);
+                v = vn;
+                n = nn;
+                sl = sn;
+                ev = en;
+            }
+            probe((tot - 1) % kWave + 1);
+        }
+        if (acc) atomicAdd(&L.hits[acc_lo], acc);
+        wave_lds_sync();
+        if (lane < nin && L.hits[lane]) atomicAdd(&support[eab], L.hits[lane]);
+        if (staged)
+            for (int x = lane; x < d; x += kWave) {
+                const uint32_t c = (L.cnt[x >> 2] >> (8 * (x & 3))) & 0xffu;
+                if (c) atomicAdd(&support[b0 + x], c);
+            }
+        wave_lds_sync();  // before the next unit is staged
         }
       }
     }
@@ -305,7 +409,8 @@ void in_edges(pgabb_graph *g, DArray<int64_t> &in_off, DArray<uint32_t> &in_pos)
     in_pos = std::move(alt ? pos_alt : pos);
 }
 
-uint64_t edge_support(pgabb_graph *g, uint32_t *out, bool out_on_device) {
+uint64_t edge_support(pgabb_graph *g, uint32_t *out, bool out_on_device, DArray<int64_t> *in_off_out,
+                      DArray<uint32_t> *in_pos_out) {
     hipStream_t s = g->stream;
     const auto t0 = std::chrono::steady_clock::now();
     const int64_t m = g->m;
@@ -325,19 +430,14 @@ uint64_t edge_support(pgabb_graph *g, uint32_t *out, bool out_on_device) {
         }
         // in-edges of every vertex: CSR positions sorted by the higher end
         // (stable, so ascending in the lower end), offsets from the kept
-        // in-degrees
+        // in-degrees; and the length of the walk that each starts
         DArray<int32_t> rest(static_cast<size_t>(m), s);
-        k_sup_rest<<<grid_for(n, kSupB), kSupB, 0, s>>>(g->row_off.get(), n, rest.get());
+        k_sup_rest<<<std::min(grid_for(n, kSupB / 16), 16384u), kSupB, 0, s>>>(g->row_off.get(), n, rest.get());
         PGABB_HIP(hipGetLastError());
         DArray<int64_t> in_off;
         DArray<uint32_t> in_pos_arr;
         in_edges(g, in_off, in_pos_arr);
         const uint32_t *in_pos = in_pos_arr.get();
-        DArray<int32_t> in_len(static_cast<size_t>(m), s);
-        k_sup_in_len<<<grid_for(m, kSupB), kSupB, 0, s>>>(in_pos, rest.get(), m, in_len.get());
-        PGABB_HIP(hipGetLastError());
-        rest.release();
-
         // work units (at most one per owner plus one per kSupUnitEdges in-edges)
         DArray<int64_t> upre(static_cast<size_t>(n) + 1, s);
         const int64_t max_units = static_cast<int64_t>(n) + m / kSupUnitEdges + 1;
@@ -352,13 +452,14 @@ uint64_t edge_support(pgabb_graph *g, uint32_t *out, bool out_on_device) {
         DArray<unsigned long long> ctr(kCtr, s);
         PGABB_HIP(hipMemsetAsync(ctr.get(), 0, kCtr * sizeof(unsigned long long), s));
         PGABB_HIP(hipMemsetAsync(sup, 0, sizeof(uint32_t) * static_cast<size_t>(m), s));
-        // four workgroups of four waves fit a CU's LDS
+        // six workgroups of four waves fit a CU's LDS
         const int64_t want = (max_units + kSupWaves - 1) / kSupWaves;
-        const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want, 256 * 4)));
+        const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want, 256 * 6)));
         StreamTimer tm;
         tm.start(s);
         k_edge_support<<<grid, kSupWaves * kWave, 0, s>>>(g->row_off.get(), g->col.get(), in_off.get(), in_pos,
-                                                           in_len.get(), units.get(), upre.get() + n, sup, ctr.get(),
+                                                           rest.get(), units.get(), upre.get() + n,
+                                                           std::max(0, n - kSupHubs), sup, ctr.get(),
                                                            ctr.get() + kCtr - 1);
         PGABB_HIP(hipGetLastError());
         tm.stop(s);
@@ -369,6 +470,8 @@ uint64_t edge_support(pgabb_graph *g, uint32_t *out, bool out_on_device) {
             PGABB_HIP(hipMemcpyAsync(out, sup, sizeof(uint32_t) * static_cast<size_t>(m), hipMemcpyDeviceToHost,
                                      s));
         PGABB_HIP(hipStreamSynchronize(s));
+        if (in_off_out) *in_off_out = std::move(in_off);
+        if (in_pos_out) *in_pos_out = std::move(in_pos_arr);
         triangles = h[0];
         g->t_kernel_ms = tm.ms();
         g->kernel_launches = 1;

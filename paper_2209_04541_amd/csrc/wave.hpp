@@ -105,6 +105,18 @@ __device__ __forceinline__ gptr<T> as_global(const T *p) {
     return (gptr<T>)(p);
 }
 
+// Calls f(row, e, e1) for every entry e of every row of a CSR, e1 the row's
+// end: 16 lanes take a row (rows are mostly short; a thread per row reads them
+// uncoalesced and waits for the longest of 64).
+template <class F>
+__device__ __forceinline__ void for_row_entries(const int64_t *__restrict__ row_off, int32_t n, F f) {
+    const int64_t per = blockDim.x / 16;
+    for (int64_t r = blockIdx.x * per + threadIdx.x / 16; r < n; r += gridDim.x * per) {
+        const int64_t e1 = row_off[r + 1];
+        for (int64_t e = row_off[r] + (threadIdx.x & 15); e < e1; e += 16) f(static_cast<int32_t>(r), e, e1);
+    }
+}
+
 // Sum across the wave, returned to every lane.
 template <class T>
 __device__ __forceinline__ T wave_sum(T x) {
