@@ -4,7 +4,9 @@
 // peeling does.
 //
 // One support pass counts the triangles of every edge; then each round
-// takes the live edges with fewer than k - 2 (the round's frontier), and for
+// takes the live edges with fewer than k - 2 (the round's frontier: found by
+// a scan for the first round, and afterwards listed by whoever takes the
+// triangle that brings an edge below), and for
 // every triangle a frontier edge closes with two edges that are still there,
 // the triangle vanishes: each of its edges outside the frontier loses one
 // from its count.  A triangle with two or three frontier edges is handled
@@ -35,15 +37,17 @@ namespace {
 
 constexpr int kKB = 256;
 constexpr int kPeelWaves = 4;
+// Groups of a round per wave (peeling of R-MAT scale 18, k = 8, at 4 / 16 / 64:
+// 1.97 / 1.61 / 1.82 ms; of a random geometric graph 0.63 / 0.74 / 1.05).
+constexpr int kPeelGroups = 8;
+constexpr int kTrussRound = 4;  // rounds queued per host round trip
 
 enum : uint8_t { kLive = 0, kDying = 1, kDead = 2 };
 
-// Lower end (row) of every oriented edge, a thread per row.
+// Lower end (row) of every oriented edge.
 __global__ __launch_bounds__(kKB) void k_kt_rows(const int64_t *__restrict__ row_off, int32_t n,
                                                   int32_t *__restrict__ lo_end) {
-    for (int64_t a = blockIdx.x * static_cast<int64_t>(kKB) + threadIdx.x; a < n;
-         a += static_cast<int64_t>(gridDim.x) * kKB)
-        for (int64_t e = row_off[a]; e < row_off[a + 1]; ++e) lo_end[e] = static_cast<int32_t>(a);
+    for_row_entries(row_off, n, [&](int32_t a, int64_t e, int64_t) { lo_end[e] = a; });
 }
 
 // Lower end of the edge in every in-edge slot.
@@ -61,37 +65,54 @@ __global__ __launch_bounds__(kKB) void k_kt_clear(uint8_t *__restrict__ state, i
         state[e] = kLive;
 }
 
-// The frontier: live edges with fewer than `need` triangles become dying
-// and are appended to `front` (one counter atomic per wave).
+// The first frontier: live edges with fewer than `need` triangles become dying
+// and are appended to `front`, with one counter atomic per workgroup and
+// kFrontPer * kKB edges (one per wave of 64 edges took 446 us on R-MAT scale
+// 18: 59 K atomics on one word).
+constexpr int kFrontPer = 16;
 __global__ __launch_bounds__(kKB) void k_kt_front(const uint32_t *__restrict__ sup, int64_t m, uint32_t need,
                                                    uint8_t *__restrict__ state, uint32_t *__restrict__ front,
                                                    unsigned long long *__restrict__ nfront) {
-    const int lane = lane_id();
-    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-    for (int64_t base = blockIdx.x * static_cast<int64_t>(kKB); base < m;
-         base += static_cast<int64_t>(gridDim.x) * kKB) {
-        const int64_t e = base + threadIdx.x;  // the whole wave iterates together
-        bool take = false;
-        if (e < m && state[e] == kLive && sup[e] < need) {
-            take = true;
-            state[e] = kDying;
+    __shared__ uint32_t s_n;
+    __shared__ unsigned long long s_at;
+    for (int64_t base = blockIdx.x * static_cast<int64_t>(kKB) * kFrontPer; base < m;
+         base += static_cast<int64_t>(gridDim.x) * kKB * kFrontPer) {
+        if (threadIdx.x == 0) s_n = 0;
+        __syncthreads();
+        uint32_t mine = 0, take = 0;
+#pragma unroll
+        for (int q = 0; q < kFrontPer; ++q) {
+            const int64_t e = base + q * kKB + threadIdx.x;
+            if (e < m && sup[e] < need) take |= 1u << q;
         }
-        const uint64_t mask = __ballot(take);
-        if (mask == 0) continue;
-        unsigned long long at = 0;
-        if (lane == 0) at = atomicAdd(nfront, static_cast<unsigned long long>(__popcll(mask)));
-        at = shfl_t(at, 0);
-        if (take) front[at + __popcll(mask & below)] = static_cast<uint32_t>(e);
+        mine = __popc(take);
+        uint32_t at = mine ? atomicAdd(&s_n, mine) : 0u;
+        __syncthreads();
+        if (threadIdx.x == 0 && s_n) s_at = atomicAdd(nfront, static_cast<unsigned long long>(s_n));
+        __syncthreads();
+        while (take) {
+            const int q = __builtin_ctz(take);
+            take &= take - 1;
+            const int64_t e = base + q * kKB + threadIdx.x;
+            state[e] = kDying;
+            front[s_at + at++] = static_cast<uint32_t>(e);
+        }
+        __syncthreads();  // before the next turn's counter
     }
 }
 
-__global__ __launch_bounds__(kKB) void k_kt_kill(const uint32_t *__restrict__ front,
+// After a round: its frontier is dead, the next one's edges are dying.
+__global__ __launch_bounds__(kKB) void k_kt_turn(const uint32_t *__restrict__ front,
                                                   const unsigned long long *__restrict__ nfront,
+                                                  const uint32_t *__restrict__ after,
+                                                  const unsigned long long *__restrict__ nafter,
                                                   uint8_t *__restrict__ state) {
-    const int64_t cnt = static_cast<int64_t>(*nfront);
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(kKB) + threadIdx.x; i < cnt;
-         i += static_cast<int64_t>(gridDim.x) * kKB)
-        state[front[i]] = kDead;
+    const int64_t a = static_cast<int64_t>(*nfront), b = static_cast<int64_t>(*nafter);
+    for (int64_t i = blockIdx.x * static_cast<int64_t>(kKB) + threadIdx.x; i < a + b;
+         i += static_cast<int64_t>(gridDim.x) * kKB) {
+        if (i < a) state[front[i]] = kDead;
+        else state[after[i - a]] = kDying;
+    }
 }
 
 struct PeelLds {
@@ -104,6 +125,8 @@ struct PeelLds {
     int64_t iv0[kWave], iv1[kWave];  // v's in-edge slots
     int64_t ov0[kWave], ov1[kWave];  // v's out-edge positions
     int32_t own[kWave];     // list starts of the current batch
+    int32_t left[kWave];    // triangles of the frontier edge still to be met
+    int32_t from[kWave];    // first of u's neighbours in the walk
 };
 
 // First index in [lo, hi) of the sorted x whose value is at least w.
@@ -117,8 +140,17 @@ __device__ __forceinline__ I lower_at(gptr<int32_t> x, I lo, I hi, int32_t w) {
     return lo;
 }
 
-// One round's triangle updates: groups of 64 frontier edges, one per lane,
-// from a work counter.
+// One round's triangle updates: groups of up to 64 frontier edges, one per
+// lane.  A group is a chain of dependent loads (each batch of 64 neighbours
+// ends in binary searches), so small frontiers are cut into groups of few
+// edges, down to a part of one edge's neighbours.  Groups are dealt to the
+// waves in turn: taken from a counter, every wave's last (empty) take alone
+// made a round of any size last 100 us, one word serving some 80 M atomics a
+// second.  An edge's count says how many of its triangles are left to be met,
+// so an edge in none walks nothing and the others' neighbours after the last
+// triangle cost no load.  An edge that a vanished triangle brings below
+// `need` is appended to `after`, the next round's frontier, by the one
+// decrement that does.
 __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *__restrict__ front_,
                                                                 const unsigned long long *__restrict__ nfront_,
                                                                 const int64_t *__restrict__ row_off_,
@@ -128,8 +160,9 @@ __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *_
                                                                 const uint32_t *__restrict__ in_pos_,
                                                                 const int32_t *__restrict__ in_nb_,
                                                                 const uint8_t *__restrict__ state_,
-                                                                uint32_t *__restrict__ sup,
-                                                                unsigned long long *__restrict__ next) {
+                                                                uint32_t *__restrict__ sup, uint32_t need,
+                                                                uint32_t *__restrict__ after,
+                                                                unsigned long long *__restrict__ nafter) {
     __shared__ PeelLds s_lds[kPeelWaves];
     PeelLds &L = s_lds[threadIdx.x / kWave];
     const int lane = lane_id();
@@ -140,21 +173,34 @@ __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *_
     const gptr<uint32_t> ip = as_global(in_pos_);
     const gptr<uint8_t> state = as_global(state_);
     const int64_t cnt = static_cast<int64_t>(*as_global(nfront_));
+    if (cnt == 0) return;
     L.own[lane] = 0;
     wave_lds_sync();
-    for (;;) {
-        unsigned long long g0 = 0;
-        if (lane == 0) g0 = atomicAdd(next, 1ull);
-        g0 = shfl_t(g0, 0);
-        const int64_t first = static_cast<int64_t>(g0) * kWave;
+    // edges per group, and groups per edge: about kPeelGroups groups per wave
+    // of the launch
+    const int64_t want = static_cast<int64_t>(gridDim.x) * kPeelWaves * kPeelGroups;
+    const int64_t per = max(min(cnt / want, static_cast<int64_t>(kWave)), static_cast<int64_t>(1));
+    const int32_t parts = static_cast<int32_t>(max(min(want / cnt, static_cast<int64_t>(kWave)), static_cast<int64_t>(1)));
+    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+    const int64_t waves = static_cast<int64_t>(gridDim.x) * kPeelWaves;
+    for (int64_t g0 = blockIdx.x * static_cast<int64_t>(kPeelWaves) + threadIdx.x / kWave;; g0 += waves) {
+        const int64_t first = g0 / parts * per;
         if (first >= cnt) break;
+        const int32_t part = static_cast<int32_t>(g0 % parts);
         const int64_t idx = first + lane;
         int32_t len = 0;
-        if (idx < cnt) {
+        if (lane < per && idx < cnt) {
             const uint32_t e = front[idx];
             const int32_t u = lo_end[e], v = col[e];
             const int64_t iu0 = io[u], iu1 = io[u + 1], ou0 = ro[u], ou1 = ro[u + 1];
-            len = static_cast<int32_t>((iu1 - iu0) + (ou1 - ou0));
+            // the edge's count: its triangles with edges still present
+            const int32_t left = static_cast<int32_t>(sup[e]);
+            L.left[lane] = left;
+            const int32_t all = left ? static_cast<int32_t>((iu1 - iu0) + (ou1 - ou0)) : 0;
+            // this part's neighbours [from, from + len)
+            const int32_t share = (all + parts - 1) / parts, from = min(share * part, all);
+            len = min(share, all - from);
+            L.from[lane] = from;
             L.e[lane] = e;
             L.v[lane] = v;
             L.nin_u[lane] = static_cast<int32_t>(iu1 - iu0);
@@ -183,48 +229,69 @@ __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *_
             const uint32_t sl1 = max(wave_max_scan_dpp(o), carry);
             carry = __builtin_amdgcn_readlane(sl1, kWave - 1);
             const int32_t el = base + lane;
-            if (el >= total) continue;
-            const int sl = static_cast<int>(sl1) - 1;
-            const int32_t t = el - L.pre[sl];  // neighbour t of u
-            const uint32_t e = L.e[sl];
-            const int32_t v = L.v[sl];
-            int32_t w;
-            uint32_t f;  // edge (u, w)
-            if (t < L.nin_u[sl]) {
-                const int64_t k = L.iu0[sl] + t;
-                w = in_nb[k];
-                f = ip[k];
-            } else {
-                const int64_t q = L.ou0[sl] + (t - L.nin_u[sl]);
-                w = col[q];
-                f = static_cast<uint32_t>(q);
-            }
-            if (w == v) continue;
-            const uint8_t sf = state[f];
-            if (sf == kDead) continue;
-            uint32_t gq;  // edge (v, w), if any
-            uint8_t sg;
-            if (w < v) {
-                const int64_t k0 = L.iv0[sl], k1 = L.iv1[sl];
-                const int64_t k = lower_at<int64_t>(in_nb, k0, k1, w);
-                if (k >= k1 || in_nb[k] != w) continue;
-                gq = ip[k];
-            } else {
-                const int64_t q0 = L.ov0[sl], q1 = L.ov1[sl];
-                const int64_t q = lower_at<int64_t>(col, q0, q1, w);
-                if (q >= q1 || col[q] != w) continue;
-                gq = static_cast<uint32_t>(q);
-            }
-            sg = state[gq];
-            if (sg == kDead) continue;
-            // the triangle vanishes; only its frontier edge of smallest
-            // position updates the others
-            if ((sf == kDying && f < e) || (sg == kDying && gq < e)) continue;
-            if (sf == kLive) atomicSub(&sup[f], 1u);
-            if (sg == kLive) atomicSub(&sup[gq], 1u);
+            // the lane's neighbour w of u: one off the counts of (u, w) and (v,
+            // w) if all three edges are there; f, gq: those that fell below need
+            uint32_t drop_f = UINT32_MAX, drop_g = UINT32_MAX;
+            auto visit = [&]() {
+                const int sl = static_cast<int>(sl1) - 1;
+                if (L.left[sl] <= 0) return;  // all met
+                const int32_t t = L.from[sl] + (el - L.pre[sl]);  // neighbour t of u
+                const uint32_t e = L.e[sl];
+                const int32_t v = L.v[sl];
+                int32_t w;
+                uint32_t f;  // edge (u, w)
+                if (t < L.nin_u[sl]) {
+                    const int64_t k = L.iu0[sl] + t;
+                    w = in_nb[k];
+                    f = ip[k];
+                } else {
+                    const int64_t q = L.ou0[sl] + (t - L.nin_u[sl]);
+                    w = col[q];
+                    f = static_cast<uint32_t>(q);
+                }
+                if (w == v) return;
+                const uint8_t sf = state[f];
+                if (sf == kDead) return;
+                uint32_t gq;  // edge (v, w), if any
+                if (w < v) {
+                    const int64_t k0 = L.iv0[sl], k1 = L.iv1[sl];
+                    const int64_t k = lower_at<int64_t>(in_nb, k0, k1, w);
+                    if (k >= k1 || in_nb[k] != w) return;
+                    gq = ip[k];
+                } else {
+                    const int64_t q0 = L.ov0[sl], q1 = L.ov1[sl];
+                    const int64_t q = lower_at<int64_t>(col, q0, q1, w);
+                    if (q >= q1 || col[q] != w) return;
+                    gq = static_cast<uint32_t>(q);
+                }
+                const uint8_t sg = state[gq];
+                if (sg == kDead) return;
+                atomicSub(&L.left[sl], 1);
+                // the triangle vanishes; only its frontier edge of smallest
+                // position updates the others
+                if ((sf == kDying && f < e) || (sg == kDying && gq < e)) return;
+                if (sf == kLive && atomicSub(&sup[f], 1u) == need) drop_f = f;
+                if (sg == kLive && atomicSub(&sup[gq], 1u) == need) drop_g = gq;
+            };
+            if (el < total) visit();
+            const uint64_t mf = __ballot(drop_f != UINT32_MAX), mg = __ballot(drop_g != UINT32_MAX);
+            if ((mf | mg) == 0) continue;
+            const int nf = __popcll(mf);
+            unsigned long long at = 0;
+            if (lane == 0) at = atomicAdd(nafter, static_cast<unsigned long long>(nf + __popcll(mg)));
+            at = shfl_t(at, 0);
+            if (drop_f != UINT32_MAX) after[at + __popcll(mf & below)] = drop_f;
+            if (drop_g != UINT32_MAX) after[at + nf + __popcll(mg & below)] = drop_g;
         }
         wave_lds_sync();  // before the next group overwrites the lane records
     }
+}
+
+// Clears p[0, n) (n <= 64), p[0] to *first if given.
+__global__ void k_kt_zero(unsigned long long *p, const unsigned long long *first, int32_t n) {
+    const unsigned long long f = first ? *first : 0ull;
+    const int32_t i = threadIdx.x;
+    if (i < n) p[i] = i == 0 ? f : 0ull;
 }
 
 __global__ __launch_bounds__(kKB) void k_kt_keep(const uint8_t *__restrict__ state, int64_t m,
@@ -253,43 +320,51 @@ int64_t ktruss(pgabb_graph *g, int32_t k, uint8_t *keep, bool on_device, int32_t
         PGABB_HIP(hipGetLastError());
         if (need > 0) {  // k <= 2: every edge stays
             DArray<uint32_t> sup(static_cast<size_t>(m), s);
-            edge_support(g, sup.get(), true);
-            kernel_ms += g->t_kernel_ms;
-            DArray<int32_t> lo_end(static_cast<size_t>(m), s), in_nb(static_cast<size_t>(m), s);
             DArray<int64_t> in_off;
             DArray<uint32_t> in_pos;
-            in_edges(g, in_off, in_pos);
-            k_kt_rows<<<grid_for(n, kKB), kKB, 0, s>>>(g->row_off.get(), n, lo_end.get());
+            edge_support(g, sup.get(), true, &in_off, &in_pos);
+            kernel_ms += g->t_kernel_ms;
+            DArray<int32_t> lo_end(static_cast<size_t>(m), s), in_nb(static_cast<size_t>(m), s);
+            k_kt_rows<<<std::min(grid_for(n, kKB / 16), 16384u), kKB, 0, s>>>(g->row_off.get(), n, lo_end.get());
             k_kt_in_nb<<<grid_for(m, kKB), kKB, 0, s>>>(in_pos.get(), lo_end.get(), m, in_nb.get());
             PGABB_HIP(hipGetLastError());
-            DArray<uint32_t> front(static_cast<size_t>(m), s);
-            DArray<unsigned long long> ctr(2, s);  // frontier size, group counter
-            Staged<unsigned long long> h_front(1, s);
-            const unsigned front_grid = std::min<unsigned>(grid_for(m, kKB), 256u * 8u);
-            for (;;) {
-                PGABB_HIP(hipMemsetAsync(ctr.get(), 0, 2 * sizeof(unsigned long long), s));
-                k_kt_front<<<front_grid, kKB, 0, s>>>(sup.get(), m, need, state.get(), front.get(), ctr.get());
-                PGABB_HIP(hipGetLastError());
-                PGABB_HIP(hipMemcpyAsync(h_front.get(), ctr.get(), sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                                         s));
-                PGABB_HIP(hipStreamSynchronize(s));
-                const int64_t nf = static_cast<int64_t>(h_front[0]);
-                if (nf == 0) break;
-                ++rounds;
-                live -= nf;
-                const int64_t groups = (nf + kWave - 1) / kWave;
-                const unsigned grid = static_cast<unsigned>(
-                    std::max<int64_t>(1, std::min<int64_t>((groups + kPeelWaves - 1) / kPeelWaves, 256 * 8)));
-                StreamTimer tm;
+            DArray<uint32_t> front_a(static_cast<size_t>(m), s), front_b(static_cast<size_t>(m), s);
+            // kTrussRound rounds are queued per host round trip (a round after
+            // an empty frontier does nothing): frontier sizes of the rounds
+            // and of the one after
+            constexpr int kCtr = kTrussRound + 1;
+            DArray<unsigned long long> ctr(kCtr, s);
+            Staged<unsigned long long> h_front(kTrussRound + 1, s);
+            uint32_t *front = front_a.get(), *after = front_b.get();
+            k_kt_zero<<<1, kWave, 0, s>>>(ctr.get(), nullptr, kCtr);
+            k_kt_front<<<std::min(grid_for(m, kKB * kFrontPer), 256u * 8u), kKB, 0, s>>>(sup.get(), m, need, state.get(),
+                                                                                       front, ctr.get());
+            PGABB_HIP(hipGetLastError());
+            const unsigned grid = std::min(grid_for(m, kPeelWaves), 256u * 8u);
+            StreamTimer tm;
+            for (bool more = true; more;) {
                 tm.start(s);
-                k_kt_peel<<<grid, kPeelWaves * kWave, 0, s>>>(front.get(), ctr.get(), g->row_off.get(), g->col.get(),
-                                                               lo_end.get(), in_off.get(), in_pos.get(), in_nb.get(),
-                                                               state.get(), sup.get(), ctr.get() + 1);
+                for (int q = 0; q < kTrussRound; ++q) {
+                    k_kt_peel<<<grid, kPeelWaves * kWave, 0, s>>>(front, ctr.get() + q, g->row_off.get(), g->col.get(),
+                                                                   lo_end.get(), in_off.get(), in_pos.get(),
+                                                                   in_nb.get(), state.get(), sup.get(), need, after,
+                                                                   ctr.get() + q + 1);
+                    k_kt_turn<<<std::min(grid_for(m, kKB), 1024u), kKB, 0, s>>>(front, ctr.get() + q, after,
+                                                                             ctr.get() + q + 1, state.get());
+                    std::swap(front, after);
+                }
                 tm.stop(s);
-                k_kt_kill<<<std::min<unsigned>(grid_for(nf, kKB), 1024u), kKB, 0, s>>>(front.get(), ctr.get(),
-                                                                                    state.get());
                 PGABB_HIP(hipGetLastError());
+                PGABB_HIP(hipMemcpyAsync(h_front.get(), ctr.get(), h_front.bytes(), hipMemcpyDeviceToHost, s));
+                // the next rounds start from the last frontier
+                k_kt_zero<<<1, kWave, 0, s>>>(ctr.get(), ctr.get() + kTrussRound, kCtr);
+                PGABB_HIP(hipStreamSynchronize(s));
                 kernel_ms += tm.ms();
+                more = h_front[kTrussRound] != 0;
+                for (int q = 0; q < kTrussRound; ++q) {
+                    rounds += h_front[q] ? 1 : 0;
+                    live -= static_cast<int64_t>(h_front[q]);
+                }
             }
         }
         if (keep) {
