@@ -25,6 +25,12 @@ namespace {
 
 constexpr int B = 256;
 constexpr uint64_t kSentinel = ~0ull;
+// Up to this many pairs the high ends are counted with one atomic each (64 K
+// of them take less than the launches of a sort); above they are sorted.
+constexpr int64_t kHiAtomics = 65536;
+// Up to this many dedupe tiles each adds up the counts before its own (64 KB
+// from L2); above they are scanned first.
+constexpr int64_t kUniqDirect = 16384;
 
 __global__ void k_make_keys(const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
                             int64_t m, int32_t n, int nb, uint64_t *__restrict__ keys,
@@ -43,63 +49,131 @@ __global__ void k_make_keys(const int32_t *__restrict__ src, const int32_t *__re
     }
 }
 
-// flag[e] = 1 for the first key of each run of equal valid keys.
-__global__ void k_first_of_run(const uint64_t *__restrict__ keys, int64_t m, uint64_t valid_limit,
-                               uint32_t *__restrict__ flag) {
-    for (int64_t e = blockIdx.x * int64_t(B) + threadIdx.x; e < m; e += int64_t(gridDim.x) * B) {
-        const uint64_t k = keys[e];
-        flag[e] = (k < valid_limit && (e == 0 || keys[e - 1] != k)) ? 1u : 0u;
+// Dedupe: a tile of UT keys per workgroup.  The first launch counts the keys
+// that are the first of a run of equal valid keys; the second adds up the
+// counts of the tiles before its own, places its first keys, and makes the
+// degrees' parts on the way.  (Flags, a scan of them, a compaction and a pass
+// over the result for the low ends' run lengths moved twice the bytes: 270 ->
+// 125 us for the 16.8 M keys of R-MAT scale 20.)
+constexpr int kUniqPer = 8;
+constexpr int64_t UT = int64_t(B) * kUniqPer;
+
+__global__ __launch_bounds__(B) void k_uniq_count(const uint64_t *__restrict__ keys, int64_t m, uint64_t valid_limit,
+                                                  uint32_t *__restrict__ sums) {
+    __shared__ uint32_t wt[B / 64];
+    const int64_t base = blockIdx.x * UT;
+    uint32_t c = 0;
+#pragma unroll
+    for (int q = 0; q < kUniqPer; ++q) {
+        const int64_t e = base + q * B + threadIdx.x;
+        if (e < m) {
+            const uint64_t k = keys[e];
+            c += (k < valid_limit && (e == 0 || keys[e - 1] != k)) ? 1u : 0u;
+        }
+    }
+    c = wave_sum(c);
+    if (lane_id() == 0) wt[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int w = 0; w < B / 64; ++w) t += wt[w];
+        sums[blockIdx.x] = t;
     }
 }
 
-__global__ void k_compact(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ flag,
-                          const uint32_t *__restrict__ pos, int64_t m, uint64_t *__restrict__ out) {
-    for (int64_t e = blockIdx.x * int64_t(B) + threadIdx.x; e < m; e += int64_t(gridDim.x) * B)
-        if (flag[e]) out[pos[e]] = keys[e];
-}
-
-// Distinct keys are sorted by (lo, hi): the lo ends form runs, so each run
-// adds its length once.  The hi ends are copied out, sorted, and counted the
-// same way (scattered atomics on hub vertices would serialise).  The loop
-// bound is uniform across a wave so every lane takes part in the ballots.
-__global__ void k_degrees_lo(const uint64_t *__restrict__ keys, int64_t m, int nb,
-                             int32_t *__restrict__ deg, uint32_t *__restrict__ his) {
+// Distinct keys, in order, to out[0, m') (total: m').  They are sorted by (lo,
+// hi), so the low ends form runs: start[lo] and end[lo] are the run's bounds
+// (0, 0 without one).  The high ends go to his (to be sorted and counted: on
+// large inputs scattered atomics on hub vertices would serialise), or, with
+// his null, each adds one to deg_hi.
+template <bool SCANNED>
+__global__ __launch_bounds__(B) void k_uniq_write(const uint64_t *__restrict__ keys, int64_t m, uint64_t valid_limit,
+                                                  int nb, const uint32_t *__restrict__ sums,
+                                                  uint64_t *__restrict__ out, uint32_t *__restrict__ start,
+                                                  uint32_t *__restrict__ end, uint32_t *__restrict__ his,
+                                                  uint32_t *__restrict__ deg_hi, uint32_t *__restrict__ total) {
+    __shared__ uint32_t wt[B / 64];
+    const int w = threadIdx.x >> 6, lane = lane_id();
     const uint64_t mask = (1ull << nb) - 1;
+    uint32_t at = 0;  // distinct keys before this tile
+    if (SCANNED) {
+        at = sums[blockIdx.x];
+    } else {
+        for (uint32_t q = threadIdx.x; q < blockIdx.x; q += B) at += sums[q];
+        at = wave_sum(at);
+        if (lane == 0) wt[w] = at;
+        __syncthreads();
+        at = 0;
+        for (int q = 0; q < B / 64; ++q) at += wt[q];
+        __syncthreads();
+    }
+    const int64_t base = blockIdx.x * UT;
+    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+#pragma unroll
+    for (int q = 0; q < kUniqPer; ++q) {
+        const int64_t e = base + q * B + threadIdx.x;
+        uint64_t k = ~0ull, prev = ~0ull;
+        if (e < m) {
+            k = keys[e];
+            if (e > 0) prev = keys[e - 1];
+        }
+        const bool first = e < m && k < valid_limit && (e == 0 || prev != k);
+        const uint64_t firsts = __ballot(first);
+        if (lane == 0) wt[w] = static_cast<uint32_t>(__popcll(firsts));
+        __syncthreads();
+        uint32_t pos = at + static_cast<uint32_t>(__popcll(firsts & below));
+        for (int x = 0; x < B / 64; ++x) {
+            if (x < w) pos += wt[x];
+            at += wt[x];
+        }
+        __syncthreads();
+        // the run of the key before ends where a new low end (or the sentinels) begins
+        const bool prev_valid = e < m && e > 0 && prev < valid_limit;
+        if (prev_valid && (k >= valid_limit || (prev >> nb) != (k >> nb))) end[prev >> nb] = pos;
+        if (first) {
+            const uint32_t hi = static_cast<uint32_t>(k & mask);
+            out[pos] = k;
+            if (e == 0 || (prev >> nb) != (k >> nb)) start[k >> nb] = pos;
+            if (his) his[pos] = hi;
+            else atomicAdd(&deg_hi[hi], 1u);
+        }
+        if (e == m - 1) {
+            const uint32_t after = pos + (first ? 1u : 0u);
+            *total = after;
+            if (k < valid_limit) end[k >> nb] = after;
+        }
+    }
+}
+
+__global__ void k_degrees_hi(const uint32_t *__restrict__ his, int64_t m, int32_t *__restrict__ deg_hi) {
     const int64_t stride = int64_t(gridDim.x) * B;
     for (int64_t base = blockIdx.x * int64_t(B) + (threadIdx.x & ~63); base < m; base += stride) {
         const int64_t e = base + lane_id();
         const bool valid = e < m;
-        const uint64_t k = valid ? keys[e] : 0ull;
-        add_run_lengths(valid, static_cast<int64_t>(k >> nb), deg);
-        if (valid) his[e] = static_cast<uint32_t>(k & mask);
+        add_run_lengths(valid, valid ? static_cast<int64_t>(his[e]) : 0, deg_hi);
     }
 }
 
-__global__ void k_degrees_hi(const uint32_t *__restrict__ his, int64_t m, int32_t *__restrict__ deg) {
-    const int64_t stride = int64_t(gridDim.x) * B;
-    for (int64_t base = blockIdx.x * int64_t(B) + (threadIdx.x & ~63); base < m; base += stride) {
-        const int64_t e = base + lane_id();
-        const bool valid = e < m;
-        add_run_lengths(valid, valid ? static_cast<int64_t>(his[e]) : 0, deg);
-    }
-}
-
-__global__ void k_deg_keys(const int32_t *__restrict__ deg, int32_t n, uint32_t *__restrict__ dk,
-                           uint32_t *__restrict__ dv) {
+// The degrees (into deg), and with dk the sort's keys and values; without, the
+// ranks in id order.
+__global__ void k_deg_keys(const uint32_t *__restrict__ start, const uint32_t *__restrict__ end,
+                           const uint32_t *__restrict__ deg_hi, int32_t n, int32_t *__restrict__ deg,
+                           uint32_t *__restrict__ dk, uint32_t *__restrict__ dv, int32_t *__restrict__ rank) {
     for (int64_t v = blockIdx.x * int64_t(B) + threadIdx.x; v < n; v += int64_t(gridDim.x) * B) {
-        dk[v] = static_cast<uint32_t>(deg[v]);
-        dv[v] = static_cast<uint32_t>(v);
+        const uint32_t d = end[v] - start[v] + deg_hi[v];
+        deg[v] = static_cast<int32_t>(d);
+        if (dk) {
+            dk[v] = d;
+            dv[v] = static_cast<uint32_t>(v);
+        } else {
+            rank[v] = static_cast<int32_t>(v);
+        }
     }
 }
 
 __global__ void k_invert(const uint32_t *__restrict__ perm, int32_t n, int32_t *__restrict__ rank) {
     for (int64_t r = blockIdx.x * int64_t(B) + threadIdx.x; r < n; r += int64_t(gridDim.x) * B)
         rank[perm[r]] = static_cast<int32_t>(r);
-}
-
-__global__ void k_identity(int32_t n, int32_t *__restrict__ rank) {
-    for (int64_t r = blockIdx.x * int64_t(B) + threadIdx.x; r < n; r += int64_t(gridDim.x) * B)
-        rank[r] = static_cast<int32_t>(r);
 }
 
 __global__ void k_orient(const uint64_t *__restrict__ ukeys, int64_t m, int nb,
@@ -127,58 +201,65 @@ __global__ void k_row_counts_and_cols(const uint64_t *__restrict__ okeys, int64_
     }
 }
 
-__global__ void k_widen(const int32_t *__restrict__ in, int32_t n, int64_t *__restrict__ out) {
-    for (int64_t v = blockIdx.x * int64_t(B) + threadIdx.x; v < n; v += int64_t(gridDim.x) * B)
-        out[v] = in[v];
-}
-
 struct Stats {
     int32_t max_out;
-    int32_t pad;
-    unsigned long long isolated;
-    unsigned long long probe_work;
+    int32_t max_in;
+    unsigned long long sum[kStatSums];  // by Stat
 };
 
 // Per vertex v (rank r): indeg[r] = deg[v] - outdeg[r], the edges of v
 // whose other end ranks lower; and the statistics, reduced per workgroup
-// (one atomic each; launched with a small grid): the longest oriented row,
-// the isolated vertices and the probe work W = sum over oriented edges
-// (x, y) of outdeg[y] = sum over y of indeg[y] outdeg[y].
+// (one atomic each; launched with a small grid): the longest row and column,
+// the isolated vertices, the probe work W = sum over oriented edges (x, y) of
+// outdeg[y] = sum over y of indeg[y] outdeg[y], and what a partition into one
+// block needs to know of it.
 __global__ __launch_bounds__(B) void k_vertex_stats(const int32_t *__restrict__ deg,
                                                     const int32_t *__restrict__ rank,
                                                     const int32_t *__restrict__ outdeg, int32_t n,
                                                     int32_t *__restrict__ indeg, Stats *st) {
-    __shared__ int32_t s_mx[B / 64];
-    __shared__ unsigned long long s_iso[B / 64], s_w[B / 64];
-    int32_t mx = 0;
-    unsigned long long iso = 0, w = 0;
+    __shared__ int32_t s_mx[B / 64][2];
+    __shared__ unsigned long long s_sum[B / 64][kStatSums];
+    int32_t mo = 0, mi = 0;
+    unsigned long long sum[kStatSums] = {};
     for (int64_t v = blockIdx.x * int64_t(B) + threadIdx.x; v < n; v += int64_t(gridDim.x) * B) {
         const int32_t r = rank[v];
         const int32_t o = outdeg[r], i = deg[v] - o;
         indeg[r] = i;
-        mx = max(mx, o);
-        iso += deg[v] == 0;
-        w += static_cast<unsigned long long>(i) * static_cast<unsigned long long>(o);
+        mo = max(mo, o);
+        mi = max(mi, i);
+        sum[kStatIsolated] += deg[v] == 0;
+        sum[kStatProbeWork] += static_cast<unsigned long long>(i) * static_cast<unsigned long long>(o);
+        sum[kStatRowSquares] += static_cast<unsigned long long>(o) * static_cast<unsigned long long>(o);
+        sum[kStatRows] += o > 0;
+        sum[kStatCols] += i > 0;
+        sum[kStatRowItems] += (o + kSplitV - 1) / kSplitV;
+        sum[kStatColItems] += (i + kSplitV - 1) / kSplitV;
     }
 #pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) mx = max(mx, __shfl_xor(mx, d));
-    iso = wave_sum(iso);
-    w = wave_sum(w);
+    for (int d = 1; d < kWave; d <<= 1) {
+        mo = max(mo, __shfl_xor(mo, d));
+        mi = max(mi, __shfl_xor(mi, d));
+    }
+#pragma unroll
+    for (int q = 0; q < kStatSums; ++q) sum[q] = wave_sum(sum[q]);
     if (lane_id() == 0) {
-        s_mx[threadIdx.x >> 6] = mx;
-        s_iso[threadIdx.x >> 6] = iso;
-        s_w[threadIdx.x >> 6] = w;
+        s_mx[threadIdx.x >> 6][0] = mo;
+        s_mx[threadIdx.x >> 6][1] = mi;
+        for (int q = 0; q < kStatSums; ++q) s_sum[threadIdx.x >> 6][q] = sum[q];
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int q = 1; q < B / 64; ++q) {
-            mx = max(mx, s_mx[q]);
-            iso += s_iso[q];
-            w += s_w[q];
+            mo = max(mo, s_mx[q][0]);
+            mi = max(mi, s_mx[q][1]);
         }
-        atomicMax(&st->max_out, mx);
-        atomicAdd(&st->isolated, iso);
-        atomicAdd(&st->probe_work, w);
+        atomicMax(&st->max_out, mo);
+        atomicMax(&st->max_in, mi);
+    }
+    if (threadIdx.x < kStatSums) {
+        unsigned long long t = 0;
+        for (int q = 0; q < B / 64; ++q) t += s_sum[q][threadIdx.x];
+        if (t) atomicAdd(&st->sum[threadIdx.x], t);
     }
 }
 
@@ -201,20 +282,25 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
     g->indeg.reset(static_cast<size_t>(n), s);
     g->row_off.reset(static_cast<size_t>(n) + 1, s);
     if (n > 0) PGABB_HIP(hipMemsetAsync(g->outdeg.get(), 0, sizeof(int32_t) * n, s));
-    PGABB_HIP(hipMemsetAsync(g->row_off.get(), 0, sizeof(int64_t) * (static_cast<size_t>(n) + 1), s));
+    else PGABB_HIP(hipMemsetAsync(g->row_off.get(), 0, sizeof(int64_t), s));  // (else written by the scan)
 
     DArray<int32_t> deg(static_cast<size_t>(n), s);
-    if (n > 0) PGABB_HIP(hipMemsetAsync(deg.get(), 0, sizeof(int32_t) * n, s));
     g->m = 0;
+    // what starts at zero, cleared at once: the statistics, two words (an
+    // endpoint lay out of range; distinct edges), the low ends' run bounds and
+    // the high ends' counts
+    constexpr size_t kHead = (sizeof(Stats) + sizeof(uint32_t) - 1) / sizeof(uint32_t);
+    const size_t nz = kHead + 2 + 3 * static_cast<size_t>(n);
+    DArray<uint32_t> zeroed(nz, s);
+    PGABB_HIP(hipMemsetAsync(zeroed.get(), 0, nz * sizeof(uint32_t), s));
+    Stats *st = reinterpret_cast<Stats *>(zeroed.get());
+    uint32_t *meta = zeroed.get() + kHead, *run_start = meta + 2, *run_end = run_start + n, *deg_hi = run_end + n;
 
     if (m > 0) {
         DArray<uint64_t> keys(static_cast<size_t>(m), s), alt(static_cast<size_t>(m), s);
-        // meta[0]: an endpoint lay out of range; meta[1]: distinct edges.
         // Out-of-range edges get the sentinel key, so sorting and compacting
-        // them is harmless and one round trip reports both.
-        DArray<uint32_t> meta(2, s);
-        PGABB_HIP(hipMemsetAsync(meta.get(), 0, 2 * sizeof(uint32_t), s));
-        k_make_keys<<<cap_grid(m), B, 0, s>>>(src, dst, m, n, nb, keys.get(), meta.get());
+        // them is harmless and one round trip reports both words.
+        k_make_keys<<<cap_grid(m), B, 0, s>>>(src, dst, m, n, nb, keys.get(), meta);
         PGABB_HIP(hipGetLastError());
 
         // 1-2: sort and dedupe.  Valid keys are below (n-1) << nb | (n-1) + 1;
@@ -223,15 +309,26 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
         uint64_t *k0 = keys.get(), *k1 = alt.get();
         if (radix_sort_u64_bits(k0, k1, nullptr, nullptr, m, 0, kbits, s)) std::swap(k0, k1);
         const uint64_t valid_limit = (static_cast<uint64_t>(n - 1) << nb) + static_cast<uint64_t>(n);
+        DArray<uint32_t> his;
+        if (m > kHiAtomics) his.reset(static_cast<size_t>(m), s);
         {
-            DArray<uint32_t> flag(static_cast<size_t>(m), s), pos(static_cast<size_t>(m), s);
-            k_first_of_run<<<cap_grid(m), B, 0, s>>>(k0, m, valid_limit, flag.get());
+            const int64_t tiles = (m + UT - 1) / UT;
+            DArray<uint32_t> sums(static_cast<size_t>(tiles), s);
+            k_uniq_count<<<static_cast<unsigned>(tiles), B, 0, s>>>(k0, m, valid_limit, sums.get());
             PGABB_HIP(hipGetLastError());
-            scan_exclusive_u32(flag.get(), pos.get(), m, meta.get() + 1, s);
-            k_compact<<<cap_grid(m), B, 0, s>>>(k0, flag.get(), pos.get(), m, k1);
+            if (tiles > kUniqDirect) {
+                scan_exclusive_u32(sums.get(), sums.get(), tiles, nullptr, s);
+                k_uniq_write<true><<<static_cast<unsigned>(tiles), B, 0, s>>>(k0, m, valid_limit, nb, sums.get(), k1,
+                                                                             run_start, run_end, his.get(), deg_hi,
+                                                                             meta + 1);
+            } else {
+                k_uniq_write<false><<<static_cast<unsigned>(tiles), B, 0, s>>>(k0, m, valid_limit, nb, sums.get(), k1,
+                                                                              run_start, run_end, his.get(), deg_hi,
+                                                                              meta + 1);
+            }
             PGABB_HIP(hipGetLastError());
             Staged<uint32_t> mh(2, s);
-            PGABB_HIP(hipMemcpyAsync(mh.get(), meta.get(), mh.bytes(), hipMemcpyDeviceToHost, s));
+            PGABB_HIP(hipMemcpyAsync(mh.get(), meta, mh.bytes(), hipMemcpyDeviceToHost, s));
             PGABB_HIP(hipStreamSynchronize(s));
             PGABB_REQUIRE(!mh[0], PGABB_EINVAL, "an edge endpoint lies outside [0, %d)", n);
             g->m = mh[1];
@@ -239,22 +336,22 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
         std::swap(k0, k1);  // k0: distinct keys [0, m')
         const int64_t mu = g->m;
 
-        // 3: degrees
-        if (mu > 0) {
-            DArray<uint32_t> his(static_cast<size_t>(mu), s), his_alt(static_cast<size_t>(mu), s);
-            k_degrees_lo<<<cap_grid(mu), B, 0, s>>>(k0, mu, nb, deg.get(), his.get());
-            PGABB_HIP(hipGetLastError());
+        // 3: the high ends' counts, where not added one by one
+        if (mu > 0 && his.get()) {
+            DArray<uint32_t> his_alt(static_cast<size_t>(mu), s);
             uint32_t *hs = his.get();
             if (radix_sort_u32(his.get(), his_alt.get(), nullptr, nullptr, mu, nb, s)) hs = his_alt.get();
-            k_degrees_hi<<<cap_grid(mu), B, 0, s>>>(hs, mu, deg.get());
+            k_degrees_hi<<<cap_grid(mu), B, 0, s>>>(hs, mu, reinterpret_cast<int32_t *>(deg_hi));
             PGABB_HIP(hipGetLastError());
         }
-        // 4: ranks
+        // 4: degrees and ranks
         if (g->flags & PGABB_ORDER_BY_ID) {
-            k_identity<<<cap_grid(n), B, 0, s>>>(n, g->rank.get());
+            k_deg_keys<<<cap_grid(n), B, 0, s>>>(run_start, run_end, deg_hi, n, deg.get(), nullptr, nullptr,
+                                                 g->rank.get());
         } else {
             DArray<uint32_t> dk(n, s), dka(n, s), dv(n, s), dva(n, s);
-            k_deg_keys<<<cap_grid(n), B, 0, s>>>(deg.get(), n, dk.get(), dv.get());
+            k_deg_keys<<<cap_grid(n), B, 0, s>>>(run_start, run_end, deg_hi, n, deg.get(), dk.get(), dv.get(),
+                                                 nullptr);
             PGABB_HIP(hipGetLastError());
             uint32_t *perm = dv.get();
             if (radix_sort_u32(dk.get(), dka.get(), dv.get(), dva.get(), n, nb, s)) perm = dva.get();
@@ -273,33 +370,28 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
             k_row_counts_and_cols<<<cap_grid(mu), B, 0, s>>>(k1, mu, nb, g->outdeg.get(), g->col.get());
             PGABB_HIP(hipGetLastError());
         }
-    } else {
-        k_identity<<<cap_grid(n), B, 0, s>>>(n, g->rank.get());
+    } else if (n > 0) {
+        k_deg_keys<<<cap_grid(n), B, 0, s>>>(run_start, run_end, deg_hi, n, deg.get(), nullptr, nullptr,
+                                             g->rank.get());  // every degree 0, ranks in id order
         PGABB_HIP(hipGetLastError());
     }
     if (g->m == 0) g->col.release();
 
-    if (n > 0) {
-        DArray<int64_t> wide(static_cast<size_t>(n), s);
-        k_widen<<<cap_grid(n), B, 0, s>>>(g->outdeg.get(), n, wide.get());
-        PGABB_HIP(hipGetLastError());
-        scan_exclusive_i64(wide.get(), g->row_off.get(), n, g->row_off.get() + n, s);
-    }
-
     // statistics for sizing kernels and stating algorithmic bytes
-    DArray<Stats> st(1, s);
-    PGABB_HIP(hipMemsetAsync(st.get(), 0, sizeof(Stats), s));
     if (n > 0) {
+        scan_exclusive_i32(g->outdeg.get(), g->row_off.get(), n, g->row_off.get() + n, s);
         k_vertex_stats<<<std::min(cap_grid(n), 1024u), B, 0, s>>>(deg.get(), g->rank.get(), g->outdeg.get(), n,
-                                                                  g->indeg.get(), st.get());
+                                                                  g->indeg.get(), st);
+        PGABB_HIP(hipGetLastError());
     }
-    PGABB_HIP(hipGetLastError());
     Staged<Stats> hs(1, s);
-    PGABB_HIP(hipMemcpyAsync(hs.get(), st.get(), sizeof(Stats), hipMemcpyDeviceToHost, s));
+    PGABB_HIP(hipMemcpyAsync(hs.get(), st, sizeof(Stats), hipMemcpyDeviceToHost, s));
     PGABB_HIP(hipStreamSynchronize(s));
     g->max_out = hs[0].max_out;
-    g->isolated = static_cast<int64_t>(hs[0].isolated);
-    g->probe_work = hs[0].probe_work;
+    g->max_in = hs[0].max_in;
+    for (int q = 0; q < kStatSums; ++q) g->stat[q] = hs[0].sum[q];
+    g->isolated = static_cast<int64_t>(g->stat[kStatIsolated]);
+    g->probe_work = g->stat[kStatProbeWork];
 }
 
 }  // namespace pgabb

@@ -190,6 +190,8 @@ void scan_exclusive_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *
                         hipStream_t s);
 void scan_exclusive_i64(const int64_t *in, int64_t *out, int64_t n, int64_t *total_dev,
                         hipStream_t s);
+// The same from 32-bit values to 64-bit sums.
+void scan_exclusive_i32(const int32_t *in, int64_t *out, int64_t n, int64_t *total_dev, hipStream_t s);
 
 // Stable LSD radix sort on bits [0, nbits) of the keys.  `keys`/`vals` hold
 // the input; `keys_alt`/`vals_alt` are scratch of the same size.  Returns

@@ -65,6 +65,18 @@ struct BlockInfo {
     int64_t walk_hi(int orient) const { return orient == kOrientCol ? end() : off_citems(); }
 };
 
+// Sums over the vertices that the build keeps (o: out-edges, i: in-edges).
+enum Stat : int {
+    kStatIsolated = 0,    // vertices without edges
+    kStatProbeWork = 1,   // i o: the entries row walks read
+    kStatRowSquares = 2,  // o o: the entries column walks of one block read
+    kStatRows = 3,        // o > 0
+    kStatCols = 4,        // i > 0
+    kStatRowItems = 5,    // work items of the rows, of the columns (one block)
+    kStatColItems = 6,
+    kStatSums = 7
+};
+
 // Device view of one block.
 struct BlockRef {
     const int32_t *rptr;
@@ -102,7 +114,9 @@ struct pgabb_graph {
     int64_t m = 0;  // m'
     int nb = 1;     // bits per vertex id in packed keys
     int64_t isolated = 0;
-    int32_t max_out = 0;
+    int32_t max_out = 0;          // longest oriented row
+    int32_t max_in = 0;           // and column
+    uint64_t stat[pgabb::kStatSums] = {};  // by pgabb::Stat
     uint64_t probe_work = 0;      // sum over oriented edges (x, y) of |N+(y)|
     uint64_t probe_work_col = 0;  // entries column walks read under the current cuts
     int64_t walked_columns = 0;   // the last count walked columns
