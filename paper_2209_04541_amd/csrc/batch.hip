@@ -239,6 +239,9 @@ __global__ void k_graph_row_pre_b(const uint32_t *__restrict__ pos, const int64_
 // with one counter for all, every XCD held rows of every graph in flight.
 constexpr int kBatchQueues = 8;
 constexpr int kBatchQueueStride = 32;  // counters 256 bytes apart
+// Ranges a wave tries before it is done (a launch of fewer workgroups than
+// ranges: all of them).
+constexpr int kBatchTries = 3;
 constexpr int kBatchQueueWords = kBatchQueues * kBatchQueueStride;
 
 struct BatchArgs {
@@ -268,17 +271,40 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_batch(BatchArgs a) {
         wave_lds_sync();
     }
     const int64_t per = (a.last - a.first + a.nq - 1) / a.nq;
-    const int home = static_cast<int>(blockIdx.x % a.nq);
-    for (int qi = 0; qi < a.nq; ++qi) {
-      const int q = (home + qi) % a.nq;
-      const int64_t q0 = a.first + q * per;
-      const int64_t q1 = min(q0 + per, a.last);
-      for (;;) {
-        unsigned long long g0 = 0;
-        if (lane == 0) g0 = atomicAdd(&a.next[q * kBatchQueueStride], static_cast<unsigned long long>(a.grab));
-        g0 = shfl_t(g0, 0);
-        const int64_t i0 = q0 + static_cast<int64_t>(g0);
-        if (i0 >= q1) break;
+    int q = static_cast<int>(blockIdx.x % a.nq);
+    // a wave's first rows of its own range are given by its number among the
+    // range's waves; takes from a counter go on after those (see UnitTaker)
+    int64_t mine = static_cast<int64_t>(blockIdx.x / a.nq) * WAVES + (threadIdx.x >> 6);
+    int tries = static_cast<int>(gridDim.x) >= a.nq ? kBatchTries : a.nq;
+    int32_t gcur = -1;  // the graph being counted, and the lane's hits for it
+    unsigned long long acc = 0;
+    uint32_t cnt = 0;
+    auto flush = [&]() {
+        if (gcur < 0) return;
+        const unsigned long long s = wave_sum(acc + cnt);
+        if (lane == 0 && s) atomicAdd(&a.counts[gcur], s);
+        acc = 0;
+        cnt = 0;
+    };
+    while (tries > 0) {
+        const int64_t q0 = a.first + q * per;
+        const int64_t q1 = min(q0 + per, a.last);
+        int64_t i0;
+        if (mine >= 0) {
+            i0 = q0 + mine * a.grab;
+            mine = -1;
+        } else {
+            const int64_t homes = q < static_cast<int>(gridDim.x) ? (gridDim.x - q + a.nq - 1) / a.nq : 0;
+            unsigned long long g0 = 0;
+            if (lane == 0) g0 = atomicAdd(&a.next[q * kBatchQueueStride], static_cast<unsigned long long>(a.grab));
+            g0 = shfl_t(g0, 0);
+            i0 = q0 + homes * WAVES * a.grab + static_cast<int64_t>(g0);
+        }
+        if (i0 >= q1) {
+            --tries;
+            q = (q + 1) % a.nq;
+            continue;
+        }
         const int64_t i1 = min(i0 + a.grab, q1);
         const int32_t nrow = static_cast<int32_t>(i1 - i0);  // at most 64
         // the grab's row headers, lane l holding row i0 + l: graph, row,
@@ -295,8 +321,6 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_batch(BatchArgs a) {
             h_vb = static_cast<int32_t>(vb);
             h_nv = static_cast<int32_t>(a.vbase[h_gid + 1] - vb);
         }
-        int32_t gcur = __builtin_amdgcn_readfirstlane(h_gid);
-        uint32_t cnt = 0;
         // rows of at most kTinyCap entries: walked together, graph by graph
         const bool lv = lane < nrow;
         uint64_t tiny = __ballot(lv && h_se > h_sb && h_se - h_sb <= kTinyCap);
@@ -306,9 +330,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_batch(BatchArgs a) {
             const uint64_t mg = tiny & __ballot(h_gid == gid);
             tiny &= ~mg;
             if (gid != gcur) {
-                const unsigned long long s = wave_sum(static_cast<unsigned long long>(cnt));
-                if (lane == 0 && s) atomicAdd(&a.counts[gcur], s);
-                cnt = 0;
+                flush();
                 gcur = gid;
             }
             cnt += tiny_items<1>(mg, h_sb, h_se, h_sb, h_se, a.col, a.col, a.rptr, a.col, own, lane);
@@ -318,9 +340,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_batch(BatchArgs a) {
             rest &= rest - 1;
             const int32_t gid = __builtin_amdgcn_readlane(h_gid, l);
             if (gid != gcur) {
-                const unsigned long long s = wave_sum(static_cast<unsigned long long>(cnt));
-                if (lane == 0 && s) atomicAdd(&a.counts[gcur], s);
-                cnt = 0;
+                flush();
                 gcur = gid;
             }
             const int32_t sb = __builtin_amdgcn_readlane(h_sb, l), se = __builtin_amdgcn_readlane(h_se, l);
@@ -328,10 +348,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_tc_batch(BatchArgs a) {
                                                  __builtin_amdgcn_readlane(h_nv, l), lds,
                                                  __builtin_amdgcn_readlane(h_vb, l));
         }
-        const unsigned long long s = wave_sum(static_cast<unsigned long long>(cnt));
-        if (lane == 0 && s) atomicAdd(&a.counts[gcur], s);
-      }
+        acc += cnt;
+        cnt = 0;
     }
+    flush();
 }
 
 __global__ void k_zero_u64(unsigned long long *p, int64_t n) {

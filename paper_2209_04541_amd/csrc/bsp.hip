@@ -220,29 +220,22 @@ __global__ __launch_bounds__(kBB) void k_sv_hook_edges(const int64_t *__restrict
     wave_lds_sync();
     const gptr<int64_t> ro = as_global(row_off);
     const int64_t groups = (static_cast<int64_t>(n) + kHookRows - 1) / kHookRows;
-    const int home = static_cast<int>(blockIdx.x % kBspQueues);
-    for (int qi = 0; qi < kBspQueues; ++qi) {
-        const int q = (home + qi) % kBspQueues;
-        for (;;) {
-            unsigned long long c = 0;
-            if (lane == 0) c = atomicAdd(&next[q * kBspStride], 1ull);
-            c = shfl_t(c, 0);
-            const int64_t g = static_cast<int64_t>(c) * kBspQueues + q;
-            if (g >= groups) break;
-            const int64_t x = lane < kHookRows ? n - 1 - g * kHookRows - lane : -1;
-            const int64_t e0 = x >= 0 ? ro[x] : 0, e1 = x >= 0 ? ro[x + 1] : 0;
-            const int32_t cu = x >= 0 ? __atomic_load_n(&C[x], __ATOMIC_RELAXED) : 0;
-            walk_lists(col + e0, static_cast<int32_t>(e1 - e0), 0, own, lane,
-                       [&](int32_t m, int src, const int32_t (&y)[kSeg]) {
-                           const int32_t c0 = __shfl(cu, src);
-                           int32_t cv[kSeg];
+    UnitTaker<kBspQueues, kBspStride> taker(next, groups, static_cast<int64_t>(gridDim.x) * (kBB / kWave),
+                                            static_cast<int64_t>(blockIdx.x) * (kBB / kWave) + threadIdx.x / kWave);
+    for (int64_t g; (g = taker.take(lane)) >= 0;) {
+        const int64_t x = lane < kHookRows ? n - 1 - g * kHookRows - lane : -1;
+        const int64_t e0 = x >= 0 ? ro[x] : 0, e1 = x >= 0 ? ro[x + 1] : 0;
+        const int32_t cu = x >= 0 ? __atomic_load_n(&C[x], __ATOMIC_RELAXED) : 0;
+        walk_lists(col + e0, static_cast<int32_t>(e1 - e0), 0, own, lane,
+                   [&](int32_t m, int src, const int32_t (&y)[kSeg]) {
+                       const int32_t c0 = __shfl(cu, src);
+                       int32_t cv[kSeg];
 #pragma unroll
-                           for (int k = 0; k < kSeg; ++k)
-                               cv[k] = k < m ? __atomic_load_n(&C[y[k]], __ATOMIC_RELAXED) : c0;
+                       for (int k = 0; k < kSeg; ++k)
+                           cv[k] = k < m ? __atomic_load_n(&C[y[k]], __ATOMIC_RELAXED) : c0;
 #pragma unroll
-                           for (int k = 0; k < kSeg; ++k) sv_hook(C, c0, cv[k]);
-                       });
-        }
+                       for (int k = 0; k < kSeg; ++k) sv_hook(C, c0, cv[k]);
+                   });
     }
 }
 

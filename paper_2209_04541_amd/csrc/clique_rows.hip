@@ -432,37 +432,31 @@ __global__ __launch_bounds__(kRowThreads) void k_quad_rows(RowArgs a) {
     uint64_t *M = s_m + wv * kWaveWords;
     int32_t *mem = s_mem + wv * kWaveRow;
     const int64_t nchunks = (nsmall + kRowGrab - 1) / kRowGrab;
-    const int home = static_cast<int>(blockIdx.x % kRowQueues);
-    for (int qi = 0; qi < kRowQueues; ++qi) {
-        const int qq = (home + qi) % kRowQueues;
-        for (;;) {
-            unsigned long long c0 = 0;
-            if (lane == 0) c0 = atomicAdd(&a.next[(1 + qq) * kRowQueueStride], 1ull);
-            c0 = shfl_t(c0, 0);
-            const int64_t c = static_cast<int64_t>(c0) * kRowQueues + qq;
-            if (c >= nchunks) break;
-            const int64_t t1 = min((c + 1) * kRowGrab, nsmall);
-            for (int64_t t = c * kRowGrab; t < t1; ++t) {
-                const int32_t v = __builtin_amdgcn_readfirstlane(a.small[t]);
-                const int64_t e0 = ro[v];
-                const int32_t d = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(ro[v + 1] - e0));
-                const int32_t NB = (d + kWave - 1) / kWave;
-                for (int32_t y = lane; y < d; y += kWave) mem[y] = col[e0 + y];
-                wave_lds_sync();
-                if (d <= kWave) induced_bits_short(a, mem, d, M, lane);
-                else induced_bits<1>(a, mem, d, NB, M, 0, lane);
-                int32_t ns = 1, i = 0;
-                if (BLOCKS) {
-                    ns = member_stripes(a, s_cuts, mem, d, s_seg[wv], s_sst[wv], lane);
-                    i = stripe_of(v);
-                }
-                wave_lds_sync();
-                unsigned long long part = 0;
-                induced_triangles<1, BLOCKS>(M, d, NB, ns, s_seg[wv], s_sst[wv], 0, lane, part, adder(i));
-                if (!BLOCKS) acc += part;
-                else if (ns == 1) flush_one(i, s_sst[wv][0], part);
-                wave_lds_sync();  // before the next vertex overwrites the matrix
+    UnitTaker<kRowQueues, kRowQueueStride> taker(a.next + kRowQueueStride, nchunks,
+                                                 static_cast<int64_t>(gridDim.x) * kRowWaves,
+                                                 static_cast<int64_t>(blockIdx.x) * kRowWaves + wv);
+    for (int64_t c; (c = taker.take(lane)) >= 0;) {
+        const int64_t t1 = min((c + 1) * kRowGrab, nsmall);
+        for (int64_t t = c * kRowGrab; t < t1; ++t) {
+            const int32_t v = __builtin_amdgcn_readfirstlane(a.small[t]);
+            const int64_t e0 = ro[v];
+            const int32_t d = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(ro[v + 1] - e0));
+            const int32_t NB = (d + kWave - 1) / kWave;
+            for (int32_t y = lane; y < d; y += kWave) mem[y] = col[e0 + y];
+            wave_lds_sync();
+            if (d <= kWave) induced_bits_short(a, mem, d, M, lane);
+            else induced_bits<1>(a, mem, d, NB, M, 0, lane);
+            int32_t ns = 1, i = 0;
+            if (BLOCKS) {
+                ns = member_stripes(a, s_cuts, mem, d, s_seg[wv], s_sst[wv], lane);
+                i = stripe_of(v);
             }
+            wave_lds_sync();
+            unsigned long long part = 0;
+            induced_triangles<1, BLOCKS>(M, d, NB, ns, s_seg[wv], s_sst[wv], 0, lane, part, adder(i));
+            if (!BLOCKS) acc += part;
+            else if (ns == 1) flush_one(i, s_sst[wv][0], part);
+            wave_lds_sync();  // before the next vertex overwrites the matrix
         }
     }
     if (!BLOCKS) {

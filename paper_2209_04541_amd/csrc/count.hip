@@ -142,6 +142,7 @@ void launch_tc_tasks(const CountArgs &args, const LaunchKind &lk, int waves, hip
     // the parts of a split launch run at the default shape (waves and unroll
     // options apply to single launches)
     unsigned long long *const next0 = a.next;
+    a.grab = std::min(a.grab * lk.nparts, kWave);  // a part counts a share of the items it takes
     for (int q = 0; q < lk.nparts; ++q) {
         a.next = next0 + static_cast<size_t>(q) * kQueueWords;  // counters of their own, cleared before
         a.stage_lo = q == 0 ? 0 : lk.hi[q - 1];
@@ -151,23 +152,25 @@ void launch_tc_tasks(const CountArgs &args, const LaunchKind &lk, int waves, hip
 }
 
 int default_grab(int64_t total_items, uint64_t walked) {
-    // A grab should carry about 16K walked entries: light items are taken
+    // A grab should carry about 12K walked entries: light items are taken
     // many at a time, so a grab's two header round trips are shared by more
     // of them; heavy ones a few at a time, so the last grabs do not leave
-    // waves idle.  (Measured on R-MAT and random geometric graphs at p = 1,
-    // 8 and 32, the best grab was 16K walked entries over the mean per item,
-    // within a few per cent.)  At most items / 32768, so a small launch
-    // still hands about four grabs to each of the chip's 8192 wave slots; at
-    // least enough for ~32K counter updates per queue: device-scope atomics
-    // on one address serialise.
+    // waves idle.  At most items / 57344, which hands each of the chip's 7168
+    // wave slots about eight grabs; at least enough for ~32K counter updates
+    // per queue.  Kernel us at grabs of 2 / 4 / 8 / 16 / 24 items (chosen):
+    // R-MAT scale 14 in one block (10 K items) 33 / 39 / 62 / 100 / 136 (2);
+    // scale 16 in 4 x 4 (0.1 M) 111 / 96 / 123 / 189 / 251 (2); scale 18 in
+    // 8 x 8 (0.75 M) 669 / 472 / 378 / 437 / 508 (13); scale 20 in 8 x 8 (2.7
+    // M) 2648 / 1956 / 1650 / 1588 / 1614 (16), in one block (0.65 M) 2493 /
+    // 2477 / 3362 / 3646 / 4370 (3).
     // walked == 0 (work unknown): the count bound alone
     if (total_items <= 0) return 2;
     const int64_t by_atomics = (total_items + int64_t(kQueues) * 32768 - 1) / (int64_t(kQueues) * 32768);
     int64_t g = by_atomics;
     if (walked > 0) {
         const double per_item = static_cast<double>(walked) / static_cast<double>(total_items);
-        const int64_t by_work = static_cast<int64_t>(16384.0 / per_item + 0.5);
-        const int64_t by_spread = total_items / 32768;
+        const int64_t by_work = static_cast<int64_t>(12288.0 / per_item + 0.5);
+        const int64_t by_spread = (total_items + 28672) / 57344;
         g = std::max<int64_t>(std::min<int64_t>(by_work, by_spread), by_atomics);
     }
     return static_cast<int>(std::max<int64_t>(2, std::min<int64_t>(g, 64)));

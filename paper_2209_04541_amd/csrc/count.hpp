@@ -5,17 +5,22 @@
 
 namespace pgabb {
 
-// Work queues of a counting launch: grab units are dealt round-robin to
-// kQueues counters; a workgroup starts on queue blockIdx % kQueues (its XCD
-// under round-robin dispatch) and moves on to the others once it is empty.
+// Work queues of a counting launch: a wave's first grab unit is its own number,
+// the others are dealt round-robin to kQueues counters; a workgroup starts on
+// queue blockIdx % kQueues (two per XCD under round-robin dispatch) and moves
+// on to the next once it is empty (see UnitTaker).
 // (Measured on R-MAT scale 20 at p = 8 and scale 24 at p = 32: one
 // contiguous range of units per queue, which keeps each XCD's waves on
 // neighbouring items and their blocks in its own L2, made the kernel 15 %
 // and 7 % slower -- the heaviest items all sit in one queue -- and runs of 4
 // to 256 units per queue were within 1 % of round-robin.)
-constexpr int kQueues = 8;
-// Counters sit 256 bytes apart so no two share a memory channel's line.
-constexpr int kQueueStride = 32;
+constexpr int kQueues = 16;
+// (One word serves some 80 M atomics a second.  Kernel time with 8 / 16 / 32
+// / 64 queues: R-MAT scale 20 in 8 x 8 blocks 1.74 / 1.71 / 1.70 / 1.70 ms,
+// scale 22 9.76 / 9.74 / 10.05 / 10.02, scale 16 in one block 386 / 351 / 361
+// / 348 us, Erdos-Renyi in 16 x 16 689 / 628 / 633 / 625 us.)
+// Counters sit 128 bytes apart so no two share a line.
+constexpr int kQueueStride = 16;
 constexpr int kQueueWords = kQueues * kQueueStride;
 // Queue counters of one counting launch: one set per part of a launch split
 // by staged-list length (at most 3 parts), all cleared before the launch, so

@@ -154,15 +154,10 @@ void k_edge_support(const int64_t *__restrict__ row_off,
     const int64_t waves = static_cast<int64_t>(gridDim.x) * kSupWaves;
     const int grab = static_cast<int>(max(min(nunits / (4 * waves), static_cast<int64_t>(kSupGrab)),
                                           static_cast<int64_t>(1)));
-    const int home = static_cast<int>(blockIdx.x % kSupQueues);
-    for (int qi = 0; qi < kSupQueues; ++qi) {
-      const int qq = (home + qi) % kSupQueues;
-      for (;;) {
-        unsigned long long c0 = 0;
-        if (lane == 0) c0 = atomicAdd(&next[qq * kSupQueueStride], 1ull);
-        c0 = shfl_t(c0, 0);
-        const int64_t u0 = (static_cast<int64_t>(c0) * kSupQueues + qq) * grab;  // grab g sits on queue g mod 8
-        if (u0 >= nunits) break;
+    UnitTaker<kSupQueues, kSupQueueStride> taker(next, (nunits + grab - 1) / grab, waves,
+                                                 static_cast<int64_t>(blockIdx.x) * kSupWaves + threadIdx.x / kWave);
+    for (int64_t g; (g = taker.take(lane)) >= 0;) {
+        const int64_t u0 = g * grab;
         const int ng = static_cast<int>(min(nunits - u0, static_cast<int64_t>(grab)));
         // the units' headers, one per lane; then per unit its in-edges, one per
         // lane (position of (a, b) and its walk's length), and the first 64
@@ -386,7 +381,6 @@ void k_edge_support(const int64_t *__restrict__ row_off,
             }
         wave_lds_sync();  // before the next unit is staged
         }
-      }
     }
     found = wave_sum(found);
     if (lane == 0 && found) atomicAdd(total, found);

@@ -144,6 +144,55 @@ __device__ __forceinline__ void add_run_lengths(bool valid, int64_t key, int32_t
     }
 }
 
+// Hands the units [0, units) of a persistent launch to its waves.  A wave's
+// first unit is its own number; the others are dealt round-robin to Q
+// counters (STRIDE words apart, zero before the launch), of which a wave
+// starts with that of its workgroup, b mod Q, and moves on when it runs dry.
+//
+// Operations on one word take some 25 ns each whoever makes them, so a wave's
+// first take and its takes that come back empty count: with all takes from
+// counters and every wave trying each of 16 queues at the end, a launch of
+// 7,168 waves spent over 200 us on them (R-MAT scale 14 counted in one block,
+// 137 us with 5,188 waves).  Queues run dry nearly together, so a wave gives
+// up after kTakeTries of them, unless the launch is too small for every queue
+// to have a workgroup of its own.  (Reading the counters before a take made it
+// worse: those reads wait for the same words.)
+constexpr int kTakeTries = 2;
+
+template <int Q, int STRIDE>
+class UnitTaker {
+  public:
+    // waves: waves of the launch, wave: this one's number (workgroup by
+    // workgroup)
+    __device__ __forceinline__ UnitTaker(unsigned long long *next, int64_t units, int64_t waves, int64_t wave)
+        : next_(next), units_(units), waves_(waves), first_(wave), q_(static_cast<int>(blockIdx.x % Q)),
+          tries_(units <= waves ? 0 : gridDim.x >= Q ? kTakeTries : Q) {}
+    // The next unit, or -1 when this wave is done; every lane calls it.
+    __device__ __forceinline__ int64_t take(int lane) {
+        if (first_ >= 0) {
+            const int64_t u = first_;
+            first_ = -1;
+            if (u >= units_) return -1;
+            return u;
+        }
+        while (tries_ > 0) {
+            unsigned long long c = 0;
+            if (lane == 0) c = atomicAdd(&next_[q_ * STRIDE], 1ull);
+            c = shfl_t(c, 0);
+            const int64_t u = waves_ + static_cast<int64_t>(c) * Q + q_;
+            if (u < units_) return u;
+            --tries_;
+            q_ = (q_ + 1) % Q;
+        }
+        return -1;
+    }
+
+  private:
+    unsigned long long *next_;
+    int64_t units_, waves_, first_;
+    int q_, tries_;
+};
+
 // Order LDS accesses of the lanes of one wave: what a lane wrote before the
 // call is visible to every lane of the wave after it.
 __device__ __forceinline__ void wave_lds_sync() {
