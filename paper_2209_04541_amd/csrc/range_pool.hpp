@@ -1,5 +1,5 @@
-// First-fit allocator of byte ranges of a device pool (the block caches of
-// the streamed counts).
+// First-fit allocator of byte ranges of a device pool (the block cache of the
+// streamed 4-clique count).
 #pragma once
 
 #include <cstdint>
