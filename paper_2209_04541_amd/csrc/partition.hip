@@ -64,12 +64,6 @@ __global__ __launch_bounds__(B) void k_nnz_cut_table(const int64_t *__restrict__
     if (threadIdx.x == 0) ct->p = p;
 }
 
-// The row walks below give each row to one wavefront: rows of the reversed
-// graph (in-edges) reach tens of thousands of entries on skewed graphs.
-// Lane l of the wave handles stripe j0 + l of the row's column stripes
-// [j0, j1] (p <= 64), finding the run of that stripe by binary search in the
-// sorted row; per-entry work strides the row 64 entries at a time.
-
 // First index in [lo, hi) whose column is >= c (hi when none).
 __device__ __forceinline__ int64_t first_at_least(const int32_t *__restrict__ col, int64_t lo,
                                                   int64_t hi, int32_t c) {
@@ -92,192 +86,224 @@ __device__ __forceinline__ int32_t stripe_lds(int32_t x, const int32_t *c, int32
     return lo;
 }
 
-struct RowRun {
-    int32_t si, j;   // row stripe; this lane's column stripe
-    int64_t lo, hi;  // this lane's run [lo, hi) (empty when lo == hi)
+// Last row in [lo, hi) that starts at or before entry e (row_off[lo] <= e).
+__device__ __forceinline__ int32_t row_search(const int64_t *__restrict__ row_off, int32_t lo, int32_t hi, int64_t e) {
+    while (hi - lo > 1) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (row_off[mid] <= e) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// The same over all n rows, 64 samples a step, by the whole wave.
+__device__ __forceinline__ int32_t row_search_wave(const int64_t *__restrict__ row_off, int32_t n, int64_t e) {
+    int32_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int32_t step = (hi - lo - 1) / kWave + 1;
+        const int64_t at = lo + static_cast<int64_t>(lane_id()) * step;
+        const uint64_t below = __ballot(at < hi && row_off[at < hi ? at : lo] <= e);
+        lo += (__popcll(below) - 1) * step;
+        if (step < hi - lo) hi = lo + step;
+    }
+    return lo;
+}
+
+// The passes over the entries give every workgroup the same number of
+// consecutive entries, whatever the rows' lengths: a row a thread or a wave
+// waits for the longest one, which took two launches (short rows flattened 64
+// to a wave, rows over 64 entries in pieces) of 30 to 80 us each, also where
+// the graph was small.  Partition into 8 x 8 blocks, before and now: R-MAT scale
+// 12 490 -> 310 us, 16 550 -> 400, 20 1460 -> 1245, 21 2540 -> 2280;
+// Erdos-Renyi, 300 K vertices of even rows, 580 -> 585 (into 4 x 4 545 -> 575).
+// Tiles of 4 B / 8 B / 16 B entries: scale 16 365 / 400 / 515 us, scale 21 2615
+// / 2270 / 2325.
+constexpr int kTile = 8 * B;  // entries of a workgroup
+// Up to this many rows are marked at their first entries; a tile that spans
+// more (a stretch of empty rows) looks its entries' rows up.
+constexpr int32_t kMarkRows = 4 * kTile;
+
+struct Tile {
+    int64_t t0;        // entries [t0, t0 + count)
+    int32_t count;
+    int32_t r0;        // row of the first entry
+    bool starts, ends; // the first entry starts its row, the last one ends its own
 };
 
-// Row x's run in stripe j0 + lane (a long row: more than 64 entries).
-// Every lane calls it for the same x.  Each lane finds where its stripe
-// starts; its run ends where the next lane's starts.  The search is first
-// narrowed by 64 evenly spaced samples of the row, read in one load: lane
-// j counts the samples below c[j] with one ballot per stripe of the row.
-__device__ __forceinline__ RowRun row_run(const int32_t *__restrict__ col, int64_t e0, int64_t e1,
-                                          int32_t x, const int32_t *c, int32_t p) {
-    RowRun r;
-    const int lane = lane_id();
-    r.si = stripe_lds(x, c, p);
-    const int32_t j0 = stripe_lds(col[e0], c, p);
-    const int32_t j1 = stripe_lds(col[e1 - 1], c, p);
-    r.j = j0 + lane;
-    const int64_t len = e1 - e0;
-    auto sample_at = [&](int q) { return e0 + ((static_cast<int64_t>(q) * len) >> 6); };
-    const int32_t sv = col[sample_at(lane)];
-    int below = 0;  // samples whose column is below c[r.j]
-    for (int32_t k = 1; k <= j1 - j0; ++k) {
-        const uint64_t m = __ballot(sv < c[j0 + k]);
-        if (lane == k) below = __popcll(m);
-    }
-    int64_t start = e0;
-    if (lane >= 1 && r.j <= j1) {
-        // samples 0 .. below-1 lie below c[r.j] (sample 0 is e0, in stripe
-        // j0 < r.j, so below >= 1) and sample `below` (or e1) does not
-        const int64_t lo = sample_at(below - 1) + 1;
-        const int64_t hi = below < 64 ? sample_at(below) : e1;
-        start = first_at_least(col, lo, hi, c[r.j]);
-    }
-    const int64_t next = __shfl(start, lane < 63 ? lane + 1 : 63);
-    r.lo = r.hi = 0;
-    if (r.j <= j1) {
-        r.lo = start;
-        r.hi = r.j == j1 ? e1 : next;
-    }
-    return r;
+// first[t]: the row of tile t's first entry; one more for the last entry.  A
+// wave finds each.  Passes over more than kTableTiles tiles, whose workgroups
+// come in several rounds, take them from there; in smaller ones two waves of
+// each workgroup search (partition of R-MAT scale 16 / 20 / 21, 430 / 7,700 /
+// 15,400 tiles, into 8 x 8 blocks: 419 / 1249 / 2287 us with the table, 400 /
+// 1289 / 2465 without).
+constexpr unsigned kTableTiles = 2048;
+__global__ __launch_bounds__(B) void k_tile_first(const int64_t *__restrict__ row_off, int32_t n, int64_t m,
+                                                  int64_t tiles, int32_t *__restrict__ first) {
+    const int64_t t = (static_cast<int64_t>(blockIdx.x) * B + threadIdx.x) / kWave;
+    if (t > tiles) return;
+    const int32_t r = row_search_wave(row_off, n, min(t * kTile, m - 1));
+    if (lane_id() == 0) first[t] = r;
 }
 
-// Rows are walked in two kinds of launch: short rows (at most kLongRow
-// entries) a thread each, or 64 at a time per wave with their entries
-// flattened over the lanes; long rows, collected into a device list first,
-// by one wave each, lane l finding the run of stripe j0 + l by binary
+// The rows of tile number `tile`: rows[i] is the row of entry t0 + i, relative
+// to r0.  Every thread of the workgroup calls it; without `first`, two waves
 // search.
-constexpr int64_t kLongRow = 64;
-
-// Calls f(si, j, lo, hi) for every non-empty run [lo, hi) of row x (a short
-// row) in column stripe j.
-template <class F>
-__device__ __forceinline__ void short_row_runs(const int32_t *__restrict__ col, int64_t e0,
-                                               int64_t e1, int32_t x, const int32_t *c,
-                                               int32_t p, F f) {
-    const int32_t si = stripe_lds(x, c, p);
-    int32_t j = stripe_lds(col[e0], c, p);
-    int64_t lo = e0;
-    for (int64_t e = e0; e < e1; ++e) {
-        const int32_t y = col[e];
-        if (y >= c[j + 1]) {
-            f(si, j, lo, e);
-            lo = e;
-            j = stripe_lds(y, c, p);
+__device__ __forceinline__ Tile tile_rows(const int64_t *__restrict__ row_off, int32_t n, int64_t m, int64_t tile,
+                                          const int32_t *__restrict__ first, int32_t *rows) {
+    __shared__ int32_t s_row[2];
+    __shared__ uint32_t s_max[B / kWave];
+    const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
+    Tile t;
+    t.t0 = tile * kTile;
+    t.count = static_cast<int32_t>(min(m - t.t0, static_cast<int64_t>(kTile)));
+    if (!first && w < 2) {
+        const int32_t r = row_search_wave(row_off, n, min(t.t0 + w * kTile, m - 1));
+        if (lane == 0) s_row[w] = r;
+    }
+    for (int i = tid; i < kTile; i += B) rows[i] = 0;
+    __syncthreads();
+    // (r1: the row of the entry after the tile)
+    t.r0 = first ? first[tile] : s_row[0];
+    const int32_t r1 = first ? first[tile + 1] : s_row[1], nr = r1 - t.r0;
+    t.starts = row_off[t.r0] == t.t0;
+    if (nr <= kMarkRows) {
+        for (int32_t q = 1 + tid; q <= nr; q += B) {
+            const int64_t e0 = row_off[t.r0 + q];
+            // (empty rows share a start)
+            if (row_off[t.r0 + q + 1] > e0 && e0 - t.t0 < t.count) rows[e0 - t.t0] = q;
         }
-    }
-    f(si, j, lo, e1);
-}
-
-// The short rows, a thread each: calls g(x, e0, e1) for every non-empty row
-// x of at most kLongRow entries.
-template <class G>
-__device__ __forceinline__ void for_short_rows(const int64_t *__restrict__ row_off, int32_t n, G g) {
-    for (int64_t x = blockIdx.x * int64_t(B) + threadIdx.x; x < n; x += int64_t(gridDim.x) * B) {
-        const int64_t e0 = row_off[x], e1 = row_off[x + 1];
-        if (e0 == e1 || e1 - e0 > kLongRow) continue;
-        g(static_cast<int32_t>(x), e0, e1);
-    }
-}
-
-// Counting kernels, which act once per run, walk each short row with one
-// thread (a run needs one comparison per entry); kernels that write every
-// entry take the rows' entries flattened instead:
-//
-// The short rows (at most kLongRow entries) of all rows, 64 consecutive rows
-// per wave, their entries flattened: the wave's short rows are numbered
-// through by a scan of their lengths (long rows count as empty), and lane l
-// takes flattened entry 64 k + l, finding its row by a search of the
-// prefix sums in LDS and the start of its run (row x, column stripe j) from
-// the run starts of the chunk (one ballot) or, for a run begun in an
-// earlier chunk, the carried start.  Calls f(x, si, j, e, y, lo) for every
-// entry e = (x, y) of a short row, lo being the first entry of its run.
-// Every lane of the workgroup must call it.  Without RUNS, only x, e and y
-// are meaningful (no stripes are looked up).
-template <bool RUNS = true, class F>
-__device__ __forceinline__ void flat_short_rows(const int64_t *__restrict__ row_off,
-                                                const int32_t *__restrict__ col, int32_t n,
-                                                const int32_t *c, int32_t p, F f) {
-    __shared__ int32_t s_pre[B / 64][65];  // flattened start of each row, then the total
-    __shared__ int64_t s_e0[B / 64][64];   // first entry of each row
-    __shared__ int32_t s_si[B / 64][64];   // row stripes
-    const int w = threadIdx.x >> 6, lane = lane_id();
-    const uint64_t le_mask = lane == 63 ? ~0ull : ((2ull << lane) - 1);
-    const int64_t stride = int64_t(gridDim.x) * B;
-    for (int64_t x0 = blockIdx.x * int64_t(B) + (threadIdx.x & ~63); x0 < n; x0 += stride) {
-        const int64_t x = x0 + lane;
-        const int64_t e0 = x < n ? row_off[x] : 0;
-        const int64_t e1 = x < n ? row_off[x + 1] : 0;
-        const int32_t len = (e1 - e0 <= kLongRow) ? static_cast<int32_t>(e1 - e0) : 0;
-        const int32_t incl = wave_inclusive_scan(len);
-        s_pre[w][lane] = incl - len;
-        if (lane == 63) s_pre[w][64] = incl;
-        s_e0[w][lane] = e0;
-        s_si[w][lane] = (RUNS && x < n) ? stripe_lds(static_cast<int32_t>(x), c, p) : 0;
-        wave_lds_sync();
-        const int32_t total = s_pre[w][64];
-        int64_t carry = 0;
-        for (int32_t base = 0; base < total; base += kWave) {
-            const int32_t t = base + lane;
-            const bool valid = t < total;
-            int r = 0;
+        __syncthreads();
+        // every entry belongs to the last row marked at or before it
+        uint32_t v[kTile / B], top = 0;
 #pragma unroll
-            for (int step = 32; step >= 1; step >>= 1)
-                if (s_pre[w][r + step] <= t) r += step;
-            const int64_t rs = s_e0[w][r];
-            const int64_t e = rs + (t - s_pre[w][r]);
-            const int32_t y = valid ? col[e] : 0;
-            int32_t j = 0;
-            int64_t lo = 0;
-            if (RUNS) {
-                j = stripe_lds(y, c, p);
-                const bool is_start = valid && (e == rs || col[e > rs ? e - 1 : rs] < c[j]);
-                const uint64_t starts = __ballot(is_start);
-                const uint64_t mine = starts & le_mask;
-                // entry number of the lane's run start: runs never cross rows,
-                // so the flattened distance back to the start is e - lo
-                const int32_t back = mine ? lane - (63 - __clzll(mine)) : lane + 1 + static_cast<int32_t>(carry);
-                lo = e - back;
-                if (starts) carry = 63 - (63 - __clzll(starts));
-                else carry += kWave;
-            }
-            if (valid) f(static_cast<int32_t>(x0 + r), s_si[w][r], j, e, y, lo);
+        for (int i = 0; i < kTile / B; ++i) {
+            top = max(top, static_cast<uint32_t>(rows[tid * (kTile / B) + i]));
+            v[i] = top;
         }
-        wave_lds_sync();
+        const uint32_t incl = wave_max_scan_dpp(top);
+        const uint32_t up = __shfl_up(incl, 1);
+        if (lane == kWave - 1) s_max[w] = incl;
+        __syncthreads();
+        uint32_t before = lane ? up : 0u;
+        for (int q = 0; q < w; ++q) before = max(before, s_max[q]);
+#pragma unroll
+        for (int i = 0; i < kTile / B; ++i) rows[tid * (kTile / B) + i] = static_cast<int32_t>(max(v[i], before));
+    } else {
+        int32_t r = t.r0;
+        for (int i = tid * (kTile / B); i < min((tid + 1) * (kTile / B), t.count); ++i) {
+            r = row_search(row_off, r, r1 + 1, t.t0 + i);
+            rows[i] = r - t.r0;
+        }
     }
+    __syncthreads();
+    t.ends = row_off[t.r0 + rows[t.count - 1] + 1] == t.t0 + t.count;
+    return t;
 }
 
-// Long rows are cut into chunks of at most kChunk entries, listed as
-// (row << 32 | chunk index), so that a hub row of the reversed graph spreads
-// over many waves.
-constexpr int64_t kChunk = 2048;
+// Calls f(x, e, y) for every entry e = (x, y) of the workgroup's tile.
+template <class F>
+__device__ __forceinline__ void for_entries(const int64_t *__restrict__ row_off, const int32_t *__restrict__ col,
+                                            int32_t n, int64_t m, const int32_t *__restrict__ first, F f) {
+    __shared__ int32_t rows[kTile];
+    const Tile t = tile_rows(row_off, n, m, blockIdx.x, first, rows);
+    for (int i = threadIdx.x; i < t.count; i += B) f(t.r0 + rows[i], t.t0 + i, col[t.t0 + i]);
+}
 
-__global__ void k_collect_long(const int64_t *__restrict__ row_off, int32_t n,
-                               int64_t *__restrict__ list, unsigned int *__restrict__ count) {
-    for (int64_t x = blockIdx.x * int64_t(B) + threadIdx.x; x < n; x += int64_t(gridDim.x) * B) {
-        const int64_t len = row_off[x + 1] - row_off[x];
-        if (len <= kLongRow) continue;
-        const unsigned int nch = static_cast<unsigned int>((len + kChunk - 1) / kChunk);
-        const unsigned int at = atomicAdd(count, nch);
-        for (unsigned int c = 0; c < nch; ++c) list[at + c] = (x << 32) | c;
+// Stripe look-up of many entries: seven thresholds in registers split the
+// stripes into eight groups; more than eight stripes leave up to three steps of
+// search in LDS.  (With all steps in LDS, and the entries' neighbours read
+// there, a pass over R-MAT scale 20 in 8 x 8 blocks took 88 us instead of 73;
+// what is left is bound by instructions, some 100 for 64 entries.)
+struct Stripes {
+    const int32_t *c;
+    int32_t p, per;  // stripes of a group
+    int32_t t[7];
+    __device__ __forceinline__ Stripes(const int32_t *cuts, int32_t np) : c(cuts), p(np), per((np + 7) / 8) {
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+            t[k] = __builtin_amdgcn_readfirstlane((k + 1) * per < np ? cuts[(k + 1) * per] : INT32_MAX);
     }
+    __device__ __forceinline__ int32_t of(int32_t y) const {
+        int32_t g = 0;
+#pragma unroll
+        for (int k = 0; k < 7; ++k) g += y >= t[k];
+        if (per == 1) return g;
+        int32_t lo = g * per, hi = min(lo + per, p) - 1;
+        while (lo < hi) {
+            const int32_t mid = (lo + hi + 1) >> 1;
+            if (c[mid] <= y) lo = mid;
+            else hi = mid - 1;
+        }
+        return lo;
+    }
+};
+
+// x of the lane before (wave_shr:1); lane 0 takes `first`.
+__device__ __forceinline__ int32_t lane_before(int32_t x, int32_t first) {
+    return __builtin_amdgcn_update_dpp(first, x, 0x138, 0xf, 0xf, false);
 }
 
-// Capacity of the chunk list: every long row adds one chunk plus one per
-// kChunk entries.
-inline size_t long_list_capacity(int32_t n, int64_t m) {
-    return static_cast<size_t>(n) + static_cast<size_t>(m / kChunk) + 1;
-}
-
-// The listed chunks of long rows, a wave at a time.  Calls g(x, e0, e1, c0,
-// c1) with the row's entries [e0, e1) and the entries [c0, c1) this call
-// owns, uniformly across the wave.
-template <class G>
-__device__ __forceinline__ void for_long_rows(const int64_t *__restrict__ row_off,
-                                              const int64_t *__restrict__ list,
-                                              const unsigned int *__restrict__ count, G g) {
-    const int64_t nwaves = (int64_t(gridDim.x) * B) >> 6;
-    const int64_t nl = *count;
-    for (int64_t i = (blockIdx.x * int64_t(B) + threadIdx.x) >> 6; i < nl; i += nwaves) {
-        const int64_t v = list[i];
-        const int32_t x = static_cast<int32_t>(v >> 32);
-        const int64_t e0 = row_off[x], e1 = row_off[x + 1];
-        const int64_t c0 = e0 + (v & 0xffffffffll) * kChunk;
-        const int64_t c1 = c0 + kChunk < e1 ? c0 + kChunk : e1;
-        g(x, e0, e1, c0, c1);
+// Calls f(x, si, j, e, y, at, last) for every entry e = (x, y) of the
+// workgroup's tiles: si and j are the stripes of x and y, at the place of e in
+// its run (row x, column stripe j), last whether e ends the run.  Every lane
+// calls it; c: the cuts, in LDS.  A wave takes 512 consecutive entries, 64 at
+// a time, and marks in one ballot the entries that begin a run, up to and
+// including the one after the 64: an entry's run began at the mark before it,
+// in the 64 or earlier ones, or, once per wave, where a search of the row finds
+// it, and an entry ends its run if a mark follows.
+template <class F>
+__device__ __forceinline__ void for_runs(const int64_t *__restrict__ row_off, const int32_t *__restrict__ col,
+                                         int32_t n, int64_t m, const int32_t *__restrict__ first, const int32_t *c,
+                                         int32_t p, F f) {
+    __shared__ int32_t rows[kTile];
+    const int lane = lane_id();
+    const uint64_t le_mask = ~0ull >> (kWave - 1 - lane);
+    constexpr int kPart = kTile / (B / kWave);
+    const Stripes stripes(c, p);
+    for (int64_t tile = blockIdx.x; tile * kTile < m; tile += gridDim.x) {
+        const Tile t = tile_rows(row_off, n, m, tile, first, rows);
+        const int i0 = static_cast<int>(threadIdx.x / kWave) * kPart, i1 = min(i0 + kPart, t.count);
+        // rows of one stripe, as nearly everywhere: no look-up per entry
+        const int32_t si0 = stripes.of(t.r0), r_end = rows[t.count - 1];
+        const bool same = t.r0 + r_end < c[si0 + 1];
+        // row and column stripe of entry t0 + i, the one after the tile included
+        // (row -1: it begins a row, whatever its number)
+        auto row_of = [&](int i) { return i < t.count ? rows[i] : t.ends ? -1 : r_end; };
+        auto col_of = [&](int i) { return i <= i1 && t.t0 + i < m ? col[t.t0 + i] : 0; };
+        if (i0 < i1) {
+            // the entry before the wave's first
+            int32_t rp = i0 ? rows[i0 - 1] : t.starts ? -1 : 0;
+            int32_t jp = t.t0 + i0 ? stripes.of(col[t.t0 + i0 - 1]) : 0;
+            int32_t y = col_of(i0 + lane), r = row_of(min(i0 + lane, i1)), j = stripes.of(y);
+            // first entry of the run that the 64 begin in, relative to t0
+            int32_t carry = INT32_MAX;
+            for (int base = i0; base < i1; base += kWave) {
+                const int i = base + lane;
+                const int32_t yn = col_of(i + kWave), rn = row_of(min(i + kWave, i1)), jn = stripes.of(yn);
+                const int32_t rb = lane_before(r, rp), jb = lane_before(j, jp);  // (on every lane)
+                const uint64_t marks = __ballot((rb != r) | (jb != j));
+                rp = __builtin_amdgcn_readlane(r, kWave - 1);
+                jp = __builtin_amdgcn_readlane(j, kWave - 1);
+                const bool more = __builtin_amdgcn_readlane(rn, 0) != rp || __builtin_amdgcn_readlane(jn, 0) != jp;
+                const uint64_t ends = (marks >> 1) | (static_cast<uint64_t>(more) << (kWave - 1));
+                if (carry == INT32_MAX && !(marks & 1)) {  // the wave's first entry lies inside a run
+                    const int32_t j0 = __builtin_amdgcn_readfirstlane(j);
+                    carry = static_cast<int32_t>(
+                        first_at_least(col, row_off[t.r0 + rows[i0]], t.t0 + i0, c[j0]) - t.t0);
+                }
+                const uint64_t mine = marks & le_mask;
+                const int32_t lo = mine ? base + (63 - __clzll(static_cast<long long>(mine))) : carry;
+                if (i < i1) {
+                    const int32_t x = t.r0 + r;
+                    f(x, same ? si0 : stripes.of(x), j, t.t0 + i, y, i - lo, ((ends >> lane) & 1) != 0);
+                }
+                if (marks) carry = base + (63 - __clzll(static_cast<long long>(marks)));
+                y = yn;
+                r = rn;
+                j = jn;
+            }
+        }
+        __syncthreads();  // before the next tile's rows are marked
     }
 }
 
@@ -287,7 +313,10 @@ __device__ __forceinline__ int pair_index(int a, int b, int p) {
     return lo * (2 * p - lo + 1) / 2 + (hi - lo);
 }
 
-constexpr int kMaxPairs = kMaxP * (kMaxP + 1) / 2;
+// Words that the workgroups of k_block_sizes add their walked entries to, and
+// their number: additions to one word take some 25 ns each.
+constexpr int kWalkWords = 64;
+constexpr unsigned kSizesGrid = 4096;
 
 // Per block (i, j): number of entries, of non-empty rows and of work items
 // (each row's run split into pieces of at most kSplitV entries).  A pass
@@ -295,29 +324,27 @@ constexpr int kMaxPairs = kMaxP * (kMaxP + 1) / 2;
 // graph; else i >= j, its transpose), so each workgroup accumulates per
 // unordered stripe pair in LDS and flushes its non-zero counters to the
 // p x p arrays.
-template <bool LONG>
 __global__ __launch_bounds__(B) void k_block_sizes(const int64_t *__restrict__ row_off,
-                                                   const int32_t *__restrict__ col, int32_t n,
-                                                   const CutTable *__restrict__ ctp, const int64_t *__restrict__ list,
-                                                   const unsigned int *__restrict__ count, bool upper,
+                                                   const int32_t *__restrict__ col, int32_t n, int64_t m,
+                                                   const int32_t *__restrict__ first,
+                                                   const CutTable *__restrict__ ctp, bool upper,
                                                    unsigned long long *__restrict__ nnz,
                                                    unsigned int *__restrict__ items,
                                                    unsigned int *__restrict__ rows,
                                                    unsigned long long *__restrict__ walk,
                                                    unsigned int *__restrict__ maxrun) {
-    __shared__ unsigned int s_nnz[kMaxPairs];
-    __shared__ unsigned int s_items[kMaxPairs];
-    __shared__ unsigned int s_rows[kMaxPairs];
-    __shared__ unsigned int s_max[kMaxPairs];
+    // per stripe pair: rows (high word) and items, then entries, then the
+    // longest run
+    extern __shared__ unsigned long long s_cnt[];
     __shared__ int32_t s_c[kMaxP + 1];
     __shared__ unsigned long long s_walk;
     const int p = ctp->p;
     const int pp = p * p;
     const int npairs = p * (p + 1) / 2;
+    unsigned int *s_nnz = reinterpret_cast<unsigned int *>(s_cnt + npairs), *s_max = s_nnz + npairs;
     for (int q = threadIdx.x; q < npairs; q += B) {
+        s_cnt[q] = 0;
         s_nnz[q] = 0;
-        s_items[q] = 0;
-        s_rows[q] = 0;
         s_max[q] = 0;
     }
     for (int q = threadIdx.x; q <= p; q += B) s_c[q] = ctp->c[q];
@@ -327,31 +354,16 @@ __global__ __launch_bounds__(B) void k_block_sizes(const int64_t *__restrict__ r
     // A_ij and every k >= j: the run of stripe j has (hi - lo) entries, each
     // walking the (e1 - lo) entries of stripes j and above.
     unsigned long long my_walk = 0;
-    int64_t row_end = 0;
-    auto add = [&](int32_t si, int32_t j, int64_t lo, int64_t hi) {
-        const int64_t cnt = hi - lo;
-        if (cnt > 0) {
-            const int t = pair_index(si, j, p);
-            atomicAdd(&s_nnz[t], static_cast<unsigned int>(cnt));
-            atomicAdd(&s_items[t], static_cast<unsigned int>((cnt + kSplitV - 1) / kSplitV));
-            atomicAdd(&s_rows[t], 1u);
-            atomicMax(&s_max[t], static_cast<unsigned int>(cnt));
-            my_walk += static_cast<unsigned long long>(cnt) * static_cast<unsigned long long>(row_end - lo);
-        }
-    };
-    if (LONG) {
-        for_long_rows(row_off, list, count, [&](int32_t x, int64_t e0, int64_t e1, int64_t c0, int64_t) {
-            row_end = e1;
-            if (c0 != e0) return;  // per-row counts: the first chunk only
-            const RowRun r = row_run(col, e0, e1, x, s_c, p);
-            add(r.si, r.j, r.lo, r.hi);
-        });
-    } else {
-        for_short_rows(row_off, n, [&](int32_t x, int64_t e0, int64_t e1) {
-            row_end = e1;
-            short_row_runs(col, e0, e1, x, s_c, p, add);
-        });
-    }
+    for_runs(row_off, col, n, m, first, s_c, p,
+             [&](int32_t x, int32_t si, int32_t j, int64_t e, int32_t, int32_t at, bool last) {
+                 if (!last) return;
+                 const unsigned int cnt = static_cast<unsigned int>(at) + 1;
+                 const int t = pair_index(si, j, p);
+                 atomicAdd(&s_cnt[t], (1ull << 32) + (cnt + kSplitV - 1) / kSplitV);
+                 atomicAdd(&s_nnz[t], cnt);
+                 if (cnt > s_max[t]) atomicMax(&s_max[t], cnt);
+                 if (walk) my_walk += cnt * static_cast<unsigned long long>(row_off[x + 1] - e + at);
+             });
     if (walk) {
         my_walk = wave_sum(my_walk);
         if (lane_id() == 0 && my_walk) atomicAdd(&s_walk, my_walk);
@@ -361,24 +373,23 @@ __global__ __launch_bounds__(B) void k_block_sizes(const int64_t *__restrict__ r
         const int a = q / p, b = q - a * p;
         if (upper ? a > b : a < b) continue;
         const int t = pair_index(a, b, p);
-        if (s_nnz[t]) {
+        if (s_cnt[t]) {
             atomicAdd(&nnz[q], static_cast<unsigned long long>(s_nnz[t]));
-            atomicAdd(&items[q], s_items[t]);
-            atomicAdd(&rows[q], s_rows[t]);
+            atomicAdd(&items[q], static_cast<unsigned int>(s_cnt[t]));
+            atomicAdd(&rows[q], static_cast<unsigned int>(s_cnt[t] >> 32));
             if (maxrun) atomicMax(&maxrun[q], s_max[t]);
         }
     }
-    if (walk && threadIdx.x == 0 && s_walk) atomicAdd(walk, s_walk);
+    if (walk && threadIdx.x == 0 && s_walk) atomicAdd(&walk[blockIdx.x % kWalkWords], s_walk);
 }
 
 // Per-row entry counts of every block the row touches, written at the row's
 // slot of the block's dense row range (slot_base indexed by (row stripe,
 // column stripe)).
-template <bool LONG>
 __global__ __launch_bounds__(B) void k_row_slot_counts(const int64_t *__restrict__ row_off,
-                                                       const int32_t *__restrict__ col, int32_t n,
-                                                       const CutTable *__restrict__ ctp, const int64_t *__restrict__ list,
-                                                       const unsigned int *__restrict__ count,
+                                                       const int32_t *__restrict__ col, int32_t n, int64_t m,
+                                                       const int32_t *__restrict__ first,
+                                                       const CutTable *__restrict__ ctp,
                                                        const int64_t *__restrict__ slot_base,
                                                        uint32_t *__restrict__ slots) {
     __shared__ int32_t s_c[kMaxP + 1];
@@ -387,21 +398,10 @@ __global__ __launch_bounds__(B) void k_row_slot_counts(const int64_t *__restrict
     for (int q = threadIdx.x; q <= p; q += B) s_c[q] = ctp->c[q];
     for (int q = threadIdx.x; q < p; q += B) s_base[q] = ctp->base[q];
     __syncthreads();
-    auto put = [&](int32_t x, int32_t si, int32_t j, int64_t lo, int64_t hi) {
-        if (hi > lo) slots[slot_base[si * p + j] + (x - s_base[si])] = static_cast<uint32_t>(hi - lo);
-    };
-    if (LONG) {
-        for_long_rows(row_off, list, count, [&](int32_t x, int64_t e0, int64_t e1, int64_t c0, int64_t) {
-            if (c0 != e0) return;  // per-row counts: the first chunk only
-            const RowRun r = row_run(col, e0, e1, x, s_c, p);
-            put(x, r.si, r.j, r.lo, r.hi);
-        });
-    } else {
-        for_short_rows(row_off, n, [&](int32_t x, int64_t e0, int64_t e1) {
-            short_row_runs(col, e0, e1, x, s_c, p,
-                           [&](int32_t si, int32_t j, int64_t lo, int64_t hi) { put(x, si, j, lo, hi); });
-        });
-    }
+    for_runs(row_off, col, n, m, first, s_c, p,
+             [&](int32_t x, int32_t si, int32_t j, int64_t, int32_t, int32_t at, bool last) {
+                 if (last) slots[slot_base[si * p + j] + (x - s_base[si])] = static_cast<uint32_t>(at) + 1;
+             });
 }
 
 // Block of slot q: the last block whose slot range starts at or before q.
@@ -468,73 +468,36 @@ __global__ __launch_bounds__(B) void k_fill_items(const uint32_t *__restrict__ f
 }
 
 // Entries: row x's run in stripe j goes to the block of (stripe(x), j) at the
-// row's dense offset, as local column ids.  In long launches the lane of
-// stripe j first computes where entry e of its run lands (dst[j] + e), then
-// the wave strides the row's entries.
-template <bool LONG>
+// row's dense offset, as local column ids (rptr_off, col_off: by stripe pair).
 __global__ __launch_bounds__(B) void k_fill_cols(const int64_t *__restrict__ row_off,
-                                                 const int32_t *__restrict__ col, int32_t n,
-                                                 const CutTable *__restrict__ ctp, const int64_t *__restrict__ list,
-                                                 const unsigned int *__restrict__ count,
-                                                 const int32_t *__restrict__ blk_index,
+                                                 const int32_t *__restrict__ col, int32_t n, int64_t m,
+                                                 const int32_t *__restrict__ first,
+                                                 const CutTable *__restrict__ ctp,
                                                  const int64_t *__restrict__ rptr_off,
                                                  const int64_t *__restrict__ col_off,
                                                  const int32_t *__restrict__ rbase,
                                                  int32_t *__restrict__ arena) {
     __shared__ int32_t s_c[kMaxP + 1];
     __shared__ int32_t s_base[kMaxP];
-    __shared__ int64_t s_dst[B / 64][kMaxP];
     const int p = ctp->p;
     for (int q = threadIdx.x; q <= p; q += B) s_c[q] = ctp->c[q];
     for (int q = threadIdx.x; q < p; q += B) s_base[q] = ctp->base[q];
     __syncthreads();
-    const int w = threadIdx.x >> 6;
-    const int lane = lane_id();
-    if (!LONG) {
-        flat_short_rows(row_off, col, n, s_c, p,
-                        [&](int32_t x, int32_t si, int32_t j, int64_t e, int32_t y, int64_t lo) {
-                            const int32_t b = blk_index[si * p + j];
-                            arena[col_off[b] + rbase[rptr_off[b] + (x - s_base[si])] + (e - lo)] = y - s_base[j];
-                        });
-        return;
-    }
-    for_long_rows(row_off, list, count, [&](int32_t x, int64_t e0, int64_t e1, int64_t c0, int64_t c1) {
-        const RowRun r = row_run(col, e0, e1, x, s_c, p);
-        if (r.hi > r.lo) {
-            const int32_t b = blk_index[r.si * p + r.j];
-            s_dst[w][lane] = col_off[b] + rbase[rptr_off[b] + (x - s_base[r.si])] - r.lo;
-        }
-        wave_lds_sync();
-        const int32_t j0 = r.j - lane;
-        for (int64_t e = c0 + lane; e < c1; e += kWave) {
-            const int32_t y = col[e];
-            const int32_t j = stripe_lds(y, s_c, p);
-            arena[s_dst[w][j - j0] + e] = y - s_base[j];
-        }
-        wave_lds_sync();
-    });
+    for_runs(row_off, col, n, m, first, s_c, p,
+             [&](int32_t x, int32_t si, int32_t j, int64_t, int32_t y, int32_t at, bool) {
+                 const int b = si * p + j;
+                 arena[col_off[b] + rbase[rptr_off[b] + (x - s_base[si])] + at] = y - s_base[j];
+             });
 }
 
 // Reversed oriented graph: for every entry (x, y), the key y and the value x.
-template <bool LONG>
 __global__ __launch_bounds__(B) void k_rev_pairs(const int64_t *__restrict__ row_off,
-                                                 const int32_t *__restrict__ col, int32_t n,
-                                                 const int64_t *__restrict__ list,
-                                                 const unsigned int *__restrict__ count,
-                                                 uint32_t *__restrict__ ky, uint32_t *__restrict__ vx) {
-    if (!LONG) {
-        flat_short_rows<false>(row_off, col, n, nullptr, 0,
-                               [&](int32_t x, int32_t, int32_t, int64_t e, int32_t y, int64_t) {
-                                   ky[e] = static_cast<uint32_t>(y);
-                                   vx[e] = static_cast<uint32_t>(x);
-                               });
-        return;
-    }
-    for_long_rows(row_off, list, count, [&](int32_t x, int64_t, int64_t, int64_t c0, int64_t c1) {
-        for (int64_t e = c0 + lane_id(); e < c1; e += kWave) {
-            ky[e] = static_cast<uint32_t>(col[e]);
-            vx[e] = static_cast<uint32_t>(x);
-        }
+                                                 const int32_t *__restrict__ col, int32_t n, int64_t m,
+                                                 const int32_t *__restrict__ first, uint32_t *__restrict__ ky,
+                                                 uint32_t *__restrict__ vx) {
+    for_entries(row_off, col, n, m, first, [&](int32_t x, int64_t e, int32_t y) {
+        ky[e] = static_cast<uint32_t>(y);
+        vx[e] = static_cast<uint32_t>(x);
     });
 }
 
@@ -545,29 +508,12 @@ __global__ __launch_bounds__(B) void k_rev_pairs(const int64_t *__restrict__ row
 // The pairs of the transpose (higher end; lower end as a local id) and the
 // block's local columns.
 __global__ __launch_bounds__(B) void k_one_pairs(const int64_t *__restrict__ row_off, const int32_t *__restrict__ col,
-                                                 int32_t n, int32_t lo, uint32_t *__restrict__ ky,
+                                                 int32_t n, int64_t m, int32_t lo, uint32_t *__restrict__ ky,
                                                  uint32_t *__restrict__ vx, int32_t *__restrict__ out_col) {
-    flat_short_rows<false>(row_off, col, n, nullptr, 0,
-                           [&](int32_t x, int32_t, int32_t, int64_t e, int32_t y, int64_t) {
-                               ky[e] = static_cast<uint32_t>(y);
-                               vx[e] = static_cast<uint32_t>(x - lo);
-                               out_col[e] = y - lo;
-                           });
-}
-
-__global__ __launch_bounds__(B) void k_one_pairs_long(const int64_t *__restrict__ row_off,
-                                                      const int32_t *__restrict__ col,
-                                                      const int64_t *__restrict__ list,
-                                                      const unsigned int *__restrict__ count, int32_t lo,
-                                                      uint32_t *__restrict__ ky, uint32_t *__restrict__ vx,
-                                                      int32_t *__restrict__ out_col) {
-    for_long_rows(row_off, list, count, [&](int32_t x, int64_t, int64_t, int64_t c0, int64_t c1) {
-        for (int64_t e = c0 + lane_id(); e < c1; e += kWave) {
-            const int32_t y = col[e];
-            ky[e] = static_cast<uint32_t>(y);
-            vx[e] = static_cast<uint32_t>(x - lo);
-            out_col[e] = y - lo;
-        }
+    for_entries(row_off, col, n, m, nullptr, [&](int32_t x, int64_t e, int32_t y) {
+        ky[e] = static_cast<uint32_t>(y);
+        vx[e] = static_cast<uint32_t>(x - lo);
+        out_col[e] = y - lo;
     });
 }
 
@@ -610,13 +556,8 @@ unsigned cap_grid(int64_t work) {
     return g > 65536u ? 65536u : g;
 }
 
-// Workgroups of a launch over long rows, whose chunks start with a chain of
-// dependent loads each: as many waves as fit the chip.
-constexpr unsigned kLongGrid = 2048;
-
-}  // namespace
-
-namespace {
+// Workgroups of a pass over m > 0 entries.
+unsigned tiles_of(int64_t m) { return static_cast<unsigned>((m + kTile - 1) / kTile); }
 
 // The partition of a non-empty graph into one block.  No sizes have to come
 // back from the device, so it is a dozen launches and no round trip, where the
@@ -654,16 +595,8 @@ void partition_one_block(pgabb_graph *g, int32_t lowest) {
     // the sort's last pass writes the transposed entries in place
     uint32_t *crow = reinterpret_cast<uint32_t *>(arena + bi.off_crow());
     uint32_t *v0 = passes % 2 ? vx.get() : crow, *v1 = passes % 2 ? crow : vx.get();
-    const unsigned lgrid = cap_grid(n);
-    k_one_pairs<<<lgrid, B, 0, s>>>(g->row_off.get(), g->col.get(), n, lo, ky.get(), v0, arena + bi.off_col());
-    if (g->max_out > kLongRow) {
-        DArray<int64_t> list(long_list_capacity(n, m), s);
-        DArray<unsigned int> nlong(1, s);
-        PGABB_HIP(hipMemsetAsync(nlong.get(), 0, sizeof(unsigned int), s));
-        k_collect_long<<<lgrid, B, 0, s>>>(g->row_off.get(), n, list.get(), nlong.get());
-        k_one_pairs_long<<<kLongGrid, B, 0, s>>>(g->row_off.get(), g->col.get(), list.get(), nlong.get(), lo, ky.get(),
-                                                 v0, arena + bi.off_col());
-    }
+    k_one_pairs<<<tiles_of(m), B, 0, s>>>(g->row_off.get(), g->col.get(), n, m, lo, ky.get(), v0,
+                                          arena + bi.off_col());
     PGABB_HIP(hipGetLastError());
     const bool alt = radix_sort_u32(ky.get(), ky_alt.get(), v0, v1, m, g->nb, s);
     if (alt != (passes % 2 == 1))  // one edge: nothing was sorted
@@ -738,25 +671,21 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
         partition_one_block(g, lowest);
     } else if (g->m > 0) {
         const size_t pp = static_cast<size_t>(p) * p;
-        const unsigned lgrid = cap_grid(n);
+        const unsigned tiles = tiles_of(g->m);
+        const bool table = tiles > kTableTiles;
+        DArray<int32_t> first_f(table ? static_cast<size_t>(tiles) + 1 : 0, s);
+        DArray<int32_t> first_r(table ? static_cast<size_t>(tiles) + 1 : 0, s);
+        const unsigned fgrid = tiles / (B / kWave) + 1;
+        if (table) k_tile_first<<<fgrid, B, 0, s>>>(g->row_off.get(), n, g->m, tiles, first_f.get());
+        PGABB_HIP(hipGetLastError());
 
         // one buffer cleared at once: block sizes -- nnz[pp] nnz_r[pp] (u64) |
-        // items[pp] items_r[pp] (u32) | walked entries of column walks (u64) |
+        // items[pp] items_r[pp] (u32) | walked entries of column walks (u64s) |
         // longest row run per block, non-empty rows, non-empty rows of the
-        // transposes (u32 each) -- which are copied back, and the numbers of
-        // long rows
-        const size_t nsz = 3 * pp + 1 + (3 * pp + 1) / 2;
-        DArray<unsigned long long> dsz(nsz + 1, s);
-        PGABB_HIP(hipMemsetAsync(dsz.get(), 0, (nsz + 1) * sizeof(unsigned long long), s));
-        unsigned int *nlong = reinterpret_cast<unsigned int *>(dsz.get() + nsz);
-
-        // rows longer than kLongRow, of the forward and the reversed graph
-        // (none: no launches over them)
-        const bool any_f = g->max_out > kLongRow, any_r = g->max_in > kLongRow;
-        DArray<int64_t> long_f(any_f ? long_list_capacity(n, g->m) : 0, s);
-        DArray<int64_t> long_r(any_r ? long_list_capacity(n, g->m) : 0, s);
-        if (any_f) k_collect_long<<<lgrid, B, 0, s>>>(g->row_off.get(), n, long_f.get(), nlong);
-        PGABB_HIP(hipGetLastError());
+        // transposes (u32 each) -- which are copied back
+        const size_t nsz = 3 * pp + kWalkWords + (3 * pp + 1) / 2;
+        DArray<unsigned long long> dsz(nsz, s);
+        PGABB_HIP(hipMemsetAsync(dsz.get(), 0, nsz * sizeof(unsigned long long), s));
 
         // ---- reversed oriented graph (in-edges, sorted by (y, x)): its blocks
         // are the transposes of the forward blocks
@@ -766,11 +695,7 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
         const int32_t *rev_col = nullptr;
         {
             DArray<uint32_t> ky(g->m, s), ky_alt(g->m, s);
-            k_rev_pairs<false><<<lgrid, B, 0, s>>>(g->row_off.get(), g->col.get(), n, long_f.get(), nlong,
-                                                   ky.get(), vx.get());
-            if (any_f)
-                k_rev_pairs<true><<<kLongGrid, B, 0, s>>>(g->row_off.get(), g->col.get(), n, long_f.get(), nlong,
-                                                          ky.get(), vx.get());
+            k_rev_pairs<<<tiles, B, 0, s>>>(g->row_off.get(), g->col.get(), n, g->m, first_f.get(), ky.get(), vx.get());
             PGABB_HIP(hipGetLastError());
             // pairs come in CSR order, ascending in x within each y, so a
             // stable sort on y orders them by (y, x)
@@ -779,25 +704,20 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
             (alt ? vx : vx_alt).release();
             scan_exclusive_i32(g->indeg.get(), rev_off.get(), n, rev_off.get() + n, s);
         }
-        if (any_r) k_collect_long<<<lgrid, B, 0, s>>>(rev_off.get(), n, long_r.get(), nlong + 1);
+        if (table) k_tile_first<<<fgrid, B, 0, s>>>(rev_off.get(), n, g->m, tiles, first_r.get());
         PGABB_HIP(hipGetLastError());
 
         // ---- block sizes, forward (entries, row items) and reversed (column items)
         unsigned long long *dnnz = dsz.get(), *dnnz_r = dnnz + pp, *dwalk = dsz.get() + 3 * pp;
         unsigned int *ditems = reinterpret_cast<unsigned int *>(dnnz_r + pp), *ditems_r = ditems + pp;
-        unsigned int *dmax = reinterpret_cast<unsigned int *>(dwalk + 1);
+        unsigned int *dmax = reinterpret_cast<unsigned int *>(dwalk + kWalkWords);
         unsigned int *drows = dmax + pp, *drows_r = drows + pp;
-        k_block_sizes<false><<<lgrid, B, 0, s>>>(g->row_off.get(), g->col.get(), n, ctp, long_f.get(), nlong,
-                                                  true, dnnz, ditems, drows, dwalk, dmax);
-        if (any_f)
-            k_block_sizes<true><<<kLongGrid, B, 0, s>>>(g->row_off.get(), g->col.get(), n, ctp, long_f.get(), nlong,
-                                                     true, dnnz, ditems, drows, dwalk, dmax);
-        k_block_sizes<false><<<lgrid, B, 0, s>>>(rev_off.get(), rev_col, n, ctp, long_r.get(), nlong + 1,
-                                                  false, dnnz_r, ditems_r, drows_r, nullptr, nullptr);
-        if (any_r)
-            k_block_sizes<true><<<kLongGrid, B, 0, s>>>(rev_off.get(), rev_col, n, ctp, long_r.get(),
-                                                     nlong + 1, false, dnnz_r, ditems_r, drows_r, nullptr,
-                                                     nullptr);
+        const unsigned sgrid = std::min(tiles, kSizesGrid);
+        const size_t slds = 4 * sizeof(unsigned int) * static_cast<size_t>(p) * (p + 1) / 2;
+        k_block_sizes<<<sgrid, B, slds, s>>>(g->row_off.get(), g->col.get(), n, g->m, first_f.get(), ctp, true, dnnz,
+                                             ditems, drows, dwalk, dmax);
+        k_block_sizes<<<sgrid, B, slds, s>>>(rev_off.get(), rev_col, n, g->m, first_r.get(), ctp, false, dnnz_r,
+                                             ditems_r, drows_r, nullptr, nullptr);
         PGABB_HIP(hipGetLastError());
         Staged<unsigned long long> hsz(nsz, s);
         PGABB_HIP(hipMemcpyAsync(hsz.get(), dsz.get(), hsz.bytes(), hipMemcpyDeviceToHost, s));
@@ -808,9 +728,9 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
         const unsigned long long *hnnz = hsz.get();
         const unsigned int *hitems = reinterpret_cast<const unsigned int *>(hsz.get() + 2 * pp);
         const unsigned int *hitems_r = hitems + pp;
-        const unsigned int *hmax = reinterpret_cast<const unsigned int *>(hsz.get() + 3 * pp + 1);
+        const unsigned int *hmax = reinterpret_cast<const unsigned int *>(hsz.get() + 3 * pp + kWalkWords);
         const unsigned int *hrows = hmax + pp, *hrows_r = hrows + pp;
-        g->probe_work_col = hsz[3 * pp];
+        for (int q = 0; q < kWalkWords; ++q) g->probe_work_col += hsz[3 * pp + q];
 
         // ---- block table (row-major block order) and chunk layout
         for (int32_t i = 0; i < p; ++i) {
@@ -854,18 +774,17 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
             const bool rev = pass == 1;
             const int64_t *off = rev ? rev_off.get() : g->row_off.get();
             const int32_t *cl = rev ? rev_col : g->col.get();
-            const int64_t *lst = rev ? long_r.get() : long_f.get();
-            const unsigned int *nl = nlong + (rev ? 1 : 0);
-            // layout: sb_pp[pp] sb_dense[nblk] rptr_off[nblk] items_off[nblk]
-            // col_off[nblk] | width[nblk] bidx[pp] (int32)
-            const size_t n64 = pp + 4 * static_cast<size_t>(nblk);
-            const size_t n32 = static_cast<size_t>(nblk) + pp;
+            const int32_t *first = rev ? first_r.get() : first_f.get();
+            // layout: sb_pp[pp] ro_pp[pp] co_pp[pp] (by stripe pair, of non-empty
+            // blocks) sb_dense[nblk] rptr_off[nblk] items_off[nblk] |
+            // width[nblk] (int32)
+            const size_t n64 = 3 * pp + 3 * static_cast<size_t>(nblk);
+            const size_t n32 = static_cast<size_t>(nblk);
             Staged<int64_t> tab(n64 + (n32 + 1) / 2, s);
-            int64_t *sb_pp = tab.get(), *sb_dense = sb_pp + pp, *rptr_off = sb_dense + nblk;
-            int64_t *items_off = rptr_off + nblk, *col_off = items_off + nblk;
-            int32_t *width = reinterpret_cast<int32_t *>(tab.get() + n64), *bidx = width + nblk;
-            std::fill(sb_pp, sb_pp + pp, int64_t(-1));
-            std::fill(bidx, bidx + pp, -1);
+            int64_t *sb_pp = tab.get(), *ro_pp = sb_pp + pp, *co_pp = ro_pp + pp;
+            int64_t *sb_dense = co_pp + pp, *rptr_off = sb_dense + nblk, *items_off = rptr_off + nblk;
+            int32_t *width = reinterpret_cast<int32_t *>(tab.get() + n64);
+            std::fill(sb_pp, sb_pp + 3 * pp, int64_t(-1));
             int64_t nslots = 0;
             for (int32_t b = 0; b < nblk; ++b) {
                 const BlockInfo &bi = g->blocks[b];
@@ -873,26 +792,23 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
                 // transpose, rows in stripe j, columns in stripe i
                 const size_t q = rev ? static_cast<size_t>(bi.j) * p + bi.i : static_cast<size_t>(bi.i) * p + bi.j;
                 sb_pp[q] = nslots;
-                bidx[q] = b;
                 sb_dense[b] = nslots;
                 width[b] = rev ? bi.cwidth : bi.width;
                 rptr_off[b] = rev ? coff[b] : bi.off_rptr();
                 items_off[b] = rev ? bi.off_citems() : bi.off_items();
-                col_off[b] = rev ? bi.off_crow() : bi.off_col();
+                ro_pp[q] = rptr_off[b];
+                co_pp[q] = rev ? bi.off_crow() : bi.off_col();
                 nslots += static_cast<int64_t>(width[b]) + 1;
             }
             DArray<int64_t> dtab(tab.size(), s);
             PGABB_HIP(hipMemcpyAsync(dtab.get(), tab.get(), tab.bytes(), hipMemcpyHostToDevice, s));
-            const int64_t *d_sb_pp = dtab.get(), *d_sb = d_sb_pp + pp, *d_ro = d_sb + nblk, *d_io = d_ro + nblk;
-            const int64_t *d_co = d_io + nblk;
-            const int32_t *d_w = reinterpret_cast<const int32_t *>(dtab.get() + n64), *d_bidx = d_w + nblk;
+            const int64_t *d_sb_pp = dtab.get(), *d_ro_pp = d_sb_pp + pp, *d_co_pp = d_ro_pp + pp;
+            const int64_t *d_sb = d_co_pp + pp, *d_ro = d_sb + nblk, *d_io = d_ro + nblk;
+            const int32_t *d_w = reinterpret_cast<const int32_t *>(dtab.get() + n64);
 
             DArray<uint32_t> slots(static_cast<size_t>(nslots) + 1, s), flags(static_cast<size_t>(nslots) + 1, s);
             PGABB_HIP(hipMemsetAsync(slots.get(), 0, (nslots + 1) * sizeof(uint32_t), s));
-            k_row_slot_counts<false><<<lgrid, B, 0, s>>>(off, cl, n, ctp, lst, nl, d_sb_pp, slots.get());
-            const bool any = rev ? any_r : any_f;
-            if (any)
-                k_row_slot_counts<true><<<kLongGrid, B, 0, s>>>(off, cl, n, ctp, lst, nl, d_sb_pp, slots.get());
+            k_row_slot_counts<<<tiles, B, 0, s>>>(off, cl, n, g->m, first, ctp, d_sb_pp, slots.get());
             PGABB_HIP(hipGetLastError());
             scan_exclusive_u32(slots.get(), slots.get(), nslots + 1, nullptr, s);
             const size_t lds = static_cast<size_t>(nblk) * sizeof(int64_t);
@@ -904,11 +820,7 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
             k_fill_items<<<cap_grid(nslots), B, lds, s>>>(flags.get(), slots.get(), nslots, d_sb, d_io, d_ro,
                                                           nblk, rbase, g->arena.get());
             PGABB_HIP(hipGetLastError());
-            k_fill_cols<false><<<lgrid, B, 0, s>>>(off, cl, n, ctp, lst, nl, d_bidx, d_ro, d_co, rbase,
-                                                   g->arena.get());
-            if (any)
-                k_fill_cols<true><<<kLongGrid, B, 0, s>>>(off, cl, n, ctp, lst, nl, d_bidx, d_ro, d_co, rbase,
-                                                      g->arena.get());
+            k_fill_cols<<<tiles, B, 0, s>>>(off, cl, n, g->m, first, ctp, d_ro_pp, d_co_pp, rbase, g->arena.get());
             PGABB_HIP(hipGetLastError());
         }
 

@@ -94,3 +94,38 @@ def test_endpoint_out_of_range_on_the_device():
         with pytest.raises(P.PgabbError) as e:
             P.Graph(5, s, d)
         assert e.value.status == P.EINVAL
+
+
+def spread(kind):
+    rng = np.random.default_rng(len(kind))
+    if kind == "stretch":  # 2 dense groups, some 50,000 empty rows between them
+        a, b = np.triu_indices(50, 1)
+        return 60000, np.concatenate([a, a + 50000]), np.concatenate([b, b + 50000])
+    if kind == "many":  # tiles of more rows than are marked: entries far apart
+        a = np.sort(rng.choice(300000, 3000, replace=False))
+        return 300100, np.concatenate([a, [3, 3, 7]]), np.concatenate([a + 1 + rng.integers(0, 90, 3000), [7, 9, 9]])
+    if kind == "star":  # one row over several tiles, runs that begin in earlier ones
+        t = rng.choice(np.arange(2, 30000), 9000, replace=False)
+        return 30000, np.concatenate([np.full(9000, 1), t[:4000]]), np.concatenate([t, t[1:4001]])
+    return 5000, rng.integers(0, 5000, 2048 * 6), rng.integers(0, 5000, 2048 * 6)
+
+
+@pytest.mark.parametrize("kind", ["stretch", "many", "star", "plain"])
+@pytest.mark.parametrize("order_by_id", [False, True])
+@pytest.mark.parametrize("p", [1, 2, 7, 64])
+def test_blocks_of_odd_rows(kind, order_by_id, p):
+    """Every triple of stripes counted by rows and by columns, with equal and
+    with nnz cuts."""
+    n, s, d = spread(kind)
+    s, d = s.astype(np.int32), d.astype(np.int32)
+    with P.Graph(n, s, d, order_by_id=order_by_id) as g:
+        row_off, col, _ = g.export_csr()
+        for mode in (P.CUT_NNZ, P.CUT_UNIFORM):
+            g.partition(p, cut_mode=mode)
+            B = oracle.block_counts(n, row_off, col, g.cuts())
+            for rows in (True, False):
+                assert g.count(by_rows=rows) == int(B.sum())
+                for (i, j, k), c in zip(*g.task_counts()):
+                    assert c == B[i, j, k]
+            want = oracle.probe_work_col(n, row_off, col, g.cuts())
+            assert g.info()["probe_work_col"] == want
