@@ -14,12 +14,10 @@
 
 #include "common.hpp"
 #include "graph.hpp"
+#include "radix.hpp"
 #include "wave.hpp"
 
 namespace pgabb {
-
-bool radix_sort_u64_bits(uint64_t *keys, uint64_t *keys_alt, uint32_t *vals, uint32_t *vals_alt,
-                         int64_t n, int lo_bit, int hi_bit, hipStream_t s);
 
 namespace {
 
@@ -32,10 +30,15 @@ constexpr int64_t kHiAtomics = 65536;
 // from L2); above they are scanned first.
 constexpr int64_t kUniqDirect = 16384;
 
-__global__ void k_make_keys(const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
-                            int64_t m, int32_t n, int nb, uint64_t *__restrict__ keys,
-                            uint32_t *__restrict__ bad) {
-    for (int64_t e = blockIdx.x * int64_t(B) + threadIdx.x; e < m; e += int64_t(gridDim.x) * B) {
+// Key of pair e, stored in keys; an endpoint out of range sets *bad and gives
+// the sentinel.
+struct PairKeys {
+    const int32_t *src, *dst;
+    int32_t n;
+    int nb;
+    uint64_t *keys;
+    uint32_t *bad;
+    __device__ __forceinline__ uint64_t operator()(int64_t e) const {
         const int32_t a = src[e], b = dst[e];
         uint64_t key = kSentinel;
         if (a < 0 || b < 0 || a >= n || b >= n) {
@@ -46,7 +49,13 @@ __global__ void k_make_keys(const int32_t *__restrict__ src, const int32_t *__re
             key = (lo << nb) | hi;
         }
         keys[e] = key;
+        return key;
     }
+};
+
+template <class Make>
+__global__ void k_make_one(Make make) {
+    make(0);
 }
 
 // Dedupe: a tile of UT keys per workgroup.  The first launch counts the keys
@@ -154,39 +163,53 @@ __global__ void k_degrees_hi(const uint32_t *__restrict__ his, int64_t m, int32_
     }
 }
 
-// The degrees (into deg), and with dk the sort's keys and values; without, the
-// ranks in id order.
-__global__ void k_deg_keys(const uint32_t *__restrict__ start, const uint32_t *__restrict__ end,
-                           const uint32_t *__restrict__ deg_hi, int32_t n, int32_t *__restrict__ deg,
-                           uint32_t *__restrict__ dk, uint32_t *__restrict__ dv, int32_t *__restrict__ rank) {
-    for (int64_t v = blockIdx.x * int64_t(B) + threadIdx.x; v < n; v += int64_t(gridDim.x) * B) {
+// Degree of vertex v, stored in deg.
+struct Degrees {
+    const uint32_t *start, *end, *deg_hi;
+    int32_t *deg;
+    __device__ __forceinline__ uint32_t operator()(int64_t v) const {
         const uint32_t d = end[v] - start[v] + deg_hi[v];
         deg[v] = static_cast<int32_t>(d);
-        if (dk) {
-            dk[v] = d;
-            dv[v] = static_cast<uint32_t>(v);
-        } else {
-            rank[v] = static_cast<int32_t>(v);
-        }
+        return d;
+    }
+};
+
+// The rank sort's keys and values.
+struct DegreeKeys {
+    Degrees degree;
+    uint32_t *dk, *dv;
+    __device__ __forceinline__ uint32_t operator()(int64_t v) const {
+        const uint32_t d = degree(v);
+        dk[v] = d;
+        dv[v] = static_cast<uint32_t>(v);
+        return d;
+    }
+};
+
+// The degrees, and ranks in id order.
+__global__ void k_degrees_by_id(Degrees degree, int32_t n, int32_t *__restrict__ rank) {
+    for (int64_t v = blockIdx.x * int64_t(B) + threadIdx.x; v < n; v += int64_t(gridDim.x) * B) {
+        degree(v);
+        rank[v] = static_cast<int32_t>(v);
     }
 }
 
-__global__ void k_invert(const uint32_t *__restrict__ perm, int32_t n, int32_t *__restrict__ rank) {
-    for (int64_t r = blockIdx.x * int64_t(B) + threadIdx.x; r < n; r += int64_t(gridDim.x) * B)
-        rank[perm[r]] = static_cast<int32_t>(r);
-}
-
-__global__ void k_orient(const uint64_t *__restrict__ ukeys, int64_t m, int nb,
-                         const int32_t *__restrict__ rank, uint64_t *__restrict__ okeys) {
-    const uint64_t mask = (1ull << nb) - 1;
-    for (int64_t e = blockIdx.x * int64_t(B) + threadIdx.x; e < m; e += int64_t(gridDim.x) * B) {
+// Key of distinct pair e by the ends' ranks.
+struct OrientedKeys {
+    const uint64_t *ukeys;
+    int nb;
+    const int32_t *rank;
+    uint64_t *okeys;
+    __device__ __forceinline__ uint64_t operator()(int64_t e) const {
         const uint64_t k = ukeys[e];
         const uint32_t ra = static_cast<uint32_t>(rank[k >> nb]);
-        const uint32_t rb = static_cast<uint32_t>(rank[k & mask]);
+        const uint32_t rb = static_cast<uint32_t>(rank[k & ((1ull << nb) - 1)]);
         const uint64_t lo = ra < rb ? ra : rb, hi = ra < rb ? rb : ra;
-        okeys[e] = (lo << nb) | hi;
+        const uint64_t key = (lo << nb) | hi;
+        okeys[e] = key;
+        return key;
     }
-}
+};
 
 __global__ void k_row_counts_and_cols(const uint64_t *__restrict__ okeys, int64_t m, int nb,
                                       int32_t *__restrict__ outdeg, int32_t *__restrict__ col) {
@@ -296,18 +319,20 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
     Stats *st = reinterpret_cast<Stats *>(zeroed.get());
     uint32_t *meta = zeroed.get() + kHead, *run_start = meta + 2, *run_end = run_start + n, *deg_hi = run_end + n;
 
+    const Degrees degrees{run_start, run_end, deg_hi, deg.get()};
     if (m > 0) {
         DArray<uint64_t> keys(static_cast<size_t>(m), s), alt(static_cast<size_t>(m), s);
         // Out-of-range edges get the sentinel key, so sorting and compacting
         // them is harmless and one round trip reports both words.
-        k_make_keys<<<cap_grid(m), B, 0, s>>>(src, dst, m, n, nb, keys.get(), meta);
-        PGABB_HIP(hipGetLastError());
+        const PairKeys pairs{src, dst, n, nb, keys.get(), meta};
 
         // 1-2: sort and dedupe.  Valid keys are below (n-1) << nb | (n-1) + 1;
         // the sentinel has every low 2nb bit set, so it sorts after them.
         const int kbits = 2 * nb;
         uint64_t *k0 = keys.get(), *k1 = alt.get();
-        if (radix_sort_u64_bits(k0, k1, nullptr, nullptr, m, 0, kbits, s)) std::swap(k0, k1);
+        if (m == 1) k_make_one<<<1, 1, 0, s>>>(pairs);
+        else if (radix_sort_made<uint64_t>(pairs, k0, k1, nullptr, nullptr, nullptr, m, 0, kbits, s)) std::swap(k0, k1);
+        PGABB_HIP(hipGetLastError());
         const uint64_t valid_limit = (static_cast<uint64_t>(n - 1) << nb) + static_cast<uint64_t>(n);
         DArray<uint32_t> his;
         if (m > kHiAtomics) his.reset(static_cast<size_t>(m), s);
@@ -345,25 +370,22 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
             PGABB_HIP(hipGetLastError());
         }
         // 4: degrees and ranks
-        if (g->flags & PGABB_ORDER_BY_ID) {
-            k_deg_keys<<<cap_grid(n), B, 0, s>>>(run_start, run_end, deg_hi, n, deg.get(), nullptr, nullptr,
-                                                 g->rank.get());
+        if ((g->flags & PGABB_ORDER_BY_ID) || n == 1) {
+            k_degrees_by_id<<<cap_grid(n), B, 0, s>>>(degrees, n, g->rank.get());
+            PGABB_HIP(hipGetLastError());
         } else {
             DArray<uint32_t> dk(n, s), dka(n, s), dv(n, s), dva(n, s);
-            k_deg_keys<<<cap_grid(n), B, 0, s>>>(run_start, run_end, deg_hi, n, deg.get(), dk.get(), dv.get(),
-                                                 nullptr);
-            PGABB_HIP(hipGetLastError());
-            uint32_t *perm = dv.get();
-            if (radix_sort_u32(dk.get(), dka.get(), dv.get(), dva.get(), n, nb, s)) perm = dva.get();
-            k_invert<<<cap_grid(n), B, 0, s>>>(perm, n, g->rank.get());
+            radix_sort_made<uint32_t>(DegreeKeys{degrees, dk.get(), dv.get()}, dk.get(), dka.get(), dv.get(), dva.get(),
+                                      g->rank.get(), n, 0, nb, s);
         }
-        PGABB_HIP(hipGetLastError());
 
         // 5: orient and sort by (row, col)
         if (mu > 0) {
-            k_orient<<<cap_grid(mu), B, 0, s>>>(k0, mu, nb, g->rank.get(), k1);
+            const OrientedKeys oriented{k0, nb, g->rank.get(), k1};
+            if (mu == 1) k_make_one<<<1, 1, 0, s>>>(oriented);
+            else if (radix_sort_made<uint64_t>(oriented, k1, k0, nullptr, nullptr, nullptr, mu, 0, kbits, s))
+                std::swap(k0, k1);
             PGABB_HIP(hipGetLastError());
-            if (radix_sort_u64_bits(k1, k0, nullptr, nullptr, mu, 0, kbits, s)) std::swap(k0, k1);
             // sorted oriented keys now in k1
             // (rows are read in segments, which may reach past the last one)
             g->col.reset(static_cast<size_t>(mu) + kSeg, s);
@@ -371,8 +393,7 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
             PGABB_HIP(hipGetLastError());
         }
     } else if (n > 0) {
-        k_deg_keys<<<cap_grid(n), B, 0, s>>>(run_start, run_end, deg_hi, n, deg.get(), nullptr, nullptr,
-                                             g->rank.get());  // every degree 0, ranks in id order
+        k_degrees_by_id<<<cap_grid(n), B, 0, s>>>(degrees, n, g->rank.get());  // every degree 0
         PGABB_HIP(hipGetLastError());
     }
     if (g->m == 0) g->col.release();

@@ -268,8 +268,16 @@ static uint64_t count_in_core(pgabb_graph *g, const pgabb_tc_options &opt) {
     const int orient = orient_of_option(opt, g);
     g->walked_columns = orient == kOrientCol;
     const int32_t T = static_cast<int32_t>(g->tasks.size());
-    Staged<TaskDesc> td(T, s);
-    Staged<int64_t> pre(static_cast<size_t>(T) + 1, s);
+    // one buffer, one copy: counts and queues (zero), the tasks' item prefix, the
+    // tasks (a copy and a clearing launch each cost a small graph as much as
+    // its counting kernel)
+    static_assert(sizeof(TaskDesc) % sizeof(int64_t) == 0 && alignof(TaskDesc) <= alignof(int64_t),
+                  "tasks follow 8-byte words");
+    const size_t ncnt = static_cast<size_t>(T) + kLaunchQueueWords, npre = static_cast<size_t>(T) + 1;
+    Staged<int64_t> args(ncnt + npre + T * (sizeof(TaskDesc) / sizeof(int64_t)), s);
+    std::fill(args.get(), args.get() + ncnt, int64_t(0));
+    int64_t *pre = args.get() + ncnt;
+    TaskDesc *td = reinterpret_cast<TaskDesc *>(pre + npre);
     pre[0] = 0;
     int32_t max_wk = 0, min_wk = INT32_MAX, max_st = 0;
     for (int32_t t = 0; t < T; ++t) {
@@ -279,20 +287,17 @@ static uint64_t count_in_core(pgabb_graph *g, const pgabb_tc_options &opt) {
         min_wk = std::min(min_wk, td[t].width_k);
         max_st = std::max(max_st, staged_max(g, g->tasks[t], orient));
     }
-    DArray<TaskDesc> dtd(T, s);
-    DArray<int64_t> dpre(static_cast<size_t>(T) + 1, s);
-    DArray<unsigned long long> dcnt(static_cast<size_t>(T) + kLaunchQueueWords, s);  // counts, then queues
-    PGABB_HIP(hipMemcpyAsync(dtd.get(), td.get(), td.bytes(), hipMemcpyHostToDevice, s));
-    PGABB_HIP(hipMemcpyAsync(dpre.get(), pre.get(), pre.bytes(), hipMemcpyHostToDevice, s));
-    PGABB_HIP(hipMemsetAsync(dcnt.get(), 0, sizeof(unsigned long long) * (T + kLaunchQueueWords), s));
+    DArray<int64_t> dargs(args.size(), s);
+    PGABB_HIP(hipMemcpyAsync(dargs.get(), args.get(), args.bytes(), hipMemcpyHostToDevice, s));
+    unsigned long long *dcnt = reinterpret_cast<unsigned long long *>(dargs.get());
 
     CountArgs a;
-    a.tasks = dtd.get();
-    a.item_pre = dpre.get();
+    a.tasks = reinterpret_cast<const TaskDesc *>(dargs.get() + ncnt + npre);
+    a.item_pre = dargs.get() + ncnt;
     a.ntasks = T;
     a.total = pre[T];
-    a.counts = dcnt.get();
-    a.next = dcnt.get() + T;
+    a.counts = dcnt;
+    a.next = dcnt + T;
     // walked entries of these tasks, at the graph's mean per item
     const uint64_t walked = static_cast<uint64_t>(static_cast<double>(walked_entries(g, orient)) * g->task_share);
     a.grab = opt.rows_per_grab > 0 ? opt.rows_per_grab : default_grab(pre[T], walked);
@@ -305,7 +310,7 @@ static uint64_t count_in_core(pgabb_graph *g, const pgabb_tc_options &opt) {
     tm.stop(s);
 
     Staged<unsigned long long> hcnt(T, s);
-    PGABB_HIP(hipMemcpyAsync(hcnt.get(), dcnt.get(), hcnt.bytes(), hipMemcpyDeviceToHost, s));
+    PGABB_HIP(hipMemcpyAsync(hcnt.get(), dcnt, hcnt.bytes(), hipMemcpyDeviceToHost, s));
     PGABB_HIP(hipStreamSynchronize(s));
     g->task_counts.assign(hcnt.get(), hcnt.get() + T);
     g->t_kernel_ms = tm.ms();

@@ -129,3 +129,11 @@ def test_blocks_of_odd_rows(kind, order_by_id, p):
                     assert c == B[i, j, k]
             want = oracle.probe_work_col(n, row_off, col, g.cuts())
             assert g.info()["probe_work_col"] == want
+
+
+@pytest.mark.parametrize("pairs", [[(0, 0)], [(0, 0), (0, 0)], [(0, 1)], [(1, 0), (0, 1), (1, 1)], [(2, 1), (1, 0)]])
+def test_fewest_pairs(pairs):
+    """Sorts of one key (made, not sorted), of none left after the loops, and
+    of one vertex."""
+    s, d = np.array(pairs, np.int32).T.copy()
+    check(int(max(s.max(), d.max())) + 1, s, d, ps=(1, 2))
