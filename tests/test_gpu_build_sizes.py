@@ -137,3 +137,14 @@ def test_fewest_pairs(pairs):
     of one vertex."""
     s, d = np.array(pairs, np.int32).T.copy()
     check(int(max(s.max(), d.max())) + 1, s, d, ps=(1, 2))
+
+
+@pytest.mark.parametrize("n", [2, 900, 8191, 8192, 8193, 300000])
+def test_high_ends(n):
+    """Counts of the high ends above 65,536 pairs: one value of the high bits,
+    several in a tile, one over many tiles (a third of the pairs end at the
+    last vertex)."""
+    m = 90001
+    s, d = pairs(n, m, n)
+    d[:m // 3] = n - 1
+    check(n, s, d, ps=(1,))
