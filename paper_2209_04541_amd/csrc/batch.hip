@@ -177,6 +177,9 @@ __global__ void k_union_csr_b(const uint64_t *__restrict__ okeys, int64_t m, int
     }
 }
 
+// Workgroups of a launch that ends in a counter of its own (see group_sum).
+constexpr unsigned kSumGrid = 1024;
+
 __global__ void k_active_flags_b(const uint32_t *__restrict__ outdeg, int64_t n,
                                  uint32_t *__restrict__ flag, int32_t *__restrict__ max_out) {
     int32_t mx = 0;
@@ -186,7 +189,7 @@ __global__ void k_active_flags_b(const uint32_t *__restrict__ outdeg, int64_t n,
     }
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) mx = max(mx, __shfl_xor(mx, d));
-    if (lane_id() == 0) atomicMax(max_out, mx);
+    if (lane_id() == 0 && mx > __atomic_load_n(max_out, __ATOMIC_RELAXED)) atomicMax(max_out, mx);
 }
 
 // Active rows and their graphs (one workgroup per graph).
@@ -216,9 +219,9 @@ __global__ void k_walked_b(const int32_t *__restrict__ rows, int64_t nactive, co
         }
         e += static_cast<unsigned long long>(rptr[u + 1] - rptr[u]);
     }
-    w = wave_sum(w);
-    e = wave_sum(e);
-    if (lane_id() == 0) {
+    w = group_sum(w);
+    e = group_sum(e);
+    if (threadIdx.x == 0) {
         if (w) atomicAdd(&out[0], w);
         if (e) atomicAdd(&out[1], e);
     }
@@ -633,7 +636,7 @@ void batch_build(pgabb_batch *b, const int32_t *n, const int64_t *eoff, const in
         DArray<int32_t> mx(1, s);
         PGABB_HIP(hipMemsetAsync(mx.get(), 0, sizeof(int32_t), s));
         PGABB_HIP(hipMemsetAsync(flag.get(), 0, sizeof(uint32_t) * (b->total_n + 1), s));
-        if (b->total_n) k_active_flags_b<<<cap_grid(b->total_n), B, 0, s>>>(outdeg.get(), b->total_n, flag.get(), mx.get());
+        if (b->total_n) k_active_flags_b<<<std::min(cap_grid(b->total_n), kSumGrid), B, 0, s>>>(outdeg.get(), b->total_n, flag.get(), mx.get());
         scan_exclusive_u32(flag.get(), pos.get(), b->total_n + 1, total.get(), s);
         uint32_t na = 0;
         PGABB_HIP(hipMemcpyAsync(&na, total.get(), sizeof(uint32_t), hipMemcpyDeviceToHost, s));
@@ -655,7 +658,7 @@ void batch_build(pgabb_batch *b, const int32_t *n, const int64_t *eoff, const in
                                      hipMemcpyDeviceToHost, s));
         DArray<unsigned long long> wk(2, s);
         k_zero_u64<<<1, B, 0, s>>>(wk.get(), 2);
-        if (na) k_walked_b<<<cap_grid(na), B, 0, s>>>(b->rows.get(), na, b->rptr.get(), b->col.get(), wk.get());
+        if (na) k_walked_b<<<std::min(cap_grid(na), kSumGrid), B, 0, s>>>(b->rows.get(), na, b->rptr.get(), b->col.get(), wk.get());
         PGABB_HIP(hipGetLastError());
         unsigned long long hw[2] = {0, 0};
         PGABB_HIP(hipMemcpyAsync(hw, wk.get(), sizeof hw, hipMemcpyDeviceToHost, s));

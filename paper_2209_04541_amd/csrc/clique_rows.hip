@@ -460,8 +460,8 @@ __global__ __launch_bounds__(kRowThreads) void k_quad_rows(RowArgs a) {
         }
     }
     if (!BLOCKS) {
-        const unsigned long long sum = wave_sum(acc);
-        if (lane == 0 && sum) atomicAdd(&a.counts[0], sum);
+        const unsigned long long sum = group_sum(acc);
+        if (threadIdx.x == 0 && sum) atomicAdd(&a.counts[0], sum);
         return;
     }
     __syncthreads();

@@ -382,8 +382,8 @@ void k_edge_support(const int64_t *__restrict__ row_off,
         wave_lds_sync();  // before the next unit is staged
         }
     }
-    found = wave_sum(found);
-    if (lane == 0 && found) atomicAdd(total, found);
+    found = group_sum(found);
+    if (threadIdx.x == 0 && found) atomicAdd(total, found);
 }
 
 }  // namespace

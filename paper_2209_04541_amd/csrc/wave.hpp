@@ -125,6 +125,21 @@ __device__ __forceinline__ T wave_sum(T x) {
     return x;
 }
 
+// Sum of v over the workgroup, returned to thread 0; every thread calls it.
+// Additions of all workgroups to one word serialise at 5 to 25 ns each, so a
+// workgroup adds once (edge support of R-MAT scale 14, one addition per wave 104
+// us, per workgroup 63).
+__device__ __forceinline__ unsigned long long group_sum(unsigned long long v) {
+    __shared__ unsigned long long s_part[1024 / kWave];
+    v = wave_sum(v);
+    __syncthreads();  // before a further sum's parts
+    if (lane_id() == 0) s_part[threadIdx.x / kWave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (unsigned q = 1; q < blockDim.x / kWave; ++q) v += s_part[q];
+    return v;
+}
+
 // For the 64 consecutive elements handled by one wave, where equal keys form
 // runs (the input is sorted), add each run's length to counter[key] with one
 // atomic from the run's first lane.  `valid` lanes must form a prefix.
