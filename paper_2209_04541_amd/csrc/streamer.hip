@@ -27,9 +27,10 @@
 // A graph partitioned on the device reaches its first streamed count with
 // the blocks still in the device arena.  Outside the hybrid mode the count
 // moves them to the host store itself, on the graph's stream: first the
-// pieces of the arena that the first tasks use, a little ahead of the window
-// that reads them, then the others.  Each block's copy back waits
-// only for its piece, so the first windows start after a small part
+// part of each block its walk reads, block by block in the order the tasks
+// first use them, a little ahead of the window that reads it, then the rest
+// of the arena.  Each block's copy back waits
+// only for that block's move, so the first windows start after a small part
 // of the store has crossed and the moves overlap the copies back (the other
 // direction of the link) and the launches.  The arena is released once the
 // count ends, leaving the same host store as a move before the count.
@@ -62,17 +63,9 @@ constexpr int kCopyStreams = 2;
 // copied back.
 constexpr uint64_t kMovesAhead = 8ull << 20;
 
-// Blocks move to the host store in pieces of at least this much: moves and the
-// copies' waits for them cost some 10 us each, more than the bytes of the
-// blocks of a small graph.
-constexpr uint64_t kPieceBytes = 2ull << 20;
-
-// Under a cap below the blocks' bytes a window copies at least this much before
-// it is cut: some 150 us of the link, about what its launches take.  When all
-// blocks fit, smaller windows only cost launches: 60 MB of a graph in space cut
-// 20 x 20 counted in windows of 8 / 32 / 64 MB: 7.4 / 5.1 / 3.8 ms.
+// A window copies at least this much before it is cut: some 150 us of the
+// link, about what its launches take.
 constexpr uint64_t kMinWindowBytes = 8ull << 20;
-constexpr uint64_t kMinFittingBytes = 64ull << 20;
 
 // Bytes of the part of a block's chunk that a walk in `orient` reads (the
 // unit of copy and of pool space), rounded up to kAlign.
@@ -257,8 +250,7 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
     // device claims work in steps small enough for the two sides to meet
     // near the balance point
     const int window_tasks = hybrid ? std::max(1, T / 32) : T;
-    const uint64_t window_new_bytes =
-        std::max<uint64_t>(total_bytes <= cap ? kMinFittingBytes : kMinWindowBytes, cap / 8);
+    const uint64_t window_new_bytes = std::max<uint64_t>(kMinWindowBytes, cap / 8);
     const uint64_t window_bytes = total_bytes <= cap ? cap : std::max<uint64_t>(kMinWindowBytes, cap / 4 * 3);
 
     std::vector<int64_t> chunk_dev(nblk, 0);  // in int32 words from pool start
@@ -278,47 +270,40 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
             if (uses[b].empty() || uses[b].back() != q) uses[b].push_back(q);
     }
 
-    // ---- the move to the host store, in pieces of whole blocks that lie next to
-    // each other in the arena, in the order that the tasks first use them
-    // (moved marks a piece's end), queued kMovesAhead ahead of the window that
-    // reads them; then the pieces that are left.  (The streams share the
-    // device's few hardware queues, and a launch waits for what its queue
-    // holds: with all moves queued before the first window, no window ran until
-    // the last move had ended, 26.3 ms for a first count of R-MAT scale 21
-    // under 160 MiB; 32 MB ahead 25 to 30 ms, 8 MB 21.1.)
-    struct Piece {
-        int64_t lo, hi;           // words of the arena
-        hipEvent_t moved;
-        int32_t pos;              // place among the moves
-    };
-    std::vector<Piece> pieces;
-    std::vector<int32_t> piece_of(nblk, 0);
-    for (int32_t b = 0; moving && b < nblk; ++b) {  // (blocks lie in the order of their numbers)
-        const BlockInfo &bi = g->blocks[b];
-        if (pieces.empty() || (pieces.back().hi - pieces.back().lo) * sizeof(int32_t) >= kPieceBytes)
-            pieces.push_back({bi.chunk_off, bi.chunk_off, nullptr, 0});
-        pieces.back().hi = bi.chunk_off + bi.chunk_len;
-        piece_of[b] = static_cast<int32_t>(pieces.size()) - 1;
-    }
-    int32_t moves = 0, moved_tasks = 0;          // pieces queued; position in `order` up to which they are
+    // ---- the move to the host store: the walked part of every block's chunk
+    // in order of first use (moved[b] marks its end), queued kMovesAhead ahead
+    // of the window that reads it, then the arena's other words.  (The streams
+    // share the device's few hardware queues, and a launch waits for what its
+    // queue holds: with all moves queued before the first window, no window
+    // ran until the last move had ended, 26.3 ms for a first count of R-MAT
+    // scale 21 under 160 MiB; 32 MB ahead 25 to 30 ms, 8 MB 21.1.)
+    std::vector<hipEvent_t> moved(nblk, nullptr);
+    std::vector<int32_t> move_pos(nblk, 0);      // place of the block among the moves
+    int32_t moves = 0, moved_tasks = 0;          // blocks queued; position in `order` up to which they are
     uint64_t move_bytes = 0;
     int32_t moved_to[kCopyStreams];              // moves that each copy stream waits for
     std::fill(std::begin(moved_to), std::end(moved_to), -1);
     auto end_moves = [&]() noexcept {
         (void)hipStreamSynchronize(s);
-        for (Piece &p : pieces) {
-            if (p.moved) (void)hipEventDestroy(p.moved);
-            p.moved = nullptr;
+        for (auto &e : moved) {
+            if (e) (void)hipEventDestroy(e);
+            e = nullptr;
         }
     };
-    auto move_piece = [&](Piece &p) {
-        if (p.moved) return;
-        const size_t bytes = sizeof(int32_t) * static_cast<size_t>(p.hi - p.lo);
-        PGABB_HIP(hipMemcpyAsync(g->host_arena.get() + p.lo, g->arena.get() + p.lo, bytes, hipMemcpyDeviceToHost, s));
-        PGABB_HIP(hipEventCreateWithFlags(&p.moved, hipEventDisableTiming));
-        PGABB_HIP(hipEventRecord(p.moved, s));
-        p.pos = moves++;
-        move_bytes += bytes;
+
+    auto move_words = [&](int64_t lo, int64_t hi) {
+        if (hi > lo)
+            PGABB_HIP(hipMemcpyAsync(g->host_arena.get() + lo, g->arena.get() + lo,
+                                     sizeof(int32_t) * static_cast<size_t>(hi - lo), hipMemcpyDeviceToHost, s));
+    };
+    // the part of the chunk that this count's walk reads
+    auto move_block = [&](int32_t b) {
+        if (moved[b]) return;
+        move_words(g->blocks[b].walk_lo(orient), g->blocks[b].walk_hi(orient));
+        PGABB_HIP(hipEventCreateWithFlags(&moved[b], hipEventDisableTiming));
+        PGABB_HIP(hipEventRecord(moved[b], s));
+        move_pos[b] = moves++;
+        move_bytes += chunk_bytes(g->blocks[b], orient);
     };
     // the blocks of the tasks before `end`, then those of the tasks after them
     // until kMovesAhead more bytes are queued
@@ -327,8 +312,21 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
         while (moved_tasks < T && move_bytes < until) {
             if (moved_tasks >= end && until == UINT64_MAX) until = move_bytes + kMovesAhead;
             const Task &t = g->tasks[order[moved_tasks++]];
-            for (int32_t b : {t.bij, t.bik, t.bjk}) move_piece(pieces[piece_of[b]]);
+            for (int32_t b : {t.bij, t.bik, t.bjk}) move_block(b);
         }
+    };
+    // every block and word that is left
+    auto move_rest = [&]() {
+        for (int32_t b = 0; b < nblk; ++b) move_block(b);
+        std::vector<std::pair<int64_t, int64_t>> walked;
+        for (const BlockInfo &bi : g->blocks) walked.emplace_back(bi.walk_lo(orient), bi.walk_hi(orient));
+        std::sort(walked.begin(), walked.end());
+        int64_t at = 0;
+        for (const auto &c : walked) {
+            move_words(at, c.first);
+            at = std::max(at, c.second);
+        }
+        move_words(at, g->arena_words);
     };
 
     uint64_t h2d = 0;
@@ -527,9 +525,9 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
                 const BlockInfo &bi = g->blocks[loads[q]];
                 hipStream_t x = copy_s[q % kCopyStreams];
                 const size_t bytes = static_cast<size_t>(bi.walk_hi(orient) - bi.walk_lo(orient)) * sizeof(int32_t);
-                if (moving && pieces[piece_of[loads[q]]].pos > moved_to[q % kCopyStreams]) {
-                    PGABB_HIP(hipStreamWaitEvent(x, pieces[piece_of[loads[q]]].moved, 0));
-                    moved_to[q % kCopyStreams] = pieces[piece_of[loads[q]]].pos;
+                if (moving && move_pos[loads[q]] > moved_to[q % kCopyStreams]) {
+                    PGABB_HIP(hipStreamWaitEvent(x, moved[loads[q]], 0));
+                    moved_to[q % kCopyStreams] = move_pos[loads[q]];
                 }
                 PGABB_HIP(hipMemcpyAsync(pool.get() + where[loads[q]], g->host_arena.get() + bi.walk_lo(orient), bytes,
                                          hipMemcpyHostToDevice, x));
@@ -596,8 +594,7 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
             ++win;
         }
         for (auto &th : host) th.join();
-        if (moving)
-            for (Piece &p : pieces) move_piece(p);
+        if (moving) move_rest();
         for (auto x : cs) PGABB_HIP(hipStreamSynchronize(x));
         for (auto x : copy_s) PGABB_HIP(hipStreamSynchronize(x));
         if (moving) {
