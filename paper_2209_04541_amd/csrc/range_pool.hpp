@@ -1,5 +1,5 @@
-// First-fit allocator of byte ranges of a device pool (the block cache of the
-// streamed 4-clique count).
+// First-fit allocator of byte ranges of a device pool (the block caches of
+// the streamed counts).
 #pragma once
 
 #include <cstdint>

@@ -6,9 +6,9 @@
 // several streams let the copy of the next assignment overlap the current
 // computation.  Instead of waiting for all tasks and clearing the device
 // when memory runs low, this keeps a block cache: a device pool of at most
-// `device_cap_bytes` in which the blocks needed furthest ahead make room (see
-// BlockPool); the copies into a range wait on the device for every stream's
-// last window that read it.
+// `device_cap_bytes` managed first-fit, with least-recently-used eviction of
+// blocks that no in-flight task still reads (every stream's last window that
+// read a block has finished before its range is reused).
 //
 // Tasks are taken in the heaviest-first order and grouped into windows of a
 // few tasks whose blocks are resident together.  In the hybrid mode host
@@ -16,20 +16,16 @@
 // from the host store, while the device takes windows from the heavy end
 // (Section 4.4: heavy tasks to the GPU, light ones to CPU threads, all
 // pulled from one task queue).  For each window the missing
-// blocks are copied on two copy streams; the window's counting launch runs on
+// blocks are copied on a copy stream; the window's counting launch runs on
 // one of several compute streams once its copies are done; windows on
 // different streams overlap, and the copies of later windows overlap earlier
-// launches.  The link is what bounds a count under a cap, so windows are
-// small, their blocks chosen for few copies, and the host waits for nothing
-// between them: R-MAT scale 21 cut 16 x 16 under 160 MiB copies 533 MB instead
-// of 1052 and takes 15.5 instead of 30.3 ms.
+// launches.
 //
 // A graph partitioned on the device reaches its first streamed count with
 // the blocks still in the device arena.  Outside the hybrid mode the count
-// moves them to the host store itself, on the graph's stream: first the
+// moves them to the host store itself, on a stream of its own: first the
 // part of each block its walk reads, block by block in the order the tasks
-// first use them, a little ahead of the window that reads it, then the rest
-// of the arena.  Each block's copy back waits
+// first use them, then the rest of the arena.  Each block's copy back waits
 // only for that block's move, so the first windows start after a small part
 // of the store has crossed and the moves overlap the copies back (the other
 // direction of the link) and the launches.  The arena is released once the
@@ -41,8 +37,8 @@
 #include <mutex>
 #include <thread>
 
-#include "block_pool.hpp"
 #include "block_readers.hpp"
+#include "range_pool.hpp"
 #include "common.hpp"
 #include "count.hpp"
 #include "graph.hpp"
@@ -53,19 +49,6 @@ namespace pgabb {
 namespace {
 
 constexpr uint64_t kAlign = 256;
-
-// Copies alternate between this many streams: one copy's start-up hides behind
-// the other's bytes (copies of 2 MB on 1 / 2 / 4 streams: 45.4 / 55.1 / 56.5
-// GB/s; with more than two, copies the other way lose more than that gains).
-constexpr int kCopyStreams = 2;
-
-// Bytes of moves to the host store that are queued ahead of the window being
-// copied back.
-constexpr uint64_t kMovesAhead = 8ull << 20;
-
-// A window copies at least this much before it is cut: some 150 us of the
-// link, about what its launches take.
-constexpr uint64_t kMinWindowBytes = 8ull << 20;
 
 // Bytes of the part of a block's chunk that a walk in `orient` reads (the
 // unit of copy and of pool space), rounded up to kAlign.
@@ -95,10 +78,7 @@ void move_blocks_to_host(pgabb_graph *g) {
 // next task is always one whose blocks are missing the fewest bytes from
 // it, the heaviest among equals.  Heaviest-first alone reloads blocks many
 // times once the cache holds a small share of them; this order keeps the
-// tasks that share blocks together.  It starts among the smallest
-// blocks and grows to the largest, so it is taken backwards: the heavy windows
-// come first and the tail is short (R-MAT scale 21 cut 16 x 16 under 160 MiB
-// 15.5 ms, forwards 17.2).  O(T^2) on the host, with per-task
+// tasks that share blocks together.  O(T^2) on the host, with per-task
 // missing bytes updated as blocks enter and leave.
 std::vector<int32_t> locality_order(const pgabb_graph *g, uint64_t cap, int orient) {
     const int32_t T = static_cast<int32_t>(g->tasks.size());
@@ -160,7 +140,6 @@ std::vector<int32_t> locality_order(const pgabb_graph *g, uint64_t cap, int orie
             enter(b);
         }
     }
-    std::reverse(order.begin(), order.end());
     return order;
 }
 
@@ -200,9 +179,9 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
 
     const int nstreams = opt.num_streams > 0 ? std::min(opt.num_streams, 16) : 4;
     std::vector<hipStream_t> cs(nstreams);
-    hipStream_t copy_s[kCopyStreams] = {};
+    hipStream_t copy_s = nullptr;
+    PGABB_HIP(hipStreamCreateWithFlags(&copy_s, hipStreamNonBlocking));
     for (auto &x : cs) PGABB_HIP(hipStreamCreateWithFlags(&x, hipStreamNonBlocking));
-    for (auto &x : copy_s) PGABB_HIP(hipStreamCreateWithFlags(&x, hipStreamNonBlocking));
 
     // device pool and per-run arrays
     // (walked lists are read in segments, which may reach past the last list)
@@ -219,14 +198,13 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
     hpre.reset(static_cast<size_t>(2 * T + 1));
     PGABB_HIP(hipStreamSynchronize(s));
 
-    BlockPool bp(cap);
+    RangePool rp(cap);
     std::vector<uint64_t> where(nblk, UINT64_MAX);   // pool offset of resident blocks
     BlockReaders readers(nblk, nstreams);            // windows per stream that read each block
-    // per compute stream: the last window that read a block evicted so far,
-    // and the last one that the copy streams wait for
-    std::vector<int32_t> last_reader(nstreams, -1), awaited(nstreams, -1);
+    std::list<int32_t> lru;                           // resident blocks, least recent first
+    std::vector<std::list<int32_t>::iterator> lru_pos(nblk);
     std::vector<hipEvent_t> done;                     // per window
-    std::vector<hipEvent_t> copied;                   // per window and copy stream
+    std::vector<hipEvent_t> copied;
     std::vector<hipEvent_t> kstart, kstop;            // per window launch timing
 
     int32_t max_wk = 0, min_wk = INT32_MAX;
@@ -241,17 +219,14 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
     g->walked_columns = orient == kOrientCol;
     const int waves = opt.waves_per_block > 0 ? opt.waves_per_block : 4;
     const int grab_opt = opt.rows_per_grab;
-    // A window is cut when its blocks would take more than three quarters of
-    // the pool (what is left can take the next window's while it is counted,
-    // and without it the blocks of one window alone scatter the room) or when
-    // it would copy more than an eighth: the first launch starts after a
-    // short copy, and later copies overlap earlier launches.
+    // A window is cut when its blocks would exceed the cap or when it would
+    // copy more than about an eighth of all block bytes: the first launch
+    // starts after a short copy, and later copies overlap earlier launches.
     // in the hybrid mode windows hold at most 1/32 of the tasks, so the
     // device claims work in steps small enough for the two sides to meet
     // near the balance point
     const int window_tasks = hybrid ? std::max(1, T / 32) : T;
-    const uint64_t window_new_bytes = std::max<uint64_t>(kMinWindowBytes, cap / 8);
-    const uint64_t window_bytes = total_bytes <= cap ? cap : std::max<uint64_t>(kMinWindowBytes, cap / 4 * 3);
+    const uint64_t window_new_bytes = std::max<uint64_t>(64ull << 20, std::min<uint64_t>(cap / 4, total_bytes / 8));
 
     std::vector<int64_t> chunk_dev(nblk, 0);  // in int32 words from pool start
     // processing order of the tasks: heaviest first when every block fits
@@ -259,74 +234,23 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
     std::vector<int32_t> order(T);
     for (int32_t t = 0; t < T; ++t) order[t] = t;
     if (total_bytes > cap) order = locality_order(g, cap, orient);
-    // positions in `order` that read each block, and the first not passed
-    std::vector<std::vector<int32_t>> uses(nblk);
-    std::vector<size_t> next_use(nblk, 0);
-    std::vector<int32_t> last_window(nblk, -1);  // that read the block
-    const double wait_cost = 0.03 * static_cast<double>(total_bytes) / std::max(nblk, 1);
-    for (int32_t q = 0; q < T; ++q) {
-        const Task &t = g->tasks[order[q]];
-        for (int32_t b : {t.bij, t.bik, t.bjk})
-            if (uses[b].empty() || uses[b].back() != q) uses[b].push_back(q);
-    }
 
-    // ---- the move to the host store: the walked part of every block's chunk
-    // in order of first use (moved[b] marks its end), queued kMovesAhead ahead
-    // of the window that reads it, then the arena's other words.  (The streams
-    // share the device's few hardware queues, and a launch waits for what its
-    // queue holds: with all moves queued before the first window, no window
-    // ran until the last move had ended, 26.3 ms for a first count of R-MAT
-    // scale 21 under 160 MiB; 32 MB ahead 25 to 30 ms, 8 MB 21.1.)
+    // ---- the move to the host store, queued in full before the first
+    // window: the walked part of every block's chunk in order of first use
+    // (moved[b] marks its end), then the arena's other words
+    hipStream_t move_s = nullptr;
+    hipEvent_t arena_ready = nullptr;
     std::vector<hipEvent_t> moved(nblk, nullptr);
-    std::vector<int32_t> move_pos(nblk, 0);      // place of the block among the moves
-    int32_t moves = 0, moved_tasks = 0;          // blocks queued; position in `order` up to which they are
-    uint64_t move_bytes = 0;
-    int32_t moved_to[kCopyStreams];              // moves that each copy stream waits for
-    std::fill(std::begin(moved_to), std::end(moved_to), -1);
     auto end_moves = [&]() noexcept {
-        (void)hipStreamSynchronize(s);
+        if (move_s) (void)hipStreamSynchronize(move_s);
         for (auto &e : moved) {
             if (e) (void)hipEventDestroy(e);
             e = nullptr;
         }
-    };
-
-    auto move_words = [&](int64_t lo, int64_t hi) {
-        if (hi > lo)
-            PGABB_HIP(hipMemcpyAsync(g->host_arena.get() + lo, g->arena.get() + lo,
-                                     sizeof(int32_t) * static_cast<size_t>(hi - lo), hipMemcpyDeviceToHost, s));
-    };
-    // the part of the chunk that this count's walk reads
-    auto move_block = [&](int32_t b) {
-        if (moved[b]) return;
-        move_words(g->blocks[b].walk_lo(orient), g->blocks[b].walk_hi(orient));
-        PGABB_HIP(hipEventCreateWithFlags(&moved[b], hipEventDisableTiming));
-        PGABB_HIP(hipEventRecord(moved[b], s));
-        move_pos[b] = moves++;
-        move_bytes += chunk_bytes(g->blocks[b], orient);
-    };
-    // the blocks of the tasks before `end`, then those of the tasks after them
-    // until kMovesAhead more bytes are queued
-    auto move_tasks = [&](int32_t end) {
-        uint64_t until = UINT64_MAX;
-        while (moved_tasks < T && move_bytes < until) {
-            if (moved_tasks >= end && until == UINT64_MAX) until = move_bytes + kMovesAhead;
-            const Task &t = g->tasks[order[moved_tasks++]];
-            for (int32_t b : {t.bij, t.bik, t.bjk}) move_block(b);
-        }
-    };
-    // every block and word that is left
-    auto move_rest = [&]() {
-        for (int32_t b = 0; b < nblk; ++b) move_block(b);
-        std::vector<std::pair<int64_t, int64_t>> walked;
-        for (const BlockInfo &bi : g->blocks) walked.emplace_back(bi.walk_lo(orient), bi.walk_hi(orient));
-        std::sort(walked.begin(), walked.end());
-        int64_t at = 0;
-        for (const auto &c : walked) {
-            move_words(at, c.first);
-            at = std::max(at, c.second);
-        }
-        move_words(at, g->arena_words);
+        if (arena_ready) (void)hipEventDestroy(arena_ready);
+        if (move_s) (void)hipStreamDestroy(move_s);
+        move_s = nullptr;
+        arena_ready = nullptr;
     };
 
     uint64_t h2d = 0;
@@ -413,8 +337,48 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
             if (th.joinable()) th.join();
     };
 
+    auto touch = [&](int32_t b) {
+        lru.erase(lru_pos[b]);
+        lru.push_back(b);
+        lru_pos[b] = std::prev(lru.end());
+    };
+
     try {
-        if (moving) g->host_arena.reset(static_cast<size_t>(g->arena_words), s, true);
+        if (moving) {
+            g->host_arena.reset(static_cast<size_t>(g->arena_words), s, true);
+            PGABB_HIP(hipStreamCreateWithFlags(&move_s, hipStreamNonBlocking));
+            PGABB_HIP(hipEventCreateWithFlags(&arena_ready, hipEventDisableTiming));
+            PGABB_HIP(hipEventRecord(arena_ready, s));  // the arena was written on the graph's stream
+            PGABB_HIP(hipStreamWaitEvent(move_s, arena_ready, 0));
+            int32_t *harena = g->host_arena.get();
+            const int32_t *darena = g->arena.get();
+            auto move_words = [&](int64_t lo, int64_t hi) {
+                if (hi > lo)
+                    PGABB_HIP(hipMemcpyAsync(harena + lo, darena + lo, sizeof(int32_t) * static_cast<size_t>(hi - lo),
+                                             hipMemcpyDeviceToHost, move_s));
+            };
+            // the part of the chunk this count's walk reads comes first
+            auto move_block = [&](int32_t b) {
+                if (moved[b]) return;
+                move_words(g->blocks[b].walk_lo(orient), g->blocks[b].walk_hi(orient));
+                PGABB_HIP(hipEventCreateWithFlags(&moved[b], hipEventDisableTiming));
+                PGABB_HIP(hipEventRecord(moved[b], move_s));
+            };
+            for (int32_t q = 0; q < T; ++q)
+                for (int32_t b : {g->tasks[order[q]].bij, g->tasks[order[q]].bik, g->tasks[order[q]].bjk})
+                    move_block(b);
+            for (int32_t b = 0; b < nblk; ++b) move_block(b);
+            // then every word outside the walked parts
+            std::vector<std::pair<int64_t, int64_t>> walked;
+            for (const BlockInfo &bi : g->blocks) walked.emplace_back(bi.walk_lo(orient), bi.walk_hi(orient));
+            std::sort(walked.begin(), walked.end());
+            int64_t at = 0;
+            for (const auto &c : walked) {
+                move_words(at, c.first);
+                at = std::max(at, c.second);
+            }
+            move_words(at, g->arena_words);
+        }
         for (;;) {
             // in the hybrid mode at most one window per stream is in flight,
             // so the device claims tasks only as fast as it counts them
@@ -448,8 +412,7 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
                     add += chunk_bytes(g->blocks[b], orient);
                     if (where[b] == UINT64_MAX) add_new += chunk_bytes(g->blocks[b], orient);
                 }
-                if (!wtasks.empty() && (pinned_bytes + add > std::min(cap, window_bytes) ||
-                                        new_bytes + add_new > window_new_bytes))
+                if (!wtasks.empty() && (pinned_bytes + add > cap || new_bytes + add_new > window_new_bytes))
                     break;
                 for (int32_t b : {t.bij, t.bik, t.bjk}) in_window[b] = 1;
                 pinned_bytes += add;
@@ -458,84 +421,75 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
             }
             qlk.unlock();
 
-            // ---- make the window's blocks resident.  If a block fits nowhere
-            // between the window's own (the pool is fragmented), wait for all
-            // in-flight work, empty the cache and place the window again into
-            // the empty pool, where it fits.
+            // ---- make the window's blocks resident.  If first-fit cannot place
+            // a block even with every block outside the window evicted (the pool
+            // is fragmented), wait for all in-flight work, empty the cache and
+            // place the window again into the empty pool, where it fits.
             std::vector<int32_t> loads;
-            size_t early = SIZE_MAX;  // loads before the first that takes room not yet waited for
-            auto in_use = [&](int32_t v) { return in_window[v] != 0; };
-            // copying v again, spread over the tasks until its next use; a block
-            // that the last window reads makes the copies wait for its count
-            auto cost = [&](int32_t v) {
-                size_t &q = next_use[v];
-                while (q < uses[v].size() && uses[v][q] < next_task) ++q;
-                const double again = q < uses[v].size() ? static_cast<double>(chunk_bytes(g->blocks[v], orient)) /
-                                                              (uses[v][q] - next_task + 1)
-                                                        : 0;
-                return again + (last_window[v] == win - 1 ? wait_cost : 0);
-            };
-            auto evict = [&](int32_t v) {
-                readers.release(v, [&](int32_t w) {
-                    last_reader[w % nstreams] = std::max(last_reader[w % nstreams], w);
-                    if (w > awaited[w % nstreams]) early = std::min(early, loads.size());
-                });
-                where[v] = UINT64_MAX;
-            };
             bool placed = false;
             for (int attempt = 0; attempt < 2 && !placed; ++attempt) {
                 loads.clear();
-                early = SIZE_MAX;
                 placed = true;
                 for (int32_t ti : wtasks) {
                     for (int32_t b : {g->tasks[ti].bij, g->tasks[ti].bik, g->tasks[ti].bjk}) {
-                        if (where[b] != UINT64_MAX) continue;
-                        where[b] = bp.place(b, chunk_bytes(g->blocks[b], orient), in_use, cost, evict);
-                        if (where[b] == UINT64_MAX) {
+                        if (where[b] != UINT64_MAX) {
+                            touch(b);
+                            continue;
+                        }
+                        const uint64_t need = chunk_bytes(g->blocks[b], orient);
+                        uint64_t off = rp.alloc(need);
+                        while (off == UINT64_MAX) {
+                            auto it = lru.begin();
+                            while (it != lru.end() && in_window[*it]) ++it;
+                            if (it == lru.end()) break;
+                            const int32_t v = *it;
+                            readers.release(v, [&](int32_t w) { PGABB_HIP(hipEventSynchronize(done[w])); });
+                            rp.release(where[v], chunk_bytes(g->blocks[v], orient));
+                            where[v] = UINT64_MAX;
+                            lru.erase(it);
+                            off = rp.alloc(need);
+                        }
+                        if (off == UINT64_MAX) {
                             placed = false;
                             break;
                         }
+                        where[b] = off;
                         // the chunk's start, in words from the pool's start, as if the
                         // whole chunk were there: only [walk_lo, walk_hi) is copied
                         // and read
-                        chunk_dev[b] = static_cast<int64_t>(where[b] / sizeof(int32_t)) -
+                        chunk_dev[b] = static_cast<int64_t>(off / sizeof(int32_t)) -
                                        (g->blocks[b].walk_lo(orient) - g->blocks[b].chunk_off);
+                        lru.push_back(b);
+                        lru_pos[b] = std::prev(lru.end());
                         loads.push_back(b);
                     }
                     if (!placed) break;
                 }
                 if (!placed) {
                     for (auto x : cs) PGABB_HIP(hipStreamSynchronize(x));
-                    for (auto x : copy_s) PGABB_HIP(hipStreamSynchronize(x));
-                    std::fill(where.begin(), where.end(), UINT64_MAX);
+                    PGABB_HIP(hipStreamSynchronize(copy_s));
+                    for (int32_t v : lru) where[v] = UINT64_MAX;
+                    lru.clear();
                     readers.clear();
-                    bp.clear();
+                    rp = RangePool(cap);
                 }
             }
             PGABB_REQUIRE(placed, PGABB_ENOMEM, "device cap of %llu bytes cannot hold a window",
                           static_cast<unsigned long long>(cap));
-            if (moving) move_tasks(next_task);
-            for (size_t q = 0; q < loads.size(); ++q) {
-                // (a stream's windows finish in order: one wait covers its earlier ones)
-                for (int si = 0; q == early && si < nstreams; ++si) {
-                    if (last_reader[si] <= awaited[si]) continue;
-                    for (auto x : copy_s) PGABB_HIP(hipStreamWaitEvent(x, done[last_reader[si]], 0));
-                    awaited[si] = last_reader[si];
-                }
-                const BlockInfo &bi = g->blocks[loads[q]];
-                hipStream_t x = copy_s[q % kCopyStreams];
+            for (int32_t b : loads) {
+                const BlockInfo &bi = g->blocks[b];
                 const size_t bytes = static_cast<size_t>(bi.walk_hi(orient) - bi.walk_lo(orient)) * sizeof(int32_t);
-                if (moving && move_pos[loads[q]] > moved_to[q % kCopyStreams]) {
-                    PGABB_HIP(hipStreamWaitEvent(x, moved[loads[q]], 0));
-                    moved_to[q % kCopyStreams] = move_pos[loads[q]];
-                }
-                PGABB_HIP(hipMemcpyAsync(pool.get() + where[loads[q]], g->host_arena.get() + bi.walk_lo(orient), bytes,
-                                         hipMemcpyHostToDevice, x));
+                if (moving) PGABB_HIP(hipStreamWaitEvent(copy_s, moved[b], 0));
+                PGABB_HIP(hipMemcpyAsync(pool.get() + where[b], g->host_arena.get() + bi.walk_lo(orient), bytes,
+                                         hipMemcpyHostToDevice, copy_s));
                 h2d += bytes;
             }
-            hipEvent_t de = nullptr;
+            hipEvent_t ce = nullptr, de = nullptr;
+            PGABB_HIP(hipEventCreateWithFlags(&ce, hipEventDisableTiming));
             PGABB_HIP(hipEventCreateWithFlags(&de, hipEventDisableTiming));
+            copied.push_back(ce);
             done.push_back(de);
+            PGABB_HIP(hipEventRecord(ce, copy_s));
 
             // ---- descriptors and launch
             // descriptors sit at the tasks' positions in `order`; each keeps its
@@ -552,6 +506,7 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
             }
             const int si = win % nstreams;
             hipStream_t st = cs[si];
+            PGABB_HIP(hipStreamWaitEvent(st, ce, 0));
             hipEvent_t k0 = nullptr, k1 = nullptr;
             PGABB_HIP(hipEventCreate(&k0));
             PGABB_HIP(hipEventCreate(&k1));
@@ -561,13 +516,6 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
                                      hipMemcpyHostToDevice, st));
             PGABB_HIP(hipMemcpyAsync(dpre.get() + pre_at, hpre.get() + pre_at, sizeof(int64_t) * (W + 1),
                                      hipMemcpyHostToDevice, st));
-            for (auto x : copy_s) {
-                hipEvent_t ce = nullptr;
-                PGABB_HIP(hipEventCreateWithFlags(&ce, hipEventDisableTiming));
-                copied.push_back(ce);
-                PGABB_HIP(hipEventRecord(ce, x));
-                PGABB_HIP(hipStreamWaitEvent(st, ce, 0));
-            }
             CountArgs a;
             a.tasks = ddesc.get() + p0;
             a.item_pre = dpre.get() + pre_at;
@@ -577,7 +525,7 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
             // a grab sized from the mean would be too coarse for them
             a.grab = grab_opt > 0 ? grab_opt : default_grab(items, 0);
             a.orient = orient;
-            a.total = items;
+                a.total = items;
             a.counts = dcnt.get();
             a.next = dcnt.get() + T + static_cast<size_t>(win) * kLaunchQueueWords;
             PGABB_HIP(hipEventRecord(k0, st));
@@ -585,19 +533,16 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
             PGABB_HIP(hipEventRecord(k1, st));
             PGABB_HIP(hipEventRecord(de, st));
             for (int32_t ti : wtasks)
-                for (int32_t b : {g->tasks[ti].bij, g->tasks[ti].bik, g->tasks[ti].bjk}) {
-                    readers.read(b, si, win);
-                    last_window[b] = win;
-                }
+                for (int32_t b : {g->tasks[ti].bij, g->tasks[ti].bik, g->tasks[ti].bjk}) readers.read(b, si, win);
             pre_at += W + 1;
             if (hybrid) win_end.push_back(next_task);
             ++win;
         }
         for (auto &th : host) th.join();
-        if (moving) move_rest();
         for (auto x : cs) PGABB_HIP(hipStreamSynchronize(x));
-        for (auto x : copy_s) PGABB_HIP(hipStreamSynchronize(x));
+        PGABB_HIP(hipStreamSynchronize(copy_s));
         if (moving) {
+            PGABB_HIP(hipStreamSynchronize(move_s));
             end_moves();
             g->arena.release();
             g->blocks_on_host = true;
@@ -623,7 +568,7 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
     } catch (...) {
         stop_host();
         for (auto x : cs) (void)hipStreamSynchronize(x);
-        for (auto x : copy_s) (void)hipStreamSynchronize(x);
+        (void)hipStreamSynchronize(copy_s);
         if (moving && !g->blocks_on_host) {  // the blocks stay in the device arena
             end_moves();
             g->host_arena.release();
@@ -633,7 +578,7 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
         for (auto e : kstart) (void)hipEventDestroy(e);
         for (auto e : kstop) (void)hipEventDestroy(e);
         for (auto x : cs) (void)hipStreamDestroy(x);
-        for (auto x : copy_s) (void)hipStreamDestroy(x);
+        (void)hipStreamDestroy(copy_s);
         throw;
     }
     for (auto e : copied) (void)hipEventDestroy(e);
@@ -641,7 +586,7 @@ uint64_t count_streamed(pgabb_graph *g, const pgabb_tc_options &opt) {
     for (auto e : kstart) (void)hipEventDestroy(e);
     for (auto e : kstop) (void)hipEventDestroy(e);
     for (auto x : cs) (void)hipStreamDestroy(x);
-    for (auto x : copy_s) (void)hipStreamDestroy(x);
+    (void)hipStreamDestroy(copy_s);
     g->h2d_bytes = h2d;
     g->kernel_launches = static_cast<int64_t>(win) * lk.nparts;
     uint64_t total = 0;
