@@ -616,9 +616,7 @@ void partition_one_block(pgabb_graph *g, int32_t lowest) {
     PGABB_HIP(hipGetLastError());
 }
 
-}  // namespace
-
-void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t *cuts_host) {
+void partition_blocks(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t *cuts_host) {
     hipStream_t s = g->stream;
     const int32_t n = g->n;
     if (!g->part_timer) g->part_timer = std::make_unique<StreamTimer>();
@@ -662,7 +660,7 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
     g->tasks.clear();
     g->task_counts.clear();
     g->block_of.assign(static_cast<size_t>(p) * p, -1);
-    g->p = p;
+    g->p = 0;  // until every table and the arena are there
     g->cut_mode = cuts_host ? -1 : cut_mode;
     g->arena_words = 0;
     g->probe_work_col = 0;
@@ -851,6 +849,34 @@ void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t 
     g->task_counts.assign(g->tasks.size(), 0);
     g->part_timer->stop(s);
     g->part_time_pending = true;
+    g->p = p;
+}
+
+}  // namespace
+
+void partition_graph(pgabb_graph *g, int32_t p, int32_t cut_mode, const int32_t *cuts_host) {
+    try {
+        partition_blocks(g, p, cut_mode, cuts_host);
+    } catch (...) {
+        // Block and task tables are filled in before the arena they point into
+        // is allocated.  A partition that ends early leaves none of them, so
+        // that no later call follows them into memory that is not there: the
+        // graph is as if it had never been partitioned.  (p > 0: it ended
+        // before the previous partition was dropped.)
+        if (g->p == 0) {
+            g->arena.release();
+            g->blocks.clear();
+            g->tasks.clear();
+            g->task_counts.clear();
+            g->block_of.clear();
+            g->cuts.clear();
+            g->base.clear();
+            g->arena_words = 0;
+            g->probe_work_col = 0;
+            g->part_time_pending = false;
+        }
+        throw;
+    }
 }
 
 }  // namespace pgabb
