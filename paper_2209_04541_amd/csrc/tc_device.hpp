@@ -17,6 +17,7 @@
 #pragma once
 
 #include "graph.hpp"
+#include "rules.hpp"
 #include "wave.hpp"
 
 namespace pgabb {
@@ -41,7 +42,7 @@ __device__ __forceinline__ uint32_t filter_slot(int32_t w, int fshift, uint32_t 
 __device__ __forceinline__ uint32_t sorted_contains(gptr<int32_t> a, int32_t lo, int32_t hi, int32_t w) {
     const int32_t end = hi;
     while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
+        const int32_t mid = halfway(lo, hi);
         if (a[mid] < w) lo = mid + 1;
         else hi = mid;
     }
@@ -448,7 +449,7 @@ __device__ __forceinline__ uint32_t walk_item(Staging stg, gptr<int32_t> st_col,
         if (after >= 0 && total >= kAfterSegs * gn) {
             int32_t hi = end;
             while (__ballot(pb < hi) != 0) {  // pb: first entry above after
-                const int32_t mid = (pb + hi) >> 1;
+                const int32_t mid = halfway(pb, hi);
                 if (pb < hi) {
                     if (wk_col[mid] <= after) pb = mid + 1;
                     else hi = mid;
