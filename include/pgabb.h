@@ -430,6 +430,8 @@ pgabb_status pgabb_tc_ktruss(pgabb_graph *g, int32_t k, uint8_t *keep, uint32_t 
  * device cap (all blocks when it had none).  pgabb_graph_info_get then
  * reports the call's time, kernel time, launches and host-to-device bytes;
  * pgabb_graph_4list_counts the 4-lists and their counts.
+ * With the blocks in device memory the call takes up to 128 MB of device
+ * scratch for the time of the call, and less (more slowly) where less is left.
  * Errors: EINVAL (NULL argument), ENOMEM, EDEVICE.
  */
 pgabb_status pgabb_count_4cliques(pgabb_graph *g, uint64_t *count);

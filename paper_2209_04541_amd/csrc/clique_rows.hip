@@ -61,6 +61,9 @@ constexpr int kMaxStripes = 64;
 // = 1.6 M: 233 / 243 / 261 / 274 us).
 constexpr int kHubRanks = 32768;
 constexpr int kHubRanksShort = 4096;
+// When device memory is short the matrix is halved, down to this many ranks,
+// and then left out: every pair is then searched.
+constexpr int kHubRanksLeast = 512;
 constexpr int kRowQueues = 8;        // work counters of the single-wave vertices
 constexpr int kRowQueueStride = 32;  // words apart
 constexpr int kRowGrab = 4;          // vertices per grab
@@ -486,10 +489,18 @@ double quad_rows(pgabb_graph *g, std::vector<uint64_t> &per_list) {
     a.col = g->col.get();
     a.p = p;
     // the hub matrix: rows padded to whole 64-bit words
-    const int32_t hubs = std::min(n, g->max_out > kWave ? kHubRanks : kHubRanksShort);
+    int32_t hubs = std::min(n, g->max_out > kWave ? kHubRanks : kHubRanksShort);
+    DArray<uint32_t> hub;
+    for (;; hubs = hubs > kHubRanksLeast ? hubs / 2 : 0) {
+        a.hub_words = (hubs + 63) / 64 * 2;
+        try {
+            hub.reset(static_cast<size_t>(hubs) * a.hub_words, s);
+            break;
+        } catch (const Error &e) {
+            if (e.status != PGABB_ENOMEM || hubs == 0) throw;
+        }
+    }
     a.hub_lo = n - hubs;
-    a.hub_words = (hubs + 63) / 64 * 2;
-    DArray<uint32_t> hub(static_cast<size_t>(hubs) * a.hub_words, s);
     a.hub = hub.get();
     DArray<int32_t> lists(static_cast<size_t>(n) + static_cast<size_t>(g->m / kWaveRow) + 1, s);
     a.small = lists.get();
@@ -508,8 +519,9 @@ double quad_rows(pgabb_graph *g, std::vector<uint64_t> &per_list) {
     a.cuts = dcuts.get();
     StreamTimer tm;
     tm.start(s);
-    k_hub_rows<<<std::min(grid_for(hubs, kRB / kWave), 4096u), kRB, 0, s>>>(a.row_off, a.col, a.hub_lo, n, a.hub_words,
-                                                                            hub.get());
+    if (hubs)
+        k_hub_rows<<<std::min(grid_for(hubs, kRB / kWave), 4096u), kRB, 0, s>>>(a.row_off, a.col, a.hub_lo, n,
+                                                                                a.hub_words, hub.get());
     k_row_classes<<<grid_for(n, 4 * kRB), kRB, 0, s>>>(a.row_off, n, lists.get() + n, lists.get(), num);
     if (p == 1) k_quad_rows<false><<<256, kRowThreads, 0, s>>>(a);
     else k_quad_rows<true><<<256, kRowThreads, 0, s>>>(a);

@@ -193,6 +193,8 @@ uint64_t four_cliques(pgabb_graph *g, uint64_t device_cap_bytes);
 // The 4-cliques whose lowest vertex has at most kQuadRowCap out-edges, from
 // the oriented CSR (clique_rows.hip): counts of every (i, j, k, l) of the
 // graph's stripes, read with quad_rows_count.  Returns the device time in ms.
+// Takes a bit matrix of up to 128 MB, less where that much memory is not left,
+// and 4 bytes per vertex (ENOMEM, with nothing counted, without those).
 constexpr int kQuadRowCap = 1024;
 double quad_rows(pgabb_graph *g, std::vector<uint64_t> &per_list);
 uint64_t quad_rows_count(const std::vector<uint64_t> &per_list, const std::array<int32_t, 4> &q);

@@ -589,12 +589,19 @@ uint64_t four_cliques(pgabb_graph *g, uint64_t device_cap_bytes) {
         const bool streamed = device_cap_bytes > 0 || g->blocks_on_host;
         std::vector<uint64_t> per_list;  // in core: the rows quad_rows counts
         if (!streamed) {
-            kernel_ms += quad_rows(g, per_list);
-            ++launches;
-            if (g->max_out > kQuadRowCap) {
+            bool rows = true;  // (else memory is too short for their scratch, and the kernels here take them)
+            try {
+                kernel_ms += quad_rows(g, per_list);
+                ++launches;
+            } catch (const Error &e) {
+                if (e.status != PGABB_ENOMEM) throw;
+                rows = false;
+                per_list.clear();
+            }
+            if (!rows || g->max_out > kQuadRowCap) {
                 std::vector<const int32_t *> base(nblk);
                 for (int32_t b = 0; b < nblk; ++b) base[b] = g->arena.get() + g->blocks[b].walk_lo(kOrientRow);
-                quad_launch(g, g->quads, 0, NQ, base, dcnt.get(), NQ, true, kernel_ms, launches);
+                quad_launch(g, g->quads, 0, NQ, base, dcnt.get(), NQ, rows, kernel_ms, launches);
             }
         } else {
             // ---- streamed: the blocks move from the host store through a

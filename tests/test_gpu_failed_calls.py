@@ -81,3 +81,23 @@ def test_partition_that_runs_out_of_memory(p, before):
             assert int(g.task_counts()[1].sum()) == want
             # (sums of at most 2^16 terms in another order)
             assert np.allclose(g.pagerank(max_iter=2)[0], ranks, rtol=1e-10, atol=0)
+
+
+@pytest.mark.parametrize("p", [1, 3])
+@pytest.mark.parametrize("scale,most", [(13, 1 << 22), (13, 1 << 20), (13, 100 << 10), (11, 16 << 10), (11, 6 << 10)])
+def test_four_cliques_with_little_memory(p, scale, most):
+    """No request above `most` bytes is granted: the matrix of the highest ranks
+    (8 MB at scale 13) shrinks, down to nothing at 16 KB, and at 6 KB the
+    vertices' lists do not fit either; the 4-lists' counts stay the same."""
+    n, s, d = gen.rmat(scale, 32, gen.seed(97, 7))
+    want = oracle.four_cliques(n, s, d)
+    with P.Graph(n, s, d) as g:
+        g.partition(p)
+        assert g.info()["max_out_degree"] > 64
+        assert g.four_cliques() == want
+        ijkl, counts = g.four_clique_lists()
+        with RefusingHook(lambda k, b: b > most) as hook:
+            assert g.four_cliques() == want
+        assert hook.refused > 0
+        got_ijkl, got = g.four_clique_lists()
+        assert np.array_equal(got_ijkl, ijkl) and np.array_equal(got, counts)
