@@ -15,6 +15,7 @@
 #include "common.hpp"
 #include "graph.hpp"
 #include "radix.hpp"
+#include "rules.hpp"
 #include "wave.hpp"
 
 namespace pgabb {
@@ -190,6 +191,18 @@ __global__ __launch_bounds__(B) void k_degrees_hi(const uint32_t *__restrict__ h
             if (cnt[q]) atomicAdd(&deg_hi[(high << kLowBits) + q], cnt[q]);
         __syncthreads();
         pos = end;
+    }
+}
+
+// The same from ends that are sorted by all bits: each run of equal ends adds
+// its length once.
+__global__ __launch_bounds__(B) void k_degrees_runs(const uint32_t *__restrict__ his, int64_t m,
+                                                    int32_t *__restrict__ deg_hi) {
+    const int64_t stride = int64_t(gridDim.x) * B;
+    for (int64_t base = blockIdx.x * int64_t(B) + (threadIdx.x & ~63); base < m; base += stride) {
+        const int64_t e = base + lane_id();
+        const bool valid = e < m;
+        add_run_lengths(valid, valid ? static_cast<int64_t>(his[e]) : 0, deg_hi);
     }
 }
 
@@ -400,11 +413,13 @@ void build_graph(pgabb_graph *g, const int32_t *src, const int32_t *dst, int64_t
         if (mu > 0 && his.get()) {
             DArray<uint32_t> his_alt(static_cast<size_t>(mu), s);
             uint32_t *hs = his.get();
-            if (radix_sort_impl<uint32_t>(his.get(), his_alt.get(), nullptr, nullptr, mu, kLowBits, nb, s))
+            const bool low = degrees_by_low_bits(mu, n, kLowBits);
+            if (radix_sort_impl<uint32_t>(his.get(), his_alt.get(), nullptr, nullptr, mu, low ? kLowBits : 0, nb, s))
                 hs = his_alt.get();
             // tiles for some 512 workgroups, long enough for their LDS to pay
             const int64_t tile = std::min<int64_t>(std::max<int64_t>(mu / 512, 8192), 65536);
-            k_degrees_hi<<<static_cast<unsigned>((mu + tile - 1) / tile), B, 0, s>>>(hs, mu, tile, deg_hi);
+            if (low) k_degrees_hi<<<static_cast<unsigned>((mu + tile - 1) / tile), B, 0, s>>>(hs, mu, tile, deg_hi);
+            else k_degrees_runs<<<cap_grid(mu), B, 0, s>>>(hs, mu, reinterpret_cast<int32_t *>(deg_hi));
             PGABB_HIP(hipGetLastError());
         }
         // 4: degrees and ranks

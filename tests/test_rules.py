@@ -19,6 +19,7 @@ int main() {
     long long a, b;
     while (scanf("%31s %lld %lld", op, &a, &b) == 3) {
         if (!strcmp(op, "halfway")) printf("%lld\n", (long long)halfway((int32_t)a, (int32_t)b));
+        if (!strcmp(op, "low_bits")) printf("%d\n", degrees_by_low_bits(a, b, 13));
     }
     return 0;
 }
@@ -60,3 +61,15 @@ def test_halving_stays_inside_the_list(run, at, length):
             assert lo <= mid < hi
             lo, hi = (mid + 1, hi) if mid - at < first else (lo, mid)
         assert lo == at + first
+
+
+@pytest.mark.parametrize("ends,n", [(70000, 2**20), (70000, 2**24), (70000, 2**26), (100000, 2**28), (2**20, 2**22),
+                                    (2**22, 2**24), (2**24, 2**26), (70000, 2**31 - 1), (2**32 - 1, 2**31 - 1)])
+def test_sparse_wide_ids_are_counted_in_runs(run, ends, n):
+    """Few ends share their high bits: no 8,192 counters per value."""
+    assert run([("low_bits", ends, n)]) == [0]
+
+
+@pytest.mark.parametrize("ends,n", [(70000, 8191), (15_700_000, 2**20), (64_000_000, 2**22), (2_000_000, 2**17)])
+def test_dense_ids_are_counted_by_low_bits(run, ends, n):
+    assert run([("low_bits", ends, n)]) == [1]
