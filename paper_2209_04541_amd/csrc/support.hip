@@ -20,13 +20,14 @@
 // N+(b) is staged as a bitmap of the kSupHubs highest ranks ("hubs", which
 // hold most walked entries on skewed graphs) with the number of entries
 // before each word, so an entry is found, and its position known, with no
-// search; entries below the hubs go to a small hash table.  Held in one hash
-// table of all entries (load up to 2/3, probed until the last of 64 lanes is
-// done) a chunk of 64 walked entries cost 105 vector and 97 scalar
-// instructions and the pass was bound by them: R-MAT scale 20 7.15 ms with
-// the walked-edge atomics, 6.50 without.  Now 4.75 and 2.0 ms: bound by the
-// 424 M device atomics, which go past the L2s (one segment per lane in each
-// atomic instruction, touching four times the lines, took 9.8 ms).
+// search.  A row with entries below the hubs goes to a hash table instead, all of
+// it where it fits (kSupWideCap).  Held in one hash table (load up to 2/3, probed
+// until the last of 64 lanes is done, one entry a lane) a chunk of 64 walked
+// entries cost 105 vector and 97 scalar instructions and the pass was bound by
+// them: R-MAT scale 20 7.15 ms with the walked-edge atomics, 6.50 without.  Now
+// 4.25 ms, bound by the 424 M device atomics, which go past the L2s (2.8 ms of
+// them; one segment per lane in each atomic instruction, touching four times the
+// lines, took 9.8 ms).
 //
 // Work units are runs of at most 64 in-edges of one owner (one per lane), so
 // an owner with many in-edges spreads over many waves (each stages N+(b) and
@@ -39,6 +40,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cstddef>
 
 #include "common.hpp"
 #include "graph.hpp"
@@ -56,6 +58,22 @@ constexpr int kSupWords = kSupHubs / 32;
 constexpr int kSupCap = 1024;                 // longest row staged in LDS
 constexpr int kSupLowCap = 341;               // entries below the hubs that are (table load <= 2/3)
 constexpr int kSupTableLg = 9;
+// Rows with entries below the hubs, up to this length, take the whole LDS region
+// for one table of all their entries, counted by slot: an entry is looked up
+// once, not in the bitmap and then in a table, and dense graphs of more than
+// kSupHubs vertices without skew keep their rows in LDS.  Kernel ms, every row in
+// one hash table of 1,024 slots / bitmap and table, longer low rows searched in
+// device memory / now: 64 complete graphs of 600 vertices 8.9 / 18.5 / 8.5; random
+// geometric graphs of 20,011 vertices at degree 300 1.94 / 1.66 / 1.07, 600 5.6 /
+// 7.8 / 4.0, 1000 14.4 / 14.4 / 12.6; Erdos-Renyi, 100,001 vertices at degree 100
+// 0.92 / 0.68 / 0.39; R-MAT scale 20 7.1 / 4.96 / 4.25.
+constexpr int kSupWideCap = 682;
+constexpr int kSupWideLg = 10;
+// A segment's entries take this many steps through the table together, so that
+// their reads overlap; what is left of each then runs by itself, since together
+// all wait for the longest of 256 (0 / 1 / 2 / all steps together: degree 1000
+// 14.5 / 13.9 / 12.6 / 16.6, 600 4.0 / 4.1 / 4.0 / 4.4).
+constexpr int kSupJoined = 2;
 constexpr int kSupUnitEdges = kWave;  // in-edges per work unit (one per lane)
 // Units per grab (random geometric graph, 200,003 vertices: 549 us at 1, 399
 // at 2, 347 at 4, where a unit is a short chain of dependent loads).
@@ -64,15 +82,26 @@ constexpr int kSupQueues = 8;       // work counters, kSupQueueStride words apar
 constexpr int kSupQueueStride = 32;
 
 struct SupportLds {
-    uint32_t bits[kSupWords + 1];      // N+(b)'s hubs; a zero word after them
+    union {
+        struct {
+            int32_t key[1 << kSupTableLg];     // hash table of the entries below the hubs: entry, or -1
+            uint16_t pos[1 << kSupTableLg];    // its position in the row
+            uint32_t cnt[kSupCap / 4];         // triangles found on edge (b, row[x]), a byte each: a unit's
+                                               // 64 in-edges find at most one each
+            uint32_t bits[kSupWords + 1];      // N+(b)'s hubs; a zero word after them
+            uint16_t before[kSupWords + 2];    // N+(b)'s hubs before each word
+        };
+        struct {  // rows up to kSupWideCap entries, some of them below the hubs
+            int32_t wide_key[1 << kSupWideLg];       // hash table of all entries
+            uint32_t wide_cnt[(1 << kSupWideLg) / 4];  // the triangles, by slot
+        };
+    };
     uint32_t own[kWave];               // list positions of the flattened walk
-    uint16_t before[kSupWords + 2];    // N+(b)'s hubs before each word
-    int32_t key[1 << kSupTableLg];     // hash table of the entries below the hubs: entry, or -1
-    uint16_t pos[1 << kSupTableLg];    // its position in the row
-    uint32_t cnt[kSupCap / 4];         // triangles found on edge (b, row[x]), a byte each: a unit's
-                                       // 64 in-edges find at most one each
     uint32_t hits[kWave];              // triangles found on each in-edge of the unit
 };
+static_assert(offsetof(SupportLds, wide_cnt) + sizeof(SupportLds::wide_cnt) <=
+                  offsetof(SupportLds, bits) + kSupWords * sizeof(uint32_t),
+              "a wide row leaves the zero word");
 
 // Entries after every CSR position in its row: the length of the walk an
 // in-edge at that position starts.
@@ -185,7 +214,6 @@ void k_edge_support(const int64_t *__restrict__ row_off,
             g_len[j] = lane < __builtin_amdgcn_readlane(hin, j) ? rs[g_eab[j]] : 0;
 #pragma unroll 1
         for (int j = 0; j < ng; ++j) {
-        const int32_t b = __builtin_amdgcn_readlane(hb, j);
         const int32_t d = __builtin_amdgcn_readlane(hd, j);
         const int32_t nin = __builtin_amdgcn_readlane(hin, j);
         const int64_t b0 = shfl_t(hb0, j);
@@ -204,10 +232,15 @@ void k_edge_support(const int64_t *__restrict__ row_off,
             const int32_t x = x0 + lane;
             low += __popcll(__ballot(x < d && cl[b0 + x] < hub_lo));
         }
-        const bool staged = d <= kSupCap && low <= kSupLowCap;
+        const bool wide = low > 0 && d <= kSupWideCap;
+        const bool staged = wide || (d <= kSupCap && low <= kSupLowCap);
+        if (wide) low = d;
+        const int32_t table_end = wide ? INT32_MAX : hub_lo;  // entries below it are in the table
         const bool hubs = d > low;
-        int lg = 6;  // table of 2^lg >= 1.5 low slots
-        while ((1 << lg) * 2 < 3 * low && lg < kSupTableLg) ++lg;
+        int lg = 6;  // table of 2^lg >= 3 low slots, as far as they are there (1.5 low are)
+        while ((1 << lg) < 3 * low && lg < (wide ? kSupWideLg : kSupTableLg)) ++lg;
+        int32_t *const key = L.wide_key;  // (both tables start there)
+        uint32_t *const cnt = wide ? L.wide_cnt : L.cnt;
         const uint32_t tmask = (1u << lg) - 1u;
         const int shift = 24 - lg;
         if (staged) {
@@ -215,19 +248,19 @@ void k_edge_support(const int64_t *__restrict__ row_off,
 #pragma unroll
                 for (int q = 0; q < kSupWords / kWave; ++q) L.bits[q * kWave + lane] = 0u;
             }
-            for (int x = lane; x < (d + 3) / 4; x += kWave) L.cnt[x] = 0u;
+            for (int x = lane; x < (wide ? 1 << lg : d + 3) / 4; x += kWave) cnt[x] = 0u;
             if (low > 0)
-                for (int x = lane; x < (1 << lg); x += kWave) L.key[x] = -1;
+                for (int x = lane; x < (1 << lg); x += kWave) key[x] = -1;
             wave_lds_sync();
             for (int x = lane; x < d; x += kWave) {
                 const int32_t v = x < kWave ? v0 : cl[b0 + x];
-                const int32_t h = v - hub_lo;
-                if (h >= 0) {
+                if (v >= table_end) {
+                    const int32_t h = v - hub_lo;
                     atomicOr(&L.bits[h >> 5], 1u << (h & 31));
                 } else {
                     uint32_t s = hash_slot(v, shift, tmask);
-                    while (atomicCAS(&L.key[s], -1, v) != -1) s = (s + 1) & tmask;
-                    L.pos[s] = static_cast<uint16_t>(x);
+                    while (atomicCAS(&key[s], -1, v) != -1) s = (s + 1) & tmask;
+                    if (!wide) L.pos[s] = static_cast<uint16_t>(x);
                 }
             }
             wave_lds_sync();
@@ -290,35 +323,40 @@ void k_edge_support(const int64_t *__restrict__ row_off,
                     for (int r = 0; r < kSeg; ++r) {
                         if (((word[r] >> (h[r] & 31)) & 1u) == 0u) continue;
                         const uint32_t at = L.before[h[r] >> 5] + __popc(word[r] & ((1u << (h[r] & 31)) - 1u));
-                        atomicAdd(&L.cnt[at >> 2], 1u << (8 * (at & 3u)));
+                        atomicAdd(&cnt[at >> 2], 1u << (8 * (at & 3u)));
                         hits |= 1u << r;
                     }
                 }
                 if (low > 0) {
-                    // the segment's entries probe together: their reads overlap
                     bool go[kSeg], any = false;
                     uint32_t s[kSeg];
 #pragma unroll
                     for (int r = 0; r < kSeg; ++r) {
-                        go[r] = r < n && v[r] < hub_lo;
+                        go[r] = r < n && v[r] < table_end;
                         s[r] = hash_slot(v[r], shift, tmask);
                         any |= go[r];
                     }
-                    while (__ballot(any) != 0) {
+                    auto step = [&](int r) {
+                        const int32_t kv = key[s[r]];
+                        if (go[r] && kv == v[r]) {
+                            const uint32_t at = wide ? s[r] : L.pos[s[r]];
+                            atomicAdd(&cnt[at >> 2], 1u << (8 * (at & 3u)));
+                            hits |= 1u << r;
+                        }
+                        go[r] = go[r] && kv != -1 && kv != v[r];
+                        s[r] = (s[r] + 1) & tmask;
+                    };
+                    for (int z = 0; z < kSupJoined && __ballot(any) != 0; ++z) {
                         any = false;
 #pragma unroll
                         for (int r = 0; r < kSeg; ++r) {
-                            const int32_t kv = L.key[s[r]];
-                            if (go[r] && kv == v[r]) {
-                                const uint32_t at = L.pos[s[r]];
-                                atomicAdd(&L.cnt[at >> 2], 1u << (8 * (at & 3u)));
-                                hits |= 1u << r;
-                            }
-                            go[r] = go[r] && kv != -1 && kv != v[r];
-                            s[r] = (s[r] + 1) & tmask;
+                            step(r);
                             any |= go[r];
                         }
                     }
+#pragma unroll
+                    for (int r = 0; r < kSeg; ++r)
+                        while (__ballot(go[r]) != 0) step(r);
                 }
             } else {
 #pragma unroll
@@ -376,7 +414,13 @@ void k_edge_support(const int64_t *__restrict__ row_off,
         if (lane < nin && L.hits[lane]) atomicAdd(&support[eab], L.hits[lane]);
         if (staged)
             for (int x = lane; x < d; x += kWave) {
-                const uint32_t c = (L.cnt[x >> 2] >> (8 * (x & 3))) & 0xffu;
+                uint32_t at = x;
+                if (wide) {  // (the entry is in the table)
+                    const int32_t e = cl[b0 + x];
+                    at = hash_slot(e, shift, tmask);
+                    while (key[at] != e) at = (at + 1) & tmask;
+                }
+                const uint32_t c = (cnt[at >> 2] >> (8 * (at & 3))) & 0xffu;
                 if (c) atomicAdd(&support[b0 + x], c);
             }
         wave_lds_sync();  // before the next unit is staged
