@@ -41,6 +41,7 @@ constexpr int kPeelWaves = 4;
 // 1.97 / 1.61 / 1.82 ms; of a random geometric graph 0.63 / 0.74 / 1.05).
 constexpr int kPeelGroups = 8;
 constexpr int kTrussRound = 4;  // rounds queued per host round trip
+constexpr int kPeelQueues = 16, kPeelStride = 16;  // work counters of a round, 128 bytes apart
 
 enum : uint8_t { kLive = 0, kDying = 1, kDead = 2 };
 
@@ -68,36 +69,41 @@ __global__ __launch_bounds__(kKB) void k_kt_clear(uint8_t *__restrict__ state, i
 // The first frontier: live edges with fewer than `need` triangles become dying
 // and are appended to `front`, with one counter atomic per workgroup and
 // kFrontPer * kKB edges (one per wave of 64 edges took 446 us on R-MAT scale
-// 18: 59 K atomics on one word).
+// 18: 59 K atomics on one word), in the order of their positions: a group of the
+// peeling launch takes neighbouring entries, which then share their rows.
 constexpr int kFrontPer = 16;
 __global__ __launch_bounds__(kKB) void k_kt_front(const uint32_t *__restrict__ sup, int64_t m, uint32_t need,
                                                    uint8_t *__restrict__ state, uint32_t *__restrict__ front,
                                                    unsigned long long *__restrict__ nfront) {
-    __shared__ uint32_t s_n;
+    static_assert(kFrontPer * (kKB / kWave) == kWave, "one wave scans the counts");
+    __shared__ uint32_t s_pre[kWave];  // by 256 edges and wave: edges taken, then those taken before
     __shared__ unsigned long long s_at;
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
     for (int64_t base = blockIdx.x * static_cast<int64_t>(kKB) * kFrontPer; base < m;
          base += static_cast<int64_t>(gridDim.x) * kKB * kFrontPer) {
-        if (threadIdx.x == 0) s_n = 0;
-        __syncthreads();
-        uint32_t mine = 0, take = 0;
+        uint64_t taken[kFrontPer];  // by the wave's lanes
 #pragma unroll
         for (int q = 0; q < kFrontPer; ++q) {
             const int64_t e = base + q * kKB + threadIdx.x;
-            if (e < m && sup[e] < need) take |= 1u << q;
+            taken[q] = __ballot(e < m && sup[e] < need);
+            if (lane == 0) s_pre[q * (kKB / kWave) + w] = static_cast<uint32_t>(__popcll(taken[q]));
         }
-        mine = __popc(take);
-        uint32_t at = mine ? atomicAdd(&s_n, mine) : 0u;
         __syncthreads();
-        if (threadIdx.x == 0 && s_n) s_at = atomicAdd(nfront, static_cast<unsigned long long>(s_n));
+        if (w == 0) {
+            const uint32_t c = s_pre[lane], incl = wave_inclusive_scan(c);
+            s_pre[lane] = incl - c;
+            if (lane == kWave - 1 && incl) s_at = atomicAdd(nfront, static_cast<unsigned long long>(incl));
+        }
         __syncthreads();
-        while (take) {
-            const int q = __builtin_ctz(take);
-            take &= take - 1;
+#pragma unroll
+        for (int q = 0; q < kFrontPer; ++q) {
+            if (!((taken[q] >> lane) & 1ull)) continue;
             const int64_t e = base + q * kKB + threadIdx.x;
             state[e] = kDying;
-            front[s_at + at++] = static_cast<uint32_t>(e);
+            front[s_at + s_pre[q * (kKB / kWave) + w] + __popcll(taken[q] & below)] = static_cast<uint32_t>(e);
         }
-        __syncthreads();  // before the next turn's counter
+        __syncthreads();  // before the next turn's counts
     }
 }
 
@@ -115,18 +121,25 @@ __global__ __launch_bounds__(kKB) void k_kt_turn(const uint32_t *__restrict__ fr
     }
 }
 
+// Edges that a wave keeps for the next frontier before it adds them to the
+// device's list, of which one batch can bring two a lane.  The list's counter is
+// one word: an addition per batch made the longest launches longer (figures at
+// k_kt_peel).
+constexpr int kDropBuf = 2 * kWave;
+
 struct PeelLds {
     int32_t pre[kWave];   // position of each lane's list in the flattened walk
     uint32_t e[kWave];    // the frontier edge (u, v)
     int32_t v[kWave];
     int32_t nin_u[kWave];   // u's in-edges
-    int64_t iu0[kWave];     // u's first in-edge slot
-    int64_t ou0[kWave];     // u's first out-edge position
-    int64_t iv0[kWave], iv1[kWave];  // v's in-edge slots
-    int64_t ov0[kWave], ov1[kWave];  // v's out-edge positions
+    uint32_t iu0[kWave];     // u's first in-edge slot (m' < 2^32)
+    uint32_t ou0[kWave];     // u's first out-edge position
+    uint32_t iv0[kWave], iv1[kWave];  // v's in-edge slots
+    uint32_t ov0[kWave], ov1[kWave];  // v's out-edge positions
     int32_t own[kWave];     // list starts of the current batch
     int32_t left[kWave];    // triangles of the frontier edge still to be met
     int32_t from[kWave];    // first of u's neighbours in the walk
+    uint32_t drop[kDropBuf];  // edges for the next frontier
 };
 
 // First index in [lo, hi) of the sorted x whose value is at least w.
@@ -143,14 +156,28 @@ __device__ __forceinline__ I lower_at(gptr<int32_t> x, I lo, I hi, int32_t w) {
 // One round's triangle updates: groups of up to 64 frontier edges, one per
 // lane.  A group is a chain of dependent loads (each batch of 64 neighbours
 // ends in binary searches), so small frontiers are cut into groups of few
-// edges, down to a part of one edge's neighbours.  Groups are dealt to the
-// waves in turn: taken from a counter, every wave's last (empty) take alone
-// made a round of any size last 100 us, one word serving some 80 M atomics a
-// second.  An edge's count says how many of its triangles are left to be met,
-// so an edge in none walks nothing and the others' neighbours after the last
-// triangle cost no load.  An edge that a vanished triangle brings below
-// `need` is appended to `after`, the next round's frontier, by the one
-// decrement that does.
+// edges, down to a part of one edge's neighbours.  Groups of fewer than
+// kTakenEdges edges are dealt to the waves in turn: taken from a counter, every
+// wave's last (empty) take alone made a round of any size last 100 us, one word
+// serving some 80 M atomics a second.  Larger rounds last milliseconds, and the
+// longest of a wave's turns held them up; there the waves take their groups
+// (UnitTaker).  An edge's count says how many of its triangles are left to be
+// met, so an edge in none walks nothing and the others' neighbours after the
+// last triangle cost no load.  An edge that a vanished triangle brings below
+// `need` joins `after`, the next round's frontier, by the one decrement that
+// does; a wave gathers those in LDS.  The launch keeps eight workgroups on a CU
+// (the grid's size): positions are 32 bits wide for that.
+//
+// Longest launch on R-MAT scale 20, k = 8 / 20 / 64, ms: 4.9 / 11.6 / 24.6 with
+// groups from one counter and a scan for the next frontier (all rounds 8.5 /
+// 20.3 / 41.8); dealt in turn, an addition per batch 5.8 / 13.9 / 28.2 (6.8 /
+// 16.7 / 36.0); with the buffer 5.2 / 13.6 / 27.9 (6.0 / 15.6 / 34.0), and seven
+// workgroups on a CU 6.3 / 18.5 / 41.6; with large rounds taken 4.5 / 12.0 /
+// 26.0 (5.5 / 14.9 / 33.8).  Large rounds taken without the buffer: 5.2 / 11.0 /
+// 24.3 (6.2 / 13.7 / 32.0), but slower on clustered graphs (a random geometric
+// graph of 200,003 vertices, k = 8, all kernels 1.35 ms, 1.24 with it).
+constexpr int64_t kTakenEdges = 8;
+
 __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *__restrict__ front_,
                                                                 const unsigned long long *__restrict__ nfront_,
                                                                 const int64_t *__restrict__ row_off_,
@@ -162,7 +189,8 @@ __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *_
                                                                 const uint8_t *__restrict__ state_,
                                                                 uint32_t *__restrict__ sup, uint32_t need,
                                                                 uint32_t *__restrict__ after,
-                                                                unsigned long long *__restrict__ nafter) {
+                                                                unsigned long long *__restrict__ nafter,
+                                                                unsigned long long *__restrict__ next) {
     __shared__ PeelLds s_lds[kPeelWaves];
     PeelLds &L = s_lds[threadIdx.x / kWave];
     const int lane = lane_id();
@@ -183,9 +211,18 @@ __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *_
     const int32_t parts = static_cast<int32_t>(max(min(want / cnt, static_cast<int64_t>(kWave)), static_cast<int64_t>(1)));
     const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
     const int64_t waves = static_cast<int64_t>(gridDim.x) * kPeelWaves;
-    for (int64_t g0 = blockIdx.x * static_cast<int64_t>(kPeelWaves) + threadIdx.x / kWave;; g0 += waves) {
+    int ndrop = 0;  // edges in L.drop
+    auto append = [&](int num) {
+        unsigned long long at = 0;
+        if (lane == 0) at = atomicAdd(nafter, static_cast<unsigned long long>(num));
+        at = shfl_t(at, 0);
+        for (int i = lane; i < num; i += kWave) after[at + i] = L.drop[i];
+        wave_lds_sync();  // before the buffer is filled again
+    };
+    const int64_t wave = blockIdx.x * static_cast<int64_t>(kPeelWaves) + threadIdx.x / kWave;
+    const int64_t groups = (cnt + per - 1) / per * parts;
+    auto peel_group = [&](int64_t g0) {
         const int64_t first = g0 / parts * per;
-        if (first >= cnt) break;
         const int32_t part = static_cast<int32_t>(g0 % parts);
         const int64_t idx = first + lane;
         int32_t len = 0;
@@ -204,12 +241,12 @@ __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *_
             L.e[lane] = e;
             L.v[lane] = v;
             L.nin_u[lane] = static_cast<int32_t>(iu1 - iu0);
-            L.iu0[lane] = iu0;
-            L.ou0[lane] = ou0;
-            L.iv0[lane] = io[v];
-            L.iv1[lane] = io[v + 1];
-            L.ov0[lane] = ro[v];
-            L.ov1[lane] = ro[v + 1];
+            L.iu0[lane] = static_cast<uint32_t>(iu0);
+            L.ou0[lane] = static_cast<uint32_t>(ou0);
+            L.iv0[lane] = static_cast<uint32_t>(io[v]);
+            L.iv1[lane] = static_cast<uint32_t>(io[v + 1]);
+            L.ov0[lane] = static_cast<uint32_t>(ro[v]);
+            L.ov1[lane] = static_cast<uint32_t>(ro[v + 1]);
         }
         const int32_t incl = wave_inclusive_scan(len);
         const int32_t pre = incl - len;
@@ -241,11 +278,11 @@ __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *_
                 int32_t w;
                 uint32_t f;  // edge (u, w)
                 if (t < L.nin_u[sl]) {
-                    const int64_t k = L.iu0[sl] + t;
+                    const int64_t k = static_cast<int64_t>(L.iu0[sl]) + t;
                     w = in_nb[k];
                     f = ip[k];
                 } else {
-                    const int64_t q = L.ou0[sl] + (t - L.nin_u[sl]);
+                    const int64_t q = static_cast<int64_t>(L.ou0[sl]) + (t - L.nin_u[sl]);
                     w = col[q];
                     f = static_cast<uint32_t>(q);
                 }
@@ -276,22 +313,32 @@ __global__ __launch_bounds__(kPeelWaves *kWave) void k_kt_peel(const uint32_t *_
             if (el < total) visit();
             const uint64_t mf = __ballot(drop_f != UINT32_MAX), mg = __ballot(drop_g != UINT32_MAX);
             if ((mf | mg) == 0) continue;
-            const int nf = __popcll(mf);
-            unsigned long long at = 0;
-            if (lane == 0) at = atomicAdd(nafter, static_cast<unsigned long long>(nf + __popcll(mg)));
-            at = shfl_t(at, 0);
-            if (drop_f != UINT32_MAX) after[at + __popcll(mf & below)] = drop_f;
-            if (drop_g != UINT32_MAX) after[at + nf + __popcll(mg & below)] = drop_g;
+            const int nf = __popcll(mf), ng = __popcll(mg);
+            if (ndrop + nf + ng > kDropBuf) {
+                append(ndrop);
+                ndrop = 0;
+            }
+            if (drop_f != UINT32_MAX) L.drop[ndrop + __popcll(mf & below)] = drop_f;
+            if (drop_g != UINT32_MAX) L.drop[ndrop + nf + __popcll(mg & below)] = drop_g;
+            ndrop += nf + ng;
+            wave_lds_sync();
         }
         wave_lds_sync();  // before the next group overwrites the lane records
+    };
+    if (per >= kTakenEdges) {
+        UnitTaker<kPeelQueues, kPeelStride> taker(next, groups, waves, wave);
+        for (int64_t g0; (g0 = taker.take(lane)) >= 0;) peel_group(g0);
+    } else {
+        for (int64_t g0 = wave; g0 < groups; g0 += waves) peel_group(g0);
     }
+    if (ndrop) append(ndrop);
 }
 
-// Clears p[0, n) (n <= 64), p[0] to *first if given.
+// Clears p[0, n), p[0] to *first if given (by one wave: all its lanes have read
+// *first, which lies in there, before one of them writes).
 __global__ void k_kt_zero(unsigned long long *p, const unsigned long long *first, int32_t n) {
     const unsigned long long f = first ? *first : 0ull;
-    const int32_t i = threadIdx.x;
-    if (i < n) p[i] = i == 0 ? f : 0ull;
+    for (int32_t i = threadIdx.x; i < n; i += kWave) p[i] = i == 0 ? f : 0ull;
 }
 
 __global__ __launch_bounds__(kKB) void k_kt_keep(const uint8_t *__restrict__ state, int64_t m,
@@ -331,8 +378,8 @@ int64_t ktruss(pgabb_graph *g, int32_t k, uint8_t *keep, bool on_device, int32_t
             DArray<uint32_t> front_a(static_cast<size_t>(m), s), front_b(static_cast<size_t>(m), s);
             // kTrussRound rounds are queued per host round trip (a round after
             // an empty frontier does nothing): frontier sizes of the rounds
-            // and of the one after
-            constexpr int kCtr = kTrussRound + 1;
+            // and of the one after, then the rounds' work counters
+            constexpr int kCtr = kTrussRound + 1 + kTrussRound * kPeelQueues * kPeelStride;
             DArray<unsigned long long> ctr(kCtr, s);
             Staged<unsigned long long> h_front(kTrussRound + 1, s);
             uint32_t *front = front_a.get(), *after = front_b.get();
@@ -348,7 +395,8 @@ int64_t ktruss(pgabb_graph *g, int32_t k, uint8_t *keep, bool on_device, int32_t
                     k_kt_peel<<<grid, kPeelWaves * kWave, 0, s>>>(front, ctr.get() + q, g->row_off.get(), g->col.get(),
                                                                    lo_end.get(), in_off.get(), in_pos.get(),
                                                                    in_nb.get(), state.get(), sup.get(), need, after,
-                                                                   ctr.get() + q + 1);
+                                                                   ctr.get() + q + 1,
+                                                                   ctr.get() + kTrussRound + 1 + q * kPeelQueues * kPeelStride);
                     k_kt_turn<<<std::min(grid_for(m, kKB), 1024u), kKB, 0, s>>>(front, ctr.get() + q, after,
                                                                              ctr.get() + q + 1, state.get());
                     std::swap(front, after);
