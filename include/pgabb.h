@@ -112,7 +112,7 @@ typedef struct pgabb_tc_options {
     uint32_t flags;            /* PGABB_OPT_* */
     int32_t waves_per_block;   /* 2, 4 or 8 waves per workgroup (0 = default) */
     int32_t rows_per_grab;     /* work items a wave takes per work-counter
-                                  update, 1..64 (0 = chosen: about 16K walked
+                                  update, 1..64 (0 = chosen: about 12K walked
                                   entries per grab for in-core graphs and
                                   servers, from the item count when
                                   streaming) */

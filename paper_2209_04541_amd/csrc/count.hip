@@ -142,7 +142,6 @@ void launch_tc_tasks(const CountArgs &args, const LaunchKind &lk, int waves, hip
     // the parts of a split launch run at the default shape (waves and unroll
     // options apply to single launches)
     unsigned long long *const next0 = a.next;
-    a.grab = std::min(a.grab * lk.nparts, kWave);  // a part counts a share of the items it takes
     for (int q = 0; q < lk.nparts; ++q) {
         a.next = next0 + static_cast<size_t>(q) * kQueueWords;  // counters of their own, cleared before
         a.stage_lo = q == 0 ? 0 : lk.hi[q - 1];
@@ -300,9 +299,9 @@ static uint64_t count_in_core(pgabb_graph *g, const pgabb_tc_options &opt) {
     a.next = dcnt + T;
     // walked entries of these tasks, at the graph's mean per item
     const uint64_t walked = static_cast<uint64_t>(static_cast<double>(walked_entries(g, orient)) * g->task_share);
-    a.grab = opt.rows_per_grab > 0 ? opt.rows_per_grab : default_grab(pre[T], walked);
-    a.orient = orient;
     const LaunchKind lk = launch_kind(opt.kernel, max_st, max_wk, min_wk);
+    a.grab = grab_items(opt.rows_per_grab, default_grab(pre[T], walked), lk.nparts);
+    a.orient = orient;
     const int waves = opt.waves_per_block > 0 ? opt.waves_per_block : 4;
     StreamTimer tm;
     tm.start(s);
@@ -478,7 +477,7 @@ class MergedLaunch {
     MergedLaunch(const MergedTasks &m, const pgabb_tc_options &opt, int orient, hipStream_t s)
         : m_(m), s_(s), T_(static_cast<int32_t>(m.desc.size())) {
         lk_ = launch_kind(opt.kernel, m.max_st, m.max_wk, m.min_wk);
-        g0_ = default_grab(m.pre.back(), m.walked);
+        g0_ = grab_items(0, default_grab(m.pre.back(), m.walked), lk_.nparts);
         if (T_ == 0) return;
         Staged<TaskDesc> td(T_, s);
         Staged<int64_t> pre(static_cast<size_t>(T_) + 1, s);

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "graph.hpp"
+#include "rules.hpp"
 
 namespace pgabb {
 
@@ -60,8 +61,8 @@ struct LaunchKind {
     int pwords[3] = {0, 0, 0};
 };
 LaunchKind launch_kind(int32_t kernel, int32_t max_out, int32_t max_wk, int32_t min_wk);
-// Items per grab from the launch's items and the entries their walks read
-// (walked = 0: from the item count alone).
+// Items per grab of a whole launch from its items and the entries their walks
+// read (walked = 0: from the item count alone); see grab_items.
 int default_grab(int64_t total_items, uint64_t walked);
 // Entries a walk of graph g reads in orientation `orient` (W or W_col).
 uint64_t walked_entries(const pgabb_graph *g, int orient);

@@ -134,9 +134,9 @@ uint64_t count_noalloc(pgabb_graph *g, const pgabb_tc_options &opt) {
         a.next = dcnt + T;
         const uint64_t walked =
             static_cast<uint64_t>(static_cast<double>(walked_entries(g, orient)) * g->task_share);
-        a.grab = opt.rows_per_grab > 0 ? opt.rows_per_grab : default_grab(pre[T], walked);
-        a.orient = orient;
         const LaunchKind lk = launch_kind(opt.kernel, max_st, max_wk, min_wk);
+        a.grab = grab_items(opt.rows_per_grab, default_grab(pre[T], walked), lk.nparts);
+        a.orient = orient;
         const int waves = opt.waves_per_block > 0 ? opt.waves_per_block : 4;
         launch_tc_tasks(a, lk, waves, s, 0, opt.unroll);
 

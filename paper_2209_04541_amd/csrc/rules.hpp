@@ -25,4 +25,9 @@ constexpr bool degrees_by_low_bits(int64_t ends, int64_t n, int low_bits) {
     return ends >= kEndsPerHigh * ((n >> low_bits) + 1);
 }
 
+// Work items a wave takes per work-counter update: what the caller asked for,
+// else the chosen number, times the parts of a launch that is split by
+// staged-list length (each part counts a share of the items it takes).
+constexpr int grab_items(int asked, int chosen, int parts) { return asked > 0 ? asked : chosen * parts; }
+
 }  // namespace pgabb

@@ -255,12 +255,12 @@ static void counter_loop(pgabb_server *s) {
                 a.tasks = dtd.get();
                 a.item_pre = dpre.get();
                 a.ntasks = T;
-                a.grab = s->opt.rows_per_grab > 0 ? s->opt.rows_per_grab : default_grab(pre.back(), walked);
                 a.orient = orient_of_option(s->opt, nullptr);
                 a.total = pre.back();
                 a.counts = dcnt.get();
                 a.next = dcnt.get() + L;
                 const LaunchKind lk = launch_kind(s->opt.kernel, max_out, max_wk, min_wk);
+                a.grab = grab_items(s->opt.rows_per_grab, default_grab(pre.back(), walked), lk.nparts);
                 ktimer.start(cs);
                 launch_tc_tasks(a, lk, s->opt.waves_per_block > 0 ? s->opt.waves_per_block : 4, cs, 0,
                                 s->opt.unroll);

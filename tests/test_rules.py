@@ -19,6 +19,7 @@ int main() {
     long long a, b;
     while (scanf("%31s %lld %lld", op, &a, &b) == 3) {
         if (!strcmp(op, "halfway")) printf("%lld\n", (long long)halfway((int32_t)a, (int32_t)b));
+        if (!strcmp(op, "grab")) printf("%d\n", grab_items((int)a, (int)(b / 8), (int)(b % 8)));
         if (!strcmp(op, "low_bits")) printf("%d\n", degrees_by_low_bits(a, b, 13));
     }
     return 0;
@@ -73,3 +74,11 @@ def test_sparse_wide_ids_are_counted_in_runs(run, ends, n):
 @pytest.mark.parametrize("ends,n", [(70000, 8191), (15_700_000, 2**20), (64_000_000, 2**22), (2_000_000, 2**17)])
 def test_dense_ids_are_counted_by_low_bits(run, ends, n):
     assert run([("low_bits", ends, n)]) == [1]
+
+
+@pytest.mark.parametrize("parts", [1, 2, 3])
+@pytest.mark.parametrize("chosen", [2, 16, 64])
+def test_an_asked_for_grab_is_kept(run, parts, chosen):
+    """rows_per_grab as the caller gave it, in split launches too; a chosen one
+    grows with the parts."""
+    assert run([("grab", a, 8 * chosen + parts) for a in (0, 1, 5, 64)]) == [chosen * parts, 1, 5, 64]
