@@ -271,7 +271,9 @@ size_t pgabb_tc_count_noalloc_scratch_bytes(void);
  * batch), timed on the launch itself.  Both are searched the first time a
  * class is seen and kept in a tuning cache (in memory and in the file named
  * by PGABB_TUNE_CACHE, else $XDG_CACHE_HOME/pgabb/tune.txt or
- * $HOME/.cache/pgabb/tune.txt).  Afterwards each graph's
+ * $HOME/.cache/pgabb/tune.txt; launch shapes under a version of the counting
+ * kernels, so those found with other kernels are searched again).  Afterwards
+ * each graph's
  * pgabb_graph_task_counts holds its own tasks' counts and
  * pgabb_graph_info_get the shared launch's times and the tuning time.  Errors: EINVAL
  * (num_graphs < 0, a NULL array or graph, a graph listed twice, bad

@@ -447,7 +447,7 @@ struct TuneVal {
 // edges and longest oriented row.
 std::string tune_key(const pgabb_batch *b) {
     char key[96];
-    snprintf(key, sizeof key, "batch/G%d/N%d/M%d/D%d", bit_width_u64(static_cast<uint64_t>(b->G)),
+    snprintf(key, sizeof key, "batch/" PGABB_TUNE_KERNELS "/G%d/N%d/M%d/D%d", bit_width_u64(static_cast<uint64_t>(b->G)),
              bit_width_u64(static_cast<uint64_t>(b->max_n)), bit_width_u64(static_cast<uint64_t>(b->mu)),
              bit_width_u64(static_cast<uint64_t>(b->max_out)));
     return key;

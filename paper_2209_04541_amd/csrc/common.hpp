@@ -201,7 +201,13 @@ bool radix_sort_u64(uint64_t *keys, uint64_t *keys_alt, uint32_t *vals, uint32_t
 bool radix_sort_u32(uint32_t *keys, uint32_t *keys_alt, uint32_t *vals, uint32_t *vals_alt,
                     int64_t n, int nbits, hipStream_t s);
 
-// Persisted autotuner results (tune_cache.cpp).
+// Persisted autotuner results (tune_cache.cpp).  Keys of launch shapes carry the
+// counting kernels' version: a shape that was timed with other kernels is not
+// the best one for these, and numbers may mean something else (a new version
+// with every change of that kind).  The grid of a partition (tc_graphs_grid/)
+// does not: any of its values counts right with any kernel, and a file may hold
+// grids that someone chose.
+#define PGABB_TUNE_KERNELS "k2"
 bool tune_lookup(const std::string &key, std::vector<int> &val);
 void tune_store(const std::string &key, const std::vector<int> &val);
 void tune_forget_all();

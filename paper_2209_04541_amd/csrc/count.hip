@@ -653,7 +653,7 @@ void count_graphs(pgabb_graph *const *gs, int64_t G, const pgabb_tc_options &opt
     if (tune && ml.kind().nparts == 1 && ml.items() > 0) {
         const uint64_t per_item = mt.walked / static_cast<uint64_t>(ml.items());
         char key[160];
-        snprintf(key, sizeof key, "tc_graphs/G%d/T%d/I%d/W%d/S%d/K%d/O%d", bit_width_u64(merged.size()),
+        snprintf(key, sizeof key, "tc_graphs/" PGABB_TUNE_KERNELS "/G%d/T%d/I%d/W%d/S%d/K%d/O%d", bit_width_u64(merged.size()),
                  bit_width_u64(ml.tasks()), bit_width_u64(ml.items()), bit_width_u64(per_item),
                  bit_width_u64(mt.max_st), ml.kind().mode, orient);
         std::vector<int> v;
