@@ -68,19 +68,6 @@ struct BspSeg {
     int32_t base_y;  // rank of local id 0 on the entry side
 };
 
-// Sum of v over the workgroup (kBB threads, all of which call this),
-// returned to thread 0.
-__device__ __forceinline__ unsigned long long block_sum(unsigned long long v) {
-    __shared__ unsigned long long s_part[kBB / kWave];
-    v = wave_sum(v);
-    if (lane_id() == 0) s_part[threadIdx.x / kWave] = v;
-    __syncthreads();
-    unsigned long long t = 0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < kBB / kWave; ++w) t += s_part[w];
-    return t;
-}
-
 // Last segment s with pre[s] <= q (pre[0] = 0 <= q < pre[nseg]).
 __device__ __forceinline__ int32_t find_seg(const int64_t *__restrict__ pre, int32_t nseg, int64_t q) {
     int32_t lo = 0, hi = nseg - 1;
@@ -277,7 +264,7 @@ __global__ __launch_bounds__(kBB) void k_sv_minid(const int32_t *__restrict__ C,
             atomicMin(&minid[root], static_cast<int32_t>(v));
         c += ok && C[v] == v ? 1u : 0u;
     }
-    const unsigned long long sum = block_sum(static_cast<unsigned long long>(c));
+    const unsigned long long sum = group_sum(static_cast<unsigned long long>(c));
     if (threadIdx.x == 0 && sum) atomicAdd(roots, sum);  // one atomic per workgroup, at most 512
 }
 
