@@ -464,18 +464,23 @@ pgabb_status pgabb_graph_4list_counts(const pgabb_graph *g, int64_t *num_lists, 
 
 /*
  * Connected components (the Shiloach-Vishkin example of PGAbB Section 3.4,
- * single-block bulk-synchronous mode of Section 3.2) over the graph's device
- * blocks: even iterations hook, for every edge whose endpoints point to
- * different roots, the larger root under the smaller; odd iterations link
- * every vertex to its root by pointer jumping; the iterations end after a
- * hooking pass that hooked nothing.  A graph that was never partitioned is
- * partitioned with p = 1 first.
+ * bulk-synchronous mode of Section 3.2), in hooking iterations, each followed
+ * by one that links every vertex to its root by pointer jumping.  The first
+ * hooks every vertex under its highest neighbour, the second follows each row's
+ * last entry but one, the third every edge; for an edge whose endpoints point
+ * to different roots the lower-ranked one goes under the other, tried again
+ * where another edge got there first, so no edge is left between two trees.
+ * The passes read the rows of the oriented graph, not the blocks; the call has
+ * the same demands on the partition as pgabb_pagerank: a graph that was never
+ * partitioned is partitioned with p = 1 first, and one whose blocks a streamed
+ * count moved to host memory is refused.
  *   label          : n int32; label[v] = the smallest input id in v's
  *                    component (isolated vertices label themselves).  Host
  *                    memory, or device memory with PGABB_SUPPORT_ON_DEVICE;
  *                    complete when the call returns.  NULL allowed if n = 0.
  *   num_components : optional; components, isolated vertices included
- *   iterations     : optional; hooking plus linking iterations run (even)
+ *   iterations     : optional; hooking plus linking iterations run: 6, or 2
+ *                    for a graph without edges (0 if n = 0)
  * pgabb_graph_info_get then reports the call's time (t_count_ms), its kernel
  * time and the iterations as launches.
  * Errors: EINVAL (NULL graph, NULL label with n > 0, unknown flags), ESTATE

@@ -344,7 +344,7 @@ class Graph:
         return keep[:m], int(left.value), int(rounds.value)
 
     def components(self):
-        """Connected components (Shiloach-Vishkin over the blocks): a numpy
+        """Connected components (Shiloach-Vishkin over the rows): a numpy
         int32 array label[v] = smallest input id in v's component, the
         number of components and the iterations run."""
         n = self.info()["n"]

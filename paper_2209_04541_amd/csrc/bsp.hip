@@ -1,7 +1,7 @@
-// Single-block bulk-synchronous computations over the block partition
-// (PGAbB Section 3.2: every iteration visits every edge, and block-lists of
-// one block suffice).  Two of the paper's examples run here on the blocks
-// the triangle count uses:
+// Single-block bulk-synchronous computations (PGAbB Section 3.2: every
+// iteration visits every edge, and block-lists of one block suffice).  Two of
+// the paper's examples, the first over the rows of the oriented graph, the
+// second over the blocks the triangle count uses:
 //
 //   * connected components by Shiloach-Vishkin (Section 3.4): hooking
 //     iterations put the trees of an edge's ends under one root, linking
@@ -298,8 +298,8 @@ __global__ __launch_bounds__(kBB) void k_sv_label(const int32_t *__restrict__ C,
 // time).
 //
 // (PageRank walks the items in block order, grid-stride: dealt to per-XCD
-// queues by gather stripe, as the hooking pass is, an iteration on R-MAT
-// scale 20 took 0.81 ms against 0.72 ms.)
+// queues by the stripe they gather from, one item per lane, an iteration on
+// R-MAT scale 20 took 0.81 ms against 0.72 ms.)
 // The pull: each lane adds up its segment's shares and adds them to its
 // item's sum in LDS, and every item adds its sum to acc[x] once.
 __global__ __launch_bounds__(kBB) void k_pr_pull(const BspSeg *__restrict__ segs, const int64_t *__restrict__ pre,

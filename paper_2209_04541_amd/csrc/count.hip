@@ -79,7 +79,9 @@ void launch_mode(const CountArgs &a, int mode, int lds_words, int waves, hipStre
 
 }  // namespace
 
-// The hash class that keeps eight waves per SIMD.
+// The hash class that keeps seven waves per SIMD: a wave's region, its 64 words
+// of list positions and a quarter of the workgroup's 1 KB of counts, 28 times in
+// the 160 KB of a CU.
 constexpr int kSmallWords = 1280;
 
 int choose_lds_words(int32_t mode, int32_t max_stage_len, int32_t max_width_k) {
@@ -93,8 +95,7 @@ int choose_lds_words(int32_t mode, int32_t max_stage_len, int32_t max_width_k) {
     }
     if (mode == kModeHash) {
         // table of at least 1.5 x the longest staged row (load <= 2/3); at
-        // least 1280 words, the most that still keeps eight waves per SIMD
-        // (32 waves x 1280 words = 160 KB of LDS per CU)
+        // least 1280 words, the most that still keeps seven waves per SIMD
         const int64_t need = (3 * static_cast<int64_t>(max_stage_len) + 1) / 2;
         for (int c = 0; c < 5; ++c)
             if (need <= kTable[c]) return std::max(kClass[c], 1280);

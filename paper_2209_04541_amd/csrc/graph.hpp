@@ -200,7 +200,8 @@ double quad_rows(pgabb_graph *g, std::vector<uint64_t> &per_list);
 uint64_t quad_rows_count(const std::vector<uint64_t> &per_list, const std::array<int32_t, 4> &q);
 // Moves the device block arena to the pinned host store (once per partition).
 void move_blocks_to_host(pgabb_graph *g);
-// Connected components by Shiloach-Vishkin over the device blocks:
+// Connected components by Shiloach-Vishkin over the rows of the oriented graph
+// (the graph is partitioned and its blocks in device memory, or it is refused):
 // label[v] = smallest input id of v's component; returns the number of
 // components.
 int64_t components(pgabb_graph *g, int32_t *label, bool on_device, int32_t *iterations);

@@ -15,11 +15,11 @@ constexpr int SC_ITEMS = 8;
 constexpr int SC_TILE = SC_BLOCK * SC_ITEMS;
 
 // Up to this many tiles a workgroup of the second launch adds up the sums of
-// the tiles before its own itself (at most 64 KB read from L2), so a scan is
-// two launches; above, the sums are scanned first.
+// the tiles before its own itself (from L2: at most 64 KB, 128 of 64-bit sums),
+// so a scan is two launches; above, the sums are scanned first.
 constexpr int64_t SC_DIRECT = 16384;
 // Up to this many tiles, out not aliasing in, one launch does it all: a
-// workgroup adds up the input before its own tile (at most 64 K values).  A
+// workgroup adds up the input before its own tile (at most 32 K values).  A
 // small scan is bound by its launches.
 constexpr int64_t SC_SMALL = 16;
 

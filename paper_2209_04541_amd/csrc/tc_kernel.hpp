@@ -47,7 +47,9 @@ __device__ __forceinline__ void tc_flush(unsigned long long *__restrict__ counts
 // Seven waves per SIMD, the most that regions of 1280 words (and 64 of list
 // positions) leave room for in LDS; left alone the compiler takes 75
 // registers, six waves (R-MAT scale 20 in 32 x 32 blocks 3.23 against 2.96
-// ms, a random geometric graph of 400,001 vertices 622 against 607 us).
+// ms, a random geometric graph of 400,001 vertices 622 against 607 us).  The
+// price is at most one spilled register at the default shape, up to 17 with
+// two segments per lane.
 template <int MODE, int LDS_WORDS, int WAVES, int UNROLL, int ORIENT, bool FILTER = false>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(LDS_WORDS <= 1280 ? 7 : 4)))
 void k_tc_tasks(CountArgs a) {
