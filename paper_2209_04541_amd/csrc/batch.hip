@@ -728,6 +728,15 @@ using namespace pgabb;
 namespace pgabb {
 pgabb_status capture_status(const Error &e);
 hipStream_t library_stream();
+void forget_caller_stream(hipStream_t s) noexcept;
+
+static void drop(pgabb_batch *b) {
+    if (!b) return;
+    const hipStream_t s = b->stream;
+    (void)hipStreamSynchronize(s);
+    delete b;
+    forget_caller_stream(s);
+}
 }
 
 PGABB_API pgabb_status pgabb_batch_create(int64_t num_graphs, const int32_t *n, const int64_t *edge_off,
@@ -761,10 +770,10 @@ PGABB_API pgabb_status pgabb_batch_create(int64_t num_graphs, const int32_t *n, 
         *out = b;
         return capture_status(Error{PGABB_OK, ""});
     } catch (const Error &e) {
-        delete b;
+        drop(b);
         return capture_status(e);
     } catch (...) {
-        delete b;
+        drop(b);
         return capture_status(Error{PGABB_EDEVICE, "unexpected internal error"});
     }
 }
@@ -813,7 +822,5 @@ PGABB_API pgabb_status pgabb_batch_launch_shape(const pgabb_batch *b, int32_t *k
 }
 
 PGABB_API void pgabb_batch_destroy(pgabb_batch *b) {
-    if (!b) return;
-    (void)hipStreamSynchronize(b->stream);
-    delete b;
+    drop(b);
 }

@@ -65,6 +65,23 @@ hipStream_t library_stream() {
 
 pgabb_status capture_status(const Error &e) { return set_err(e.status, e.message); }
 
+// A graph or batch on the caller's stream has ended: the stream's owner may
+// destroy it now.
+void forget_caller_stream(hipStream_t s) noexcept {
+    try {
+        if (s && s != library_stream()) forget_stream(s);
+    } catch (...) {
+    }
+}
+
+static void drop(pgabb_graph *g) {
+    if (!g) return;
+    const hipStream_t s = g->stream;
+    (void)hipStreamSynchronize(s);
+    delete g;
+    forget_caller_stream(s);
+}
+
 }  // namespace pgabb
 
 using namespace pgabb;
@@ -156,15 +173,15 @@ PGABB_API pgabb_status pgabb_graph_from_edges(int32_t n, int64_t m, const int32_
     return set_ok();
     }
     catch (const Error &e) {
-        delete g;
+        drop(g);
         return set_err(e.status, e.message);
     }
     catch (const std::bad_alloc &) {
-        delete g;
+        drop(g);
         return set_err(PGABB_ENOMEM, "host allocation failed");
     }
     catch (...) {
-        delete g;
+        drop(g);
         return set_err(PGABB_EDEVICE, "unexpected internal error");
     }
 }
@@ -498,8 +515,7 @@ PGABB_API pgabb_status pgabb_graph_task_counts(const pgabb_graph *g, int32_t *ij
 PGABB_API void pgabb_graph_destroy(pgabb_graph *g) {
     if (!g) return;
     try {
-        (void)hipStreamSynchronize(g->stream);
-        delete g;
+        drop(g);
     } catch (...) {
     }
 }

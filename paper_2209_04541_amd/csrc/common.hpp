@@ -48,6 +48,9 @@ void dfree(void *p, hipStream_t s) noexcept;
 // block once the work enqueued on s so far has finished with it.
 void *halloc(size_t bytes);
 void hfree(void *p, hipStream_t s) noexcept;
+// Waits for s and frees the caches' blocks of the events that were recorded on
+// it: called before s is destroyed, or when its owner may destroy it.
+void forget_stream(hipStream_t s) noexcept;
 void set_allocator_hook(pgabb_alloc_fn fa, pgabb_free_fn ff, void *ctx);
 void release_cached_memory();
 size_t cached_bytes(bool host);

@@ -13,6 +13,10 @@
 //    waits for that event on its own stream (hipStreamWaitEvent) unless the
 //    event has already completed, so reuse is ordered after every earlier use
 //    whatever stream takes the block;
+//  - an event is not asked or waited for once the stream that it was recorded
+//    on is gone: before a stream is destroyed, or may be (a server's streams, a
+//    caller's after its graph), forget_stream takes the events of its blocks
+//    away, which are free from then on;
 //  - pinned host blocks (for small copies between host tables and the
 //    device, which would otherwise be pageable and synchronous, and for the
 //    host block store of a streamed graph) work the same way, except that
@@ -53,7 +57,9 @@ size_t size_class(size_t b) {
 
 struct FreeBlock {
     void *p;
-    hipEvent_t ev;
+    hipEvent_t ev;  // nullptr: the last use is known to be over
+    hipStream_t s;  // that ev was recorded on
+    bool over() const { return !ev || hipEventQuery(ev) == hipSuccess; }
 };
 
 struct Cache {
@@ -86,9 +92,11 @@ struct Cache {
     void trim(size_t keep) {
         while (cached > keep && !free.empty()) {
             auto it = std::prev(free.end());
-            (void)hipEventSynchronize(it->second.ev);
+            if (it->second.ev) {
+                (void)hipEventSynchronize(it->second.ev);
+                events.push_back(it->second.ev);
+            }
             hip_free(it->second.p);
-            events.push_back(it->second.ev);
             cached -= it->first;
             free.erase(it);
         }
@@ -131,14 +139,14 @@ Cache &host_cache() {
 // stream `s` is made to wait for the block's last free; for host blocks the
 // host waits.
 void *take(Cache &c, size_t cls, hipStream_t s) {
-    FreeBlock fb{nullptr, nullptr};
+    FreeBlock fb{nullptr, nullptr, nullptr};
     {
         std::lock_guard<std::mutex> lk(c.mu);
         auto range = c.free.equal_range(cls);
         if (range.first == range.second) return nullptr;
         auto pick = range.first;
         for (auto it = range.first; it != range.second; ++it)
-            if (hipEventQuery(it->second.ev) == hipSuccess) {
+            if (it->second.over()) {
                 pick = it;
                 break;
             }
@@ -147,13 +155,15 @@ void *take(Cache &c, size_t cls, hipStream_t s) {
         c.cached -= cls;
         c.live[fb.p] = cls;
     }
-    if (hipEventQuery(fb.ev) != hipSuccess) {
+    if (!fb.over()) {
         if (c.host) PGABB_HIP(hipEventSynchronize(fb.ev));
         else PGABB_HIP(hipStreamWaitEvent(s, fb.ev, 0));
     }
     (void)hipGetLastError();
-    std::lock_guard<std::mutex> lk(c.mu);
-    c.events.push_back(fb.ev);
+    if (fb.ev) {
+        std::lock_guard<std::mutex> lk(c.mu);
+        c.events.push_back(fb.ev);
+    }
     return fb.p;
 }
 
@@ -192,8 +202,9 @@ bool give_back(Cache &c, void *p, hipStream_t s) {
         (void)hipDeviceSynchronize();
         (void)hipEventRecord(ev, nullptr);
         (void)hipGetLastError();
+        s = nullptr;
     }
-    c.free.insert({cls, FreeBlock{p, ev}});
+    c.free.insert({cls, FreeBlock{p, ev, s}});
     c.cached += cls;
     if (c.cached > c.limit) c.trim(c.limit / 2);
     return true;
@@ -270,7 +281,7 @@ void hfree(void *p, hipStream_t s) noexcept {
     }
 }
 
-void release_cached_memory() {
+static std::vector<Cache *> all_caches() {
     std::vector<Cache *> all;
     {
         std::lock_guard<std::mutex> lk(g_caches_mu);
@@ -278,7 +289,29 @@ void release_cached_memory() {
             if (c) all.push_back(c.get());
     }
     all.push_back(&host_cache());
-    for (Cache *c : all) {
+    return all;
+}
+
+void forget_stream(hipStream_t s) noexcept {
+    try {
+        (void)hipStreamSynchronize(s);
+        for (Cache *c : all_caches()) {
+            std::lock_guard<std::mutex> lk(c->mu);
+            for (auto &f : c->free) {
+                FreeBlock &b = f.second;
+                // not over: another thread has used the stream since
+                if (b.s != s || !b.ev || !b.over()) continue;
+                c->events.push_back(b.ev);
+                b.ev = nullptr;
+            }
+        }
+        (void)hipGetLastError();
+    } catch (...) {
+    }
+}
+
+void release_cached_memory() {
+    for (Cache *c : all_caches()) {
         std::lock_guard<std::mutex> lk(c->mu);
         c->trim(0);
     }

@@ -423,7 +423,10 @@ PGABB_API void pgabb_server_destroy(pgabb_server *s) {
     for (auto &t : s->builders)
         if (t.joinable()) t.join();
     if (s->counter.joinable()) s->counter.join();
-    for (auto bs : s->build_streams) (void)hipStreamDestroy(bs);
-    (void)hipStreamDestroy(s->count_stream);
+    s->build_streams.push_back(s->count_stream);
+    for (auto bs : s->build_streams) {
+        forget_stream(bs);
+        (void)hipStreamDestroy(bs);
+    }
     delete s;
 }
