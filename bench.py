@@ -104,6 +104,8 @@ def roofline(W, m, kernel_ms, traffic_file):
     # row walks, A_ik[u] for column walks), every staged list and edge list
     # once (4 B each per oriented edge) and the two row offsets of the walked
     # endpoint (8 B per oriented edge)
+    # (a rate past the L2s: where the blocks fit the 256 MB Infinity Cache it is
+    # not HBM's, and may exceed what a device copy reaches)
     alg = 4 * W + 16 * m
     achieved = alg / (kernel_ms / 1e3) / 1e9
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -18,10 +18,12 @@
 //
 // This tests sum_a d+(a) (d+(a) - 1) / 2 pairs and reads no list per (a, b);
 // the kernel over block 4-lists walks A_kl[c] for every (a, b, c), 67.6 G
-// entries on R-MAT scale 20 against 1.2 G pairs here (155 -> 4.1 ms in one
+// entries on R-MAT scale 20 against 1.2 G pairs here (155 -> 4.3 ms in one
 // block, 187 -> 4.9 ms over 8 x 8; scale 18 over 4 x 4 26.8 -> 1.0 ms).
-// Bound by the pair tests' loads (step 1, mostly the binary searches) on
-// skewed graphs; step 2 issues about 12 instructions per 64 words of z's.
+// Bound by the pair tests' loads (step 1) on skewed graphs: on R-MAT scale 20
+// two thirds of their requests miss L2 (105 M lines, 3.1 TB/s) and the waves
+// wait 63 % of their cycles, the LDS is active 18 % and the VALU 45 %.  Step 2
+// issues about 12 instructions per 64 words of z's.
 //
 // Vertices with kWaveRow < d+ <= kGroupRow are taken by whole workgroups
 // (their matrix needs up to 128 KB of LDS), then those with 3 <= d+ <=
